@@ -10,10 +10,10 @@
 // "PVG1": a 32-byte header, block offsets, then per block comp_size, n, K
 // (bitmaps), the sizes n_1 .. n_{K-1}, and the bitmaps (LSB first).
 //
-// Encode: k_ghist (block histograms) -> host layout (the bitmap sizes follow
-// from the histograms) -> k_gbits, one workgroup per (block, bitmap): a
-// stable compaction of the block's values >= k gives each value's bit
-// position, and the values equal to k set their bit.
+// Encode: k_ghist (per slice, the values >= k) -> k_gprefix (per block, the
+// bitmap sizes and places) -> k_gscan (block offsets) -> k_ghead (stream
+// header, zeroed blocks) -> k_gsplit (per slice, every value's one 1 bit).
+// Nothing is planned on the host; the call waits once, for the length.
 // Decode: k_gdecode, one workgroup per block, tiles of kGT values: a
 // top-down count gives each bitmap's share of the tile (the 0 bits of one
 // bitmap's share are the next one's), then the bottom-up merge: a lane makes
@@ -36,7 +36,6 @@ constexpr uint32_t kGHdr = 32;
 constexpr int kGW = 64;
 constexpr int kGNT = 1024;                  // decode workgroup
 constexpr uint32_t kGT = 16 * kGNT;         // values per decode tile
-constexpr uint32_t kGSlice = 1u << 16;      // histogram slice
 
 // One Golomb job as the decode kernel sees it.
 struct GJob {
@@ -64,87 +63,322 @@ __device__ __forceinline__ uint32_t g_incl_scan(uint32_t v) {
   return v;
 }
 
+__device__ __forceinline__ void g_wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---------------------------------------------------------------------------
 // encode kernels
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_ghist(const uint8_t *in, uint64_t n, uint32_t bs, uint32_t spb,
-                                               uint32_t *hist) {
-  __shared__ uint32_t h[256];
+// A value v has one 1 bit, in bitmap v, at the position of the values >= v
+// before it; every other bit it adds is 0.  So the encoder never compacts the
+// values level by level: it computes that one position per value and sets
+// one bit.  The positions come from ranks inside a wave (ballots of v >= k),
+// the waves before it in the slice and the slices before it in the block
+// (per-slice counts of the values >= k, scanned per block).  Bound by the
+// vector instructions of the rank loop, about 25 per level up to the largest
+// of a wave's 256 values.  64 Mi values of mean code length 2 in 64 Ki blocks:
+// 165 us for the bits and 37 us for the counts, where a workgroup per (block,
+// bitmap) passing over the whole block took 3215 us, the counts 138 us and a
+// device copy per block header 1440 us; the call 6.1 -> 0.26 ms.
+constexpr uint32_t kGES = 8192;             // values per encode slice (one workgroup)
+constexpr int kGEN = 256;                   // its threads
+constexpr int kGEW = kGEN / kGW;            // its waves
+constexpr int kGSteps = kGES / (4 * kGEN);  // steps of 256 values (4 a lane) per wave
+constexpr int kGCopies = 16;                // histogram copies: lanes of equal values spread over them
+constexpr uint32_t kGStage = 4096;          // staged words: 16 KiB, mean code length up to about 14
+constexpr int kGScanNT = 1024;
+
+// One block's size (k_gprefix) and place (k_gscan).
+struct GBlk {
+  uint64_t comp;          // block bytes
+  uint32_t K, pad;        // bitmaps
+};
+
+// The 4 consecutive bytes at p + i (no alignment), zero past p + len.
+__device__ __forceinline__ uint32_t g_load4(const uint8_t *p, uint32_t i, uint32_t len) {
+  uint32_t w = 0;
+  if (i + 4 <= len) {
+    __builtin_memcpy(&w, p + i, 4);
+  } else {
+#pragma unroll
+    for (uint32_t e = 0; e < 3; ++e)
+      if (i + e < len) w |= static_cast<uint32_t>(p[i + e]) << (8 * e);
+  }
+  return w;
+}
+
+// Values present at i (0 to 4) before len.
+__device__ __forceinline__ uint32_t g_have(uint32_t i, uint32_t len) {
+  return i >= len ? 0u : len - i >= 4 ? 4u : len - i;
+}
+
+// Exclusive sum over the workgroup's kGEN threads; *total gets the sum.
+template <int NT>
+__device__ __forceinline__ uint64_t g_block_scan(uint64_t v, uint64_t *part, uint64_t *total) {
+  const uint32_t wave = threadIdx.x >> 6, lane = __lane_id();
+  uint64_t x = v;
+#pragma unroll
+  for (int o = 1; o < kGW; o <<= 1) {
+    const uint64_t y = __shfl_up(x, o, kGW);
+    if (lane >= static_cast<uint32_t>(o)) x += y;
+  }
+  if (lane == kGW - 1) part[wave] = x;
+  __syncthreads();
+  uint64_t before = 0, all = 0;
+  for (int w = 0; w < NT / kGW; ++w) {
+    const uint64_t p = part[w];
+    before += static_cast<uint32_t>(w) < wave ? p : 0u;
+    all += p;
+  }
+  *total = all;
+  __syncthreads();
+  return before + x - v;
+}
+
+// Row of slice blockIdx.x: entry k = its values >= k.
+__global__ __launch_bounds__(kGEN) void k_ghist(const uint8_t *in, uint64_t n, uint32_t bs, uint32_t spb,
+                                                uint32_t *rows) {
+  __shared__ uint32_t h[kGCopies][257];
+  __shared__ uint64_t part[kGEW];
   const uint32_t tid = threadIdx.x;
-  h[tid] = 0;
+  for (uint32_t i = tid; i < kGCopies * 257; i += kGEN) (&h[0][0])[i] = 0;
   __syncthreads();
   const uint64_t b = blockIdx.x / spb, sl = blockIdx.x % spb;
   const uint64_t b0 = b * bs, b1 = b0 + bs < n ? b0 + bs : n;
-  const uint64_t s0 = b0 + sl * kGSlice, s1 = s0 + kGSlice < b1 ? s0 + kGSlice : b1;
-  for (uint64_t i = s0 + tid; i < s1; i += 256) atomicAdd(&h[in[i]], 1u);
+  const uint64_t s0 = b0 + sl * kGES, s1 = s0 + kGES < b1 ? s0 + kGES : b1;
+  const uint32_t len = s0 < s1 ? static_cast<uint32_t>(s1 - s0) : 0u;
+  uint32_t *hc = h[tid % kGCopies];
+#pragma unroll
+  for (uint32_t t = 0; t < kGES / (4 * kGEN); ++t) {
+    const uint32_t i = 4 * (kGEN * t + tid);
+    const uint32_t w = g_load4(in + s0, i, len), have = g_have(i, len);
+#pragma unroll
+    for (uint32_t e = 0; e < 4; ++e)
+      if (e < have) atomicAdd(&hc[(w >> (8 * e)) & 255], 1u);
+  }
   __syncthreads();
-  if (h[tid]) atomicAdd(&hist[b * 256 + tid], h[tid]);
+  const uint32_t k = 255 - tid;              // a prefix sum over tid is a suffix sum over k
+  uint32_t c = 0;
+#pragma unroll
+  for (int j = 0; j < kGCopies; ++j) c += h[j][k];
+  uint64_t tot;
+  const uint64_t ex = g_block_scan<kGEN>(c, part, &tot);
+  rows[static_cast<uint64_t>(blockIdx.x) * 256 + k] = static_cast<uint32_t>(ex) + c;
 }
 
-// One workgroup per (block, bitmap k): the block's values in order, 1024 at
-// a time; a value >= k takes the next bit of bitmap k (wave ballot ranks +
-// the waves before it + the running count), and a value equal to k sets it.
-// The stream was zeroed, so bits are only ever ORed in.
-struct GLevel {
-  uint64_t in_off;        // first value of the block
-  uint64_t bit0;          // first bit of bitmap k in the stream
-  uint32_t n;             // values of the block
-  uint32_t k;
+// Per block: the slice rows become exclusive prefixes over the slices (16
+// rows read before any is rewritten), the totals are the bitmap sizes n_k,
+// and a scan of the bitmaps' bytes places them.
+__global__ __launch_bounds__(kGEN) void k_gprefix(uint32_t *rows, uint32_t spb, uint32_t *nk, uint64_t *boff,
+                                                  GBlk *blk) {
+  __shared__ uint64_t part[kGEW];
+  const uint64_t b = blockIdx.x;
+  const uint32_t k = threadIdx.x;
+  uint32_t *row = rows + b * spb * 256 + k;
+  uint32_t run = 0, s = 0;
+  for (; s + 16 <= spb; s += 16) {
+    uint32_t c[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) c[j] = row[256ull * (s + j)];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      row[256ull * (s + j)] = run;
+      run += c[j];
+    }
+  }
+  for (; s < spb; ++s) {
+    const uint32_t c = row[256ull * s];
+    row[256ull * s] = run;
+    run += c;
+  }
+  const uint32_t K = static_cast<uint32_t>(__syncthreads_count(run != 0));   // n_k never grows with k
+  uint64_t body;
+  const uint64_t off = g_block_scan<kGEN>((static_cast<uint64_t>(run) + 7) / 8, part, &body);
+  const uint64_t hlen = 12 + 4ull * (K ? K - 1 : 0);
+  nk[b * 256 + k] = run;
+  boff[b * 256 + k] = hlen + off;
+  if (k == 0) blk[b] = GBlk{hlen + body, K, 0};
+}
+
+// Block offsets in the stream (one workgroup, 1024 blocks at a time).
+__global__ __launch_bounds__(kGScanNT) void k_gscan(const GBlk *blk, uint32_t nb, uint64_t *off) {
+  __shared__ uint64_t part[kGScanNT / kGW];
+  uint64_t run = kGHdr + 8ull * (nb + 1ull);
+  for (uint64_t b0 = 0; b0 < nb; b0 += kGScanNT) {
+    const uint64_t b = b0 + threadIdx.x;
+    const uint64_t c = b < nb ? (blk[b].comp + 3) & ~3ull : 0u;
+    uint64_t tot;
+    const uint64_t ex = g_block_scan<kGScanNT>(c, part, &tot);
+    if (b < nb) off[b] = run + ex;
+    run += tot;
+  }
+  if (threadIdx.x == 0) off[nb] = run;
+}
+
+// Stream header and block table; the blocks' words are zeroed (the edges of
+// the bitmaps' slices are ORed in).  Nothing is written past out_cap.
+__global__ __launch_bounds__(256) void k_ghead(const uint64_t *off, uint32_t nb, uint64_t n, uint32_t bs,
+                                               uint32_t *out, uint64_t out_cap) {
+  const uint64_t total = off[nb];
+  if (total > out_cap) return;
+  const uint64_t step = static_cast<uint64_t>(gridDim.x) * blockDim.x;
+  const uint64_t t = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x;
+  const uint64_t w0 = (kGHdr + 8ull * (nb + 1ull)) / 4;
+  if (t == 0) {
+    out[0] = kGMagic;
+    out[1] = 1;
+    out[2] = static_cast<uint32_t>(n);
+    out[3] = static_cast<uint32_t>(n >> 32);
+    out[4] = bs;
+    out[5] = nb;
+    out[6] = out[7] = 0;
+  }
+  for (uint64_t b = t; b <= nb; b += step) reinterpret_cast<uint64_t *>(out + kGHdr / 4)[b] = off[b];
+  for (uint64_t w = w0 + t; w < total / 4; w += step) out[w] = 0;
+}
+
+struct GEncSmem {
+  uint32_t cur[kGEW][256];   // per wave: its values >= k so far; then the staged bit of its first one
+  uint64_t gw[256];          // stream word of the slice's first bit in bitmap k
+  uint32_t lw[256];          // its staged word
+  uint32_t nw[256];          // staged words of bitmap k
+  uint64_t part[kGEW];
+  uint32_t stage[kGStage];
 };
 
-__global__ __launch_bounds__(256) void k_gbits(const uint8_t *in, const GLevel *lv, uint32_t nlv,
-                                               uint32_t *out) {
-  if (blockIdx.x >= nlv) return;
-  __shared__ uint32_t wcnt[4];
-  __shared__ uint32_t run;
-  const GLevel L = lv[blockIdx.x];
+// Bits of one slice.  A wave owns kGSteps * 256 consecutive values, 4 a lane
+// per step.  For level k the ballots of v >= k give, by mbcnt, every lane's
+// count of values >= k before its own; the values equal to k keep it.  The
+// wave's running counts per level sit in LDS.  Then the slice's bitmaps are
+// staged in LDS at the alignment of their stream words, one atomicOr per
+// value, and go out as words: the first and last word of a bitmap's share
+// may belong to a neighbour too and are ORed, the others are stored.  A slice
+// of long codes that does not fit the stage sets its bits in the stream.
+__global__ __launch_bounds__(kGEN, 5) void k_gsplit(const uint8_t *in, uint64_t n, uint32_t bs, uint32_t spb,
+                                                 const uint32_t *rows, const uint32_t *nk,
+                                                 const uint64_t *boff, const GBlk *blk, const uint64_t *off,
+                                                 uint32_t nb, uint32_t *out, uint64_t out_cap) {
+  __shared__ GEncSmem sm;
+  if (off[nb] > out_cap) return;
   const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = __lane_id();
-  if (tid == 0) run = 0;
-  __syncthreads();
-  for (uint32_t c0 = 0; c0 < L.n; c0 += 1024) {
-    uint32_t v[4];
-    bool ge[4];
-    uint32_t mine = 0;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const uint32_t i = c0 + 4 * tid + u;
-      v[u] = i < L.n ? in[L.in_off + i] : 0u;
-      ge[u] = i < L.n && v[u] >= L.k;
-      mine += ge[u];
+  const uint64_t b = blockIdx.x / spb, sl = blockIdx.x % spb;
+  const uint64_t b0 = b * bs, b1 = b0 + bs < n ? b0 + bs : n;
+  const uint64_t s0 = b0 + sl * kGES, s1 = s0 + kGES < b1 ? s0 + kGES : b1;
+  if (sl == 0) {                              // block header: whole words
+    uint32_t *h = out + off[b] / 4;
+    const uint32_t K = blk[b].K;
+    if (tid == 0) {
+      h[0] = static_cast<uint32_t>(blk[b].comp);
+      h[1] = static_cast<uint32_t>(b1 - b0);
+      h[2] = K;
+    } else if (tid < K) {
+      h[2 + tid] = nk[b * 256 + tid];
     }
-    // exclusive prefix of the thread's count over the workgroup
-    const uint32_t inc = g_incl_scan(mine);
-    if (lane == kGW - 1) wcnt[wave] = inc;
-    __syncthreads();
-    uint32_t before = run + inc - mine;
-    for (uint32_t w = 0; w < wave; ++w) before += wcnt[w];
-    const uint32_t total = wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3];
+  }
+  if (s0 >= s1) return;
+  uint32_t *cur = sm.cur[wave];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (ge[u]) {
-        if (v[u] == L.k) {
-          const uint64_t bit = L.bit0 + before;
-          atomicOr(&out[bit >> 5], 1u << (bit & 31));
-        }
-        ++before;
+  for (int e = 0; e < 4; ++e) cur[kGW * e + lane] = 0;
+  g_wave_sync();
+  uint32_t vw[kGSteps];                       // 4 values a word
+  uint32_t pos[kGSteps][2];                   // two 16-bit positions a word
+  const uint32_t len = static_cast<uint32_t>(s1 - s0), i0 = wave * (256 * kGSteps) + 4 * lane;
+#pragma unroll
+  for (int t = 0; t < kGSteps; ++t) vw[t] = g_load4(in + s0, i0 + 256 * t, len);
+#pragma unroll
+  for (int t = 0; t < kGSteps; ++t) {
+    const uint32_t have = g_have(i0 + 256 * t, len);
+    int v[4];
+    uint32_t at[4], r[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (uint32_t e = 0; e < 4; ++e) {
+      const uint32_t x = (vw[t] >> (8 * e)) & 255;
+      at[e] = cur[x];
+      v[e] = e < have ? static_cast<int>(x) : -1;
+    }
+    g_wave_sync();
+    for (int k = 0; k < 256; ++k) {
+      uint64_t S[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) S[e] = __ballot(v[e] >= k);
+      const uint32_t all = static_cast<uint32_t>(__popcll(S[0]) + __popcll(S[1]) + __popcll(S[2]) + __popcll(S[3]));
+      if (all == 0) break;
+      uint32_t c = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        c = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(S[e] >> 32),
+                                      __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(S[e]), c));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        r[e] = v[e] == k ? c : r[e];
+        c += v[e] >= k ? 1u : 0u;
+      }
+      if (lane == 0) atomicAdd(&cur[k], all);   // no value back: the loop does not wait for it
+    }
+    g_wave_sync();
+    pos[t][0] = (at[0] + r[0]) | (at[1] + r[1]) << 16;
+    pos[t][1] = (at[2] + r[2]) | (at[3] + r[3]) << 16;
+    // the words as they are, opaque: otherwise the unpacked values and
+    // positions of all steps are kept for the placing below, and spilled
+    asm volatile("" : "+v"(vw[t]), "+v"(pos[t][0]), "+v"(pos[t][1]));
+  }
+  __syncthreads();
+  uint32_t words = 0, sh = 0, cw[kGEW], cnt = 0;
+  uint64_t gb = 0;
+  {
+    const uint32_t k = tid;
+#pragma unroll
+    for (int w = 0; w < kGEW; ++w) { cw[w] = sm.cur[w][k]; cnt += cw[w]; }
+    if (cnt) {
+      gb = 8 * (off[b] + boff[b * 256 + k]) + rows[static_cast<uint64_t>(blockIdx.x) * 256 + k];
+      sh = static_cast<uint32_t>(gb & 31);
+      words = (sh + cnt + 31) / 32;
+    }
+  }
+  const uint32_t Ks = static_cast<uint32_t>(__syncthreads_count(cnt != 0));
+  uint64_t tot;
+  const uint32_t lw = static_cast<uint32_t>(g_block_scan<kGEN>(words, sm.part, &tot));
+  {
+    uint32_t x = 32 * lw + sh;                // below 2^23: at most 8192 * 256 staged bits and the edges
+#pragma unroll
+    for (int w = 0; w < kGEW; ++w) { sm.cur[w][tid] = x; x += cw[w]; }
+    sm.gw[tid] = gb >> 5;
+    sm.lw[tid] = lw;
+    sm.nw[tid] = words;
+  }
+  const bool staged = tot <= kGStage;
+  if (staged)
+    for (uint32_t i = tid; i < tot; i += kGEN) sm.stage[i] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < kGSteps; ++t) {
+    const uint32_t have = g_have(i0 + 256 * t, len);
+#pragma unroll
+    for (uint32_t e = 0; e < 4; ++e) {
+      if (e >= have) continue;
+      const uint32_t k = (vw[t] >> (8 * e)) & 255;
+      const uint32_t x = cur[k] + ((pos[t][e >> 1] >> (16 * (e & 1))) & 0xFFFF);
+      if (staged) atomicOr(&sm.stage[x >> 5], 1u << (x & 31));
+      else atomicOr(&out[sm.gw[k] + ((x >> 5) - sm.lw[k])], 1u << (x & 31));
+    }
+  }
+  if (!staged) return;
+  __syncthreads();
+  for (uint32_t k = wave; k < Ks; k += kGEW) {
+    const uint32_t nw = sm.nw[k], l0 = sm.lw[k];
+    uint32_t *dst = out + sm.gw[k];
+    for (uint32_t j = lane; j < nw; j += kGW) {
+      const uint32_t w = sm.stage[l0 + j];
+      if (j == 0 || j == nw - 1) {
+        if (w) atomicOr(&dst[j], w);
+      } else {
+        dst[j] = w;
       }
     }
-    __syncthreads();
-    if (tid == 0) run += total;
-    __syncthreads();
   }
-}
-
-__global__ void k_gcopy(const uint8_t *src, uint64_t n, uint8_t *dst) {
-  for (uint64_t i = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; i < n;
-       i += static_cast<uint64_t>(gridDim.x) * blockDim.x)
-    dst[i] = src[i];
-}
-
-__global__ void k_gzero(uint32_t *p, uint64_t nw) {
-  for (uint64_t i = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; i < nw;
-       i += static_cast<uint64_t>(gridDim.x) * blockDim.x)
-    p[i] = 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -315,6 +549,26 @@ __global__ __launch_bounds__(kGNT) void k_gdecode(const GJob *jobs, const uint2 
 
 inline uint64_t galign(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
 
+// Encode workspace: slice rows, then per block the bitmap sizes, their
+// places, the block's size and its offset.
+struct GWs {
+  uint64_t rows, nk, boff, blk, off, total;
+  uint32_t spb;           // slices per block
+};
+GWs gws_layout(uint64_t n, uint32_t bs) {
+  GWs L{};
+  const uint64_t nb = div_up(n, bs);
+  L.spb = static_cast<uint32_t>(div_up(std::min<uint64_t>(n, bs), kGES));
+  uint64_t x = 0;
+  L.rows = x; x = galign(x + nb * L.spb * 1024, 256);
+  L.nk = x; x = galign(x + nb * 1024, 256);
+  L.boff = x; x = galign(x + nb * 2048, 256);
+  L.blk = x; x = galign(x + nb * sizeof(GBlk), 256);
+  L.off = x; x = galign(x + 8 * (nb + 1), 256);
+  L.total = x;
+  return L;
+}
+
 }  // namespace
 }  // namespace pivco
 
@@ -330,10 +584,7 @@ uint64_t pivco_golomb_encode_bound(uint64_t n, uint32_t block_size) {
 
 uint64_t pivco_golomb_encode_workspace(uint64_t n, uint32_t block_size) {
   if (block_size == 0) return 0;
-  const uint64_t nb = div_up(n, block_size);
-  // histograms, the (block, bitmap) list, staged headers
-  return galign(nb * 1024 + 16, 256) + galign(nb * 256 * sizeof(GLevel), 256) +
-         galign(kGHdr + 8 * (nb + 1) + nb * (12 + 4 * 255) + 64, 256);
+  return gws_layout(n, block_size).total;
 }
 
 pivco_status pivco_golomb_encode(const void *d_in, uint64_t n, uint32_t block_size, void *d_out,
@@ -341,89 +592,37 @@ pivco_status pivco_golomb_encode(const void *d_in, uint64_t n, uint32_t block_si
                                  hipStream_t s) {
   if (!h_out_len || block_size == 0 || (n && !d_in) || !d_out || (reinterpret_cast<uintptr_t>(d_out) & 15))
     return PIVCO_E_ARG;
-  const uint64_t nb = div_up(n, block_size);
-  if (nb > 0xFFFFFFFFull) return PIVCO_E_ARG;
-  if (!d_ws || ws_bytes < pivco_golomb_encode_workspace(n, block_size)) return PIVCO_E_CAPACITY;
+  const uint64_t nb64 = div_up(n, block_size);
+  if (nb64 > 0xFFFFFFFFull) return PIVCO_E_ARG;
+  const GWs L = gws_layout(n, block_size);
+  if (!d_ws || ws_bytes < L.total) return PIVCO_E_CAPACITY;
+  if (nb64 * L.spb > 0x7FFFFFFFull) return PIVCO_E_ARG;
+  const uint32_t nb = static_cast<uint32_t>(nb64), spb = L.spb;
+  const uint8_t *in = static_cast<const uint8_t *>(d_in);
   uint8_t *ws = static_cast<uint8_t *>(d_ws);
-  uint32_t *dh = reinterpret_cast<uint32_t *>(ws);
-  GLevel *dlv = reinterpret_cast<GLevel *>(ws + galign(nb * 1024 + 16, 256));
-  uint8_t *dstg = ws + galign(nb * 1024 + 16, 256) + galign(nb * 256 * sizeof(GLevel), 256);
-  std::vector<uint32_t> hist(nb * 256, 0);
+  uint32_t *rows = reinterpret_cast<uint32_t *>(ws + L.rows), *nk = reinterpret_cast<uint32_t *>(ws + L.nk);
+  uint64_t *boff = reinterpret_cast<uint64_t *>(ws + L.boff), *off = reinterpret_cast<uint64_t *>(ws + L.off);
+  GBlk *blk = reinterpret_cast<GBlk *>(ws + L.blk);
+  uint32_t *out = static_cast<uint32_t *>(d_out);
   if (nb) {
-    const uint32_t spb = static_cast<uint32_t>(div_up(block_size, kGSlice));
-    if (nb * spb > 0x7FFFFFFFull) return PIVCO_E_ARG;
-    hipLaunchKernelGGL(k_gzero, dim3(static_cast<uint32_t>(std::min<uint64_t>(4096, div_up(nb * 256, 256)))),
-                       dim3(256), 0, s, dh, nb * 256);
-    hipLaunchKernelGGL(k_ghist, dim3(static_cast<uint32_t>(nb * spb)), dim3(256), 0, s,
-                       static_cast<const uint8_t *>(d_in), n, block_size, spb, dh);
-    if (hipGetLastError() != hipSuccess) return PIVCO_E_DEVICE;
-    if (hipMemcpyAsync(hist.data(), dh, hist.size() * 4, hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-      return PIVCO_E_DEVICE;
+    hipLaunchKernelGGL(k_ghist, dim3(nb * spb), dim3(kGEN), 0, s, in, n, block_size, spb, rows);
+    hipLaunchKernelGGL(k_gprefix, dim3(nb), dim3(kGEN), 0, s, rows, spb, nk, boff, blk);
   }
-  // layout from the histograms: bitmap k of a block holds its values >= k
-  std::vector<uint8_t> stg(kGHdr + 8 * (nb + 1), 0);
-  std::vector<GLevel> lv;
-  const uint32_t w0[6] = {kGMagic, 1u, static_cast<uint32_t>(n), static_cast<uint32_t>(n >> 32), block_size,
-                          static_cast<uint32_t>(nb)};
-  std::memcpy(stg.data(), w0, sizeof(w0));
-  uint64_t off = stg.size();
-  std::vector<std::pair<uint64_t, uint64_t>> hdrs;   // (staging offset, stream offset) of block headers
-  for (uint64_t b = 0; b < nb; ++b) {
-    const uint32_t bn = static_cast<uint32_t>(std::min<uint64_t>(block_size, n - b * block_size));
-    const uint32_t *h = &hist[b * 256];
-    uint32_t K = 0;
-    for (uint32_t v = 0; v < 256; ++v) if (h[v]) K = v + 1;
-    uint64_t nk[257] = {0};
-    for (int v = 255; v >= 0; --v) nk[v] = nk[v + 1] + h[v];
-    const uint64_t hlen = 12 + 4ull * (K ? K - 1 : 0);
-    uint64_t body = 0;
-    for (uint32_t k = 0; k < K; ++k) {
-      lv.push_back(GLevel{b * block_size, 8 * (off + hlen + body), bn, k});
-      body += (nk[k] + 7) / 8;
-    }
-    const uint64_t comp = hlen + body;
-    std::memcpy(&stg[kGHdr + 8 * b], &off, 8);
-    const uint64_t hs = stg.size();
-    stg.resize(hs + hlen, 0);
-    const uint32_t c32 = static_cast<uint32_t>(comp);
-    std::memcpy(&stg[hs], &c32, 4);
-    std::memcpy(&stg[hs + 4], &bn, 4);
-    stg[hs + 8] = static_cast<uint8_t>(K);
-    stg[hs + 9] = static_cast<uint8_t>(K >> 8);
-    for (uint32_t k = 1; k < K; ++k) {
-      const uint32_t v = static_cast<uint32_t>(nk[k]);
-      std::memcpy(&stg[hs + 12 + 4 * (k - 1)], &v, 4);
-    }
-    hdrs.push_back({hs, off});
-    off += galign(comp, 4);
-  }
-  std::memcpy(&stg[kGHdr + 8 * nb], &off, 8);
-  if (off > out_cap) return PIVCO_E_CAPACITY;
-  uint8_t *out = static_cast<uint8_t *>(d_out);
-  if (hipMemcpyAsync(dstg, stg.data(), stg.size(), hipMemcpyHostToDevice, s) != hipSuccess ||
-      (lv.size() && hipMemcpyAsync(dlv, lv.data(), lv.size() * sizeof(GLevel), hipMemcpyHostToDevice, s) != hipSuccess))
+  hipLaunchKernelGGL(k_gscan, dim3(1), dim3(kGScanNT), 0, s, blk, nb, off);
+  // the stream is at most the bound: 8 words a thread when it is that large
+  const uint64_t most = pivco_golomb_encode_bound(n, block_size) / 4;
+  hipLaunchKernelGGL(k_ghead, dim3(static_cast<uint32_t>(std::min<uint64_t>(2048, div_up(most, 2048)))),
+                     dim3(256), 0, s, off, nb, n, block_size, out, out_cap);
+  if (nb)
+    hipLaunchKernelGGL(k_gsplit, dim3(nb * spb), dim3(kGEN), 0, s, in, n, block_size, spb, rows, nk, boff, blk,
+                       off, nb, out, out_cap);
+  if (hipGetLastError() != hipSuccess) return PIVCO_E_DEVICE;
+  uint64_t total = 0;
+  if (hipMemcpyAsync(&total, off + nb, 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
+      hipStreamSynchronize(s) != hipSuccess)
     return PIVCO_E_DEVICE;
-  hipLaunchKernelGGL(k_gzero, dim3(static_cast<uint32_t>(std::min<uint64_t>(8192, div_up(off / 4 + 1, 256)))),
-                     dim3(256), 0, s, reinterpret_cast<uint32_t *>(out), off / 4);
-  // stream header and tables, then every block header (one copy each)
-  hipLaunchKernelGGL(k_gcopy, dim3(static_cast<uint32_t>(std::min<uint64_t>(4096, div_up(kGHdr + 8 * (nb + 1), 256)))),
-                     dim3(256), 0, s, dstg, kGHdr + 8 * (nb + 1), out);
-  // block headers (small): one device-to-device copy each
-  for (size_t i = 0; i < hdrs.size(); ++i) {
-    const uint64_t hs = hdrs[i].first;
-    const uint64_t he = i + 1 < hdrs.size() ? hdrs[i + 1].first : stg.size();
-    if (hipMemcpyAsync(out + hdrs[i].second, dstg + hs, he - hs, hipMemcpyDeviceToDevice, s) != hipSuccess)
-      return PIVCO_E_DEVICE;
-  }
-  if (!lv.empty()) {
-    hipLaunchKernelGGL(k_gbits, dim3(static_cast<uint32_t>(lv.size())), dim3(256), 0, s,
-                       static_cast<const uint8_t *>(d_in), dlv, static_cast<uint32_t>(lv.size()),
-                       reinterpret_cast<uint32_t *>(out));
-    if (hipGetLastError() != hipSuccess) return PIVCO_E_DEVICE;
-  }
-  if (hipStreamSynchronize(s) != hipSuccess) return PIVCO_E_DEVICE;
-  *h_out_len = off;
+  if (total > out_cap) return PIVCO_E_CAPACITY;
+  *h_out_len = total;
   return PIVCO_OK;
 }
 
