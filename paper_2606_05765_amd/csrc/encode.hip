@@ -5,8 +5,7 @@
 // through it, emits one bit per symbol (its bitmap) and partitions the
 // symbols between its children (the enc_partition primitives of Table 11).
 // The driver:
-//   1. k_hist        symbol histogram of every block and of every 4Ki-symbol
-//                    slice of it (end-to-end encode time is dominated by this
+//   1. k_hist        symbol histogram of every block and of every slice of it (end-to-end encode time is dominated by this
 //                    count, Sec. 4); k_slice_prefix turns the slice counts
 //                    into per-slice prefixes;
 //   2. k_tree        optimal length-limited lengths per block (package-merge,
@@ -17,13 +16,13 @@
 //                    rANS selection rule, body sizes and offsets, and the
 //                    block header bytes;
 //   4. k_scan        offsets of every block's areas (exclusive scans);
-//   5. k_split       per slice of a block: per level, one wave per node turns
-//                    64 symbols at a time into a 64-bit ballot of code bits
-//                    (LSB first = stream order), ORs it into the node's
-//                    bitmap -- raw nodes straight into the block's byte-packed
-//                    raw image, rANS nodes into word-aligned scratch -- and
-//                    scatters the symbols to the children's segments in LDS
-//                    with ballot + mbcnt ranks (stable);
+//   5. k_split       per slice of a block: per level, every wave turns 64
+//                    symbols at a time of the level's array into a 64-bit
+//                    ballot of code bits (LSB first = stream order) and moves
+//                    them to the children's places in LDS (stable); then the
+//                    nodes' bits go out word by word -- raw nodes straight
+//                    into the block's byte-packed raw image, rANS nodes into
+//                    word-aligned scratch;
 //   6. k_chunks      the entropy-coded chunk jobs; k_rans_enc codes them
 //                    (32-lane interleaved binary rANS, one wave per chunk,
 //                    steps in reverse order), or k_fse_enc (byte tANS);
@@ -51,9 +50,9 @@ bool tree_is_complete(const uint8_t len[256], uint32_t max_len);
 namespace {
 
 constexpr int kWaveE = 64;
-constexpr uint32_t kHistSlice = 1u << 12;   // one split tile: a 4 MiB block is 1024 workgroups
-constexpr int kSplitNT = 256;
-constexpr uint32_t kSplitT = 4096;      // input symbols per tile
+// Symbols of a slice (a histogram row, a split workgroup): 16 per thread of
+// the split kernel.
+constexpr uint32_t kSliceSmall = 1u << 12, kSliceLarge = 1u << 13;
 constexpr uint32_t kHdrStride = 1216;   // block header bytes: 12 + 128 + 32 + 4 * 255 <= this
 constexpr uint32_t kLayoutWaves = 4;
 constexpr uint32_t kAsmSeg = 16384;     // output words per assembling workgroup
@@ -62,41 +61,34 @@ constexpr uint32_t kScanNT = 1024;
 constexpr uint32_t kErrArg = 1;          // a block's tree: PIVCO_E_ARG
 constexpr uint32_t kErrUnsupported = 2;  // a tANS cursor stream past its 16-bit length: PIVCO_E_UNSUPPORTED
 
-// Per-block description for the split kernel, written by k_layout.
+// Per-block description for the split kernel, written by k_layout.  Leaves
+// are numbered in code order (of the left-justified codes), so the symbols
+// that pass a node are the leaves of one interval.
 struct EncBlock {
   uint64_t in_off;        // first input symbol
   uint32_t n;             // symbols
   uint32_t I;             // internal nodes (0: constant block, nothing to split)
   uint32_t maxlen;        // node levels
-  uint32_t pad;
-  uint32_t lvl[16];       // first node id of each depth
-  uint32_t off[17];       // internal node at depth d with code prefix p: lvl[d] + p - off[d]
-  uint32_t code[256];     // code | len << 16 | D << 20 | group node << 24: a symbol
-                          // whose group of 2^D >= 2 symbols is a node ends its
-                          // path there (D = 0: no such node)
-  uint16_t child[256][2]; // internal id or 0x8000 | symbol (0x8000 for a flat node's)
+  uint32_t nleaf;         // symbols with a code
+  uint32_t lvl[18];       // first node id of each depth
+  int32_t kbase[16];      // node at depth d with code prefix p: slot p + kbase[d] (in the
+                          // split kernel's tables; a prefix without a node takes one too
+                          // where a flat-subtree tree has a single leaf among the nodes)
+  uint32_t nfl[16];       // flat nodes per level (the level's first nodes)
   uint32_t bit[256];      // node's first bit: in the block's raw image (raw
                           // node) or in its rANS bitmap words (rANS node)
   uint32_t kind[8];       // bit i: node i is rANS-coded
+  uint16_t pay[256];      // a symbol's code, left-justified in 16 bits
+  uint16_t lo[256];       // node's leaves [lo, hi), those of its right child
+  uint16_t mid[256];      // [mid, hi)
+  uint16_t hi[256];
+  uint16_t child[256][2]; // internal id, or 0x8000 for a leaf
+  uint16_t slot[256];     // node's slot
+  uint8_t leaf[256];      // leaf of each symbol (255, never a leaf then, without a code)
+  uint8_t depth[256];     // node's level
   uint8_t fd[256];        // flat node: its depth D (>= 2), 0 for binary nodes
-  uint32_t pad2;
 };
-static_assert(sizeof(EncBlock) % 16 == 0, "EncBlock copies in 16-byte units");
-
-// Node on a symbol's path at depth d (cl = EncBlock::code of the symbol; lvl
-// and off as in EncBlock):
-// above the symbol's group the internal node of its code prefix, at the
-// group's depth the group node.  The path has len - D + (D ? 1 : 0) nodes.
-__device__ __forceinline__ uint32_t path_node(const uint32_t *lvl, const uint32_t *off, uint32_t cl, uint32_t d) {
-  const uint32_t len = (cl >> 16) & 15, D = (cl >> 20) & 15;
-  if (D && d == len - D) return cl >> 24;
-  return lvl[d] + ((cl & 0xFFFF) >> (len - d)) - off[d];
-}
-
-__device__ __forceinline__ uint32_t path_len(uint32_t cl) {
-  const uint32_t len = (cl >> 16) & 15, D = (cl >> 20) & 15;
-  return len - D + (D ? 1u : 0u);
-}
+static_assert(sizeof(EncBlock) % 16 == 0, "EncBlock areas stay 16-byte aligned");
 
 // Per-block layout (k_layout), offsets (k_scan) and size (k_sizes, k_scan2).
 struct BlockLay {
@@ -226,11 +218,11 @@ __global__ void k_zero_areas(uint32_t *img, uint32_t *rbm, const Totals *tot) {
   }
 }
 
-// Histogram of every block, one workgroup per slice of kHistSlice symbols:
+// Histogram of every block, one workgroup per slice:
 // the slice's counts go to its own row of slh (the split kernel's slices
 // start at the same boundaries); a block of one slice also writes them to
 // its row of hist (k_slice_prefix writes the totals of larger blocks).
-__global__ __launch_bounds__(256) void k_hist(const uint8_t *in, uint64_t n, uint32_t bs,
+__global__ __launch_bounds__(256) void k_hist(const uint8_t *in, uint64_t n, uint32_t bs, uint32_t slice,
                                               uint32_t spb, uint32_t *hist, uint32_t *slh) {
   __shared__ uint32_t h[4][256];
   const int tid = threadIdx.x, w = tid >> 6;
@@ -239,8 +231,8 @@ __global__ __launch_bounds__(256) void k_hist(const uint8_t *in, uint64_t n, uin
   const uint64_t b = blockIdx.x / spb, sl = blockIdx.x % spb;
   const uint64_t bstart = b * bs;
   const uint64_t bend = bstart + bs < n ? bstart + bs : n;
-  const uint64_t s0 = bstart + sl * kHistSlice;
-  const uint64_t s1 = s0 + kHistSlice < bend ? s0 + kHistSlice : bend;
+  const uint64_t s0 = bstart + sl * slice;
+  const uint64_t s1 = s0 + slice < bend ? s0 + slice : bend;
   if (s0 < s1) {
     // aligned middle with dword loads, byte loads at the edges
     const uint64_t a0 = (s0 + 3) & ~3ull, a1 = s1 & ~3ull;
@@ -479,34 +471,49 @@ __global__ __launch_bounds__(kWaveE) void k_tree(const uint32_t *hist, uint32_t 
   }
 }
 
-// Layout of one block per wave.  lenm holds, per block, its 256 code
-// lengths; modes its mode (0 coded, 1 | symbol << 8 constant).  The code is
-// canonical: with cnt(L) codes of length L and fc(L) the first of them,
-// fc(L+1) = 2 (fc(L) + cnt(L)); a symbol's code is fc(len) plus its rank
-// among the symbols of its length; the internal nodes at depth d are the
-// prefixes [fc(d) + cnt(d), 2^d) numbered breadth-first, and child q of such
-// a node is a leaf iff q < fc(d+1) + cnt(d+1).  With flat-subtree trees
-// (shape 1, Sec. 2.2.3-2.2.4) the same closed form runs over the tree's
-// items: the symbols of length L are cut by the binary digits of cnt(L),
-// largest group first, a group of 2^D hanging at depth L - D; the items of a
-// depth are ordered by D descending; a group of two or more symbols is a
-// node (flat when D >= 2), numbered before the depth's internal nodes.
+// Layout of one block per workgroup, a thread per symbol, leaf or node.
+// lenm holds, per block, its 256 code lengths; modes its mode (0 coded, 1 |
+// symbol << 8 constant).  The code is canonical: with cnt(L) codes of length
+// L and fc(L) the first of them, fc(L+1) = 2 (fc(L) + cnt(L)); a symbol's
+// code is fc(len) plus its rank among the symbols of its length; the internal
+// nodes at depth d are the prefixes [fc(d) + cnt(d), 2^d) numbered
+// breadth-first, and child q of such a node is a leaf iff q < fc(d+1) +
+// cnt(d+1).  With flat-subtree trees (shape 1, Sec. 2.2.3-2.2.4) the same
+// closed form runs over the tree's items: the symbols of length L are cut by
+// the binary digits of cnt(L), largest group first, a group of 2^D hanging at
+// depth L - D; the items of a depth are ordered by D descending; a group of
+// two or more symbols is a node (flat when D >= 2), numbered before the
+// depth's internal nodes.  A node's counts are differences of the counts'
+// prefix sums in leaf order at the ends of its leaf interval.
 struct LayoutSmem {
-  uint32_t nv[256], nr[256];
-  uint32_t cnt[17], fc[18], lvl[18], lbase[17], ci[18], gn[18], off[18];
-  uint32_t maxlen, I;
-  uint8_t leafsym[256];
+  uint32_t wc[4][16];      // per wave: symbols of each length
+  uint32_t cnt[18], ci[18], gn[18], fc[18], lvl[18], lb[18], kb[18];   // lb: leaves above depth d
+  uint32_t pc[257];        // counts before each leaf
+  uint16_t lo[256];
+  uint32_t wsum[5][4];
 };
 
-__global__ __launch_bounds__(kWaveE * kLayoutWaves) void k_layout(
+// Sum of the values of the waves before this one, and of all, for the five
+// scans of the layout.
+__device__ __forceinline__ uint32_t waves_before(const uint32_t *w, uint32_t wave, uint32_t *all) {
+  uint32_t b = 0, t = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < 4; ++i) {
+    const uint32_t x = w[i];
+    b += i < wave ? x : 0u;
+    t += x;
+  }
+  *all = t;
+  return b;
+}
+
+__global__ __launch_bounds__(256) void k_layout(
     const uint8_t *lenm, const uint32_t *modes, const uint32_t *hist, uint32_t nb, uint64_t n,
     uint32_t bs, uint32_t ans_mode, uint32_t chunk_log2, uint32_t shape, const uint8_t *fse_dmax,
     EncBlock *eb, BlockLay *lay, RansNode *rnodes, uint8_t *hdr) {
-  __shared__ LayoutSmem smem[kLayoutWaves];
-  const uint32_t wave = threadIdx.x >> 6, lane = __lane_id();
-  const uint32_t b = blockIdx.x * kLayoutWaves + wave;
-  if (b >= nb) return;
-  LayoutSmem &sm = smem[wave];
+  __shared__ LayoutSmem sm;
+  const uint32_t t = threadIdx.x, wave = t >> 6, lane = __lane_id();
+  const uint32_t b = blockIdx.x;
   EncBlock &E = eb[b];
   BlockLay &Lb = lay[b];
   uint8_t *H = hdr + static_cast<uint64_t>(b) * kHdrStride;
@@ -514,7 +521,7 @@ __global__ __launch_bounds__(kWaveE * kLayoutWaves) void k_layout(
   const uint32_t nblk = static_cast<uint32_t>(n - start < bs ? n - start : bs);
   const uint32_t cw = nblk <= 65535 ? 2u : 4u;
   const uint32_t mode = modes[b];
-  if (lane == 0) {
+  if (t == 0) {
     E.in_off = start;
     E.n = nblk;
     Lb.n = nblk;
@@ -525,7 +532,7 @@ __global__ __launch_bounds__(kWaveE * kLayoutWaves) void k_layout(
     H[11] = 0;
   }
   if (mode & 1) {                        // constant block: its 12-byte header only
-    if (lane == 0) {
+    if (t == 0) {
       E.I = 0;
       E.maxlen = 0;
       Lb.hlen = kBlockFixed;
@@ -534,221 +541,229 @@ __global__ __launch_bounds__(kWaveE * kLayoutWaves) void k_layout(
     }
     return;
   }
-  // lane owns symbols 4 lane .. 4 lane + 3
-  const uint32_t lw = *reinterpret_cast<const uint32_t *>(lenm + 256ull * b + 4 * lane);
-  uint32_t l[4], c[4], rank[4] = {0, 0, 0, 0};
+  // the symbol's length, count and rank among the symbols of its length
+  const uint32_t l = lenm[256ull * b + t], c = hist[256ull * b + t];
+  uint32_t rank = 0, wcl = 0;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    l[k] = (lw >> (8 * k)) & 255;
-    c[k] = hist[256ull * b + 4 * lane + k];
-  }
-  const uint64_t below = (1ull << lane) - 1;
   for (uint32_t L = 1; L <= 15; ++L) {
-    uint64_t mk[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) mk[k] = __ballot(l[k] == L);
-    const uint32_t before = __popcll(mk[0] & below) + __popcll(mk[1] & below) +
-                            __popcll(mk[2] & below) + __popcll(mk[3] & below);
-    uint32_t own = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (l[k] == L) { rank[k] = before + own; ++own; }
-    if (lane == 0) sm.cnt[L] = __popcll(mk[0]) + __popcll(mk[1]) + __popcll(mk[2]) + __popcll(mk[3]);
+    const uint64_t mk = __ballot(l == L);
+    const uint32_t before = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mk >> 32),
+                                                      __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mk), 0u));
+    if (l == L) rank = before;
+    if (lane == L) wcl = static_cast<uint32_t>(__popcll(mk));
   }
-  if (lane == 0) {
-    sm.cnt[0] = 0;
-    sm.cnt[16] = 0;
-    // items per depth: every symbol (shape 0), or one per set binary digit D
-    // of cnt(d + D) (shape 1)
-    uint32_t maxitem = 0, lb = 0;
-    for (uint32_t d = 0; d <= 17; ++d) {
-      uint32_t ci = 0, gn = 0;
-      if (shape == 0) {
-        ci = d <= 16 ? sm.cnt[d] : 0u;
-      } else {
-        for (uint32_t D = 0; D <= 8; ++D)
-          if (d + D <= 15 && ((sm.cnt[d + D] >> D) & 1)) { ++ci; gn += D >= 1 ? 1u : 0u; }
+  if (lane < 16) sm.wc[wave][lane] = wcl;
+  sm.pc[t] = 0;
+  __syncthreads();
+  // per depth, in lane d of every wave: symbols, items, group nodes, flat
+  // nodes, leaves, first code, first node, leaves above
+  uint32_t cnt_l = 0;
+  if (lane < 16) cnt_l = sm.wc[0][lane] + sm.wc[1][lane] + sm.wc[2][lane] + sm.wc[3][lane];
+  for (uint32_t w = 0; w < wave; ++w) rank += sm.wc[w][l & 15];
+  uint32_t ci_l = cnt_l, gn_l = 0, nf_l = 0, nl_l = cnt_l;
+  if (shape) {
+    ci_l = nl_l = 0;
+#pragma unroll
+    for (uint32_t D = 0; D <= 8; ++D) {
+      const uint32_t src = lane + D;
+      const uint32_t cd = __shfl(cnt_l, static_cast<int>(src & 63), kWaveE);
+      if (src <= 15 && ((cd >> D) & 1)) {
+        ++ci_l;
+        nl_l += 1u << D;
+        gn_l += D >= 1 ? 1u : 0u;
+        nf_l += D >= 2 ? 1u : 0u;
       }
-      sm.ci[d] = ci;
-      sm.gn[d] = gn;
-      if (ci) maxitem = d;
-      if (d <= 16) { sm.lbase[d] = lb; lb += sm.cnt[d]; }
     }
-    uint32_t fcd = 0, lv = 0;
-    for (uint32_t d = 0; d <= 17; ++d) {
-      sm.fc[d] = fcd;
-      sm.lvl[d] = lv;
-      sm.off[d] = fcd + sm.ci[d] - sm.gn[d];
-      lv += sm.gn[d] + (d < maxitem ? (1u << d) - fcd - sm.ci[d] : 0u);
-      fcd = 2 * (fcd + sm.ci[d]);
-    }
-    const uint32_t levels = maxitem + (sm.gn[maxitem] ? 1u : 0u);
-    sm.maxlen = levels;
-    sm.I = sm.lvl[levels];
-    E.maxlen = levels;
-    E.I = sm.lvl[levels];
   }
-  wave_sync();
-  const uint32_t I = sm.I;
-  // codes and the symbols in (length, symbol) order
+  const uint64_t has_items = __ballot(lane <= 15 && ci_l != 0);
+  const uint32_t maxitem = has_items ? 63u - static_cast<uint32_t>(__clzll(static_cast<long long>(has_items))) : 0u;
+  uint32_t fc_l = 0, lvl_l = 0, fcd = 0, lvd = 0;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const uint32_t s = 4 * lane + k;
-    uint32_t cl = 0;
-    if (l[k]) {
-      const uint32_t L = l[k], r = rank[k];
-      if (shape == 0) {
-        cl = (sm.fc[L] + r) | (L << 16);
-      } else {
-        // the symbol's group: binary digits of cnt(L), largest first
-        const uint32_t cn = sm.cnt[L];
-        uint32_t D = 0, hi = 0;
-        for (uint32_t e = 9; e-- > 0;) {
-          if (!((cn >> e) & 1)) continue;
-          if (r < hi + (1u << e)) { D = e; break; }
-          hi += 1u << e;
-        }
-        const uint32_t m = L - D;
-        uint32_t idx = 0;                  // items of depth m with a larger D
-        for (uint32_t e = D + 1; e <= 8; ++e)
-          if (m + e <= 15 && ((sm.cnt[m + e] >> e) & 1)) ++idx;
-        const uint32_t code = ((sm.fc[m] + idx) << D) | (r - hi);
-        cl = code | (L << 16) | (D << 20) | (D ? (sm.lvl[m] + idx) << 24 : 0u);
+  for (uint32_t d = 0; d <= 16; ++d) {
+    const uint32_t cd = __builtin_amdgcn_readlane(ci_l, d), gd = __builtin_amdgcn_readlane(gn_l, d);
+    lvd += gd + (d < maxitem ? (1u << d) - fcd - cd : 0u);
+    fcd = 2 * (fcd + cd);
+    if (lane == d + 1) { fc_l = fcd; lvl_l = lvd; }
+  }
+  const uint32_t levels = maxitem + (__builtin_amdgcn_readlane(gn_l, maxitem) ? 1u : 0u);
+  const uint32_t I = __builtin_amdgcn_readlane(lvl_l, levels);
+  const uint32_t lsum = wave_incl_scan(lane < 16 ? nl_l : 0u);
+  const uint32_t nleaf = __builtin_amdgcn_readlane(lsum, 63);
+  // canonical: internal nodes only, p - fc - ci of the level; flat-subtree:
+  // every prefix of the level from its first item on
+  const uint32_t single = shape && lane < 16 ? ci_l - gn_l : 0u;
+  const uint32_t kb_l = shape ? lvl_l - fc_l + wave_incl_scan(single) - single : lvl_l - fc_l - ci_l;
+  if (wave == 0) {
+    if (lane < 18) {
+      sm.kb[lane] = kb_l;
+      sm.cnt[lane] = cnt_l; sm.ci[lane] = lane < 16 ? ci_l : 0u; sm.gn[lane] = gn_l;
+      sm.fc[lane] = fc_l; sm.lvl[lane] = lvl_l; sm.lb[lane] = lsum - (lane < 16 ? nl_l : 0u);
+      E.lvl[lane] = lvl_l;
+    }
+    if (lane < 16) {
+      E.kbase[lane] = static_cast<int32_t>(kb_l);
+      E.nfl[lane] = nf_l;
+    }
+    if (lane == 0) { E.maxlen = levels; E.I = I; E.nleaf = nleaf; }
+  }
+  __syncthreads();
+  // codes, and the leaves in code order
+  uint32_t pay = 0;
+  if (l) {
+    uint32_t code, leaf;
+    if (shape == 0) {
+      code = sm.fc[l] + rank;
+      leaf = sm.lb[l] + rank;
+    } else {
+      const uint32_t cn = sm.cnt[l];     // the symbol's group: binary digits of cnt(l), largest first
+      uint32_t D = 0, first = 0;
+      for (uint32_t e = 9; e-- > 0;) {
+        if (!((cn >> e) & 1)) continue;
+        if (rank < first + (1u << e)) { D = e; break; }
+        first += 1u << e;
       }
-      sm.leafsym[sm.lbase[L] + r] = static_cast<uint8_t>(s);
+      const uint32_t m = l - D;
+      uint32_t idx = 0, lv = 0;          // items of depth m with a larger D, and their leaves
+      for (uint32_t e = D + 1; e <= 8; ++e)
+        if (m + e <= 15 && ((sm.cnt[m + e] >> e) & 1)) { ++idx; lv += 1u << e; }
+      code = ((sm.fc[m] + idx) << D) | (rank - first);
+      leaf = sm.lb[m] + lv + (rank - first);
     }
-    E.code[s] = cl;
-    sm.nv[s] = 0;
-    sm.nr[s] = 0;
-    rank[k] = cl;                        // kept for the path walk below
+    pay = code << (16 - l);
+    sm.pc[leaf] = c;
+    E.leaf[t] = static_cast<uint8_t>(leaf);
+  } else {
+    E.leaf[t] = 255;
   }
-  if (lane < 16) E.lvl[lane] = sm.lvl[lane];
-  if (lane < 17) E.off[lane] = sm.off[lane];
-  wave_sync();
-  // symbols passing each node and going right: walk each present symbol's path
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    if (!c[k] || !l[k]) continue;
-    const uint32_t cl = rank[k], len = l[k], D = (cl >> 20) & 15;
-    for (uint32_t d = 0; d < path_len(cl); ++d) {
-      const uint32_t id = path_node(sm.lvl, sm.off, cl, d);
-      atomicAdd(&sm.nv[id], c[k]);
-      if (D >= 2 && d == len - D) break;  // a flat node has no right branch
-      if (((cl & 0xFFFF) >> (len - 1 - d)) & 1) atomicAdd(&sm.nr[id], c[k]);
-    }
+  E.pay[t] = static_cast<uint16_t>(pay);
+  __syncthreads();
+  {
+    const uint32_t own = sm.pc[t], inc = wave_incl_scan(own);
+    if (lane == kWaveE - 1) sm.wsum[0][wave] = inc;
+    __syncthreads();
+    uint32_t all;
+    const uint32_t ex = waves_before(sm.wsum[0], wave, &all) + inc - own;
+    sm.pc[t] = ex;
+    if (t == 255) sm.pc[256] = all;
   }
-  wave_sync();
-  // node table: lane owns nodes 4 lane .. 4 lane + 3
-  uint32_t fdk[4] = {0, 0, 0, 0}, dk[4] = {0, 0, 0, 0};
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const uint32_t i = 4 * lane + k;
-    if (i >= I) continue;
-    uint32_t d = 0;
-    while (sm.lvl[d + 1] <= i) ++d;
-    dk[k] = d;
-    const uint32_t r = i - sm.lvl[d];
-    uint32_t cc = 0;
+  // node t: depth, children, first leaf
+  uint32_t d = 0, fd = 0, cc = 0, lo = 0, hi = 0, slot = 0;
+  bool group = false;
+  const bool node = t < I;
+  if (node) {
+    for (uint32_t j = 1; j < levels; ++j) d += t >= sm.lvl[j] ? 1u : 0u;
+    const uint32_t r = t - sm.lvl[d];
     if (r < sm.gn[d]) {                  // group r of depth d (shape 1)
-      uint32_t D = 0, left = r;
+      uint32_t D = 0, left = r, lv = 0;
       for (uint32_t e = 8; e >= 1; --e)
         if (d + e <= 15 && ((sm.cnt[d + e] >> e) & 1)) {
           if (left == 0) { D = e; break; }
           --left;
+          lv += 1u << e;
         }
-      const uint32_t L = d + D;
-      const uint32_t first = sm.lbase[L] + (sm.cnt[L] & ~((2u << D) - 1));
-      if (D == 1) cc = (0x8000u | sm.leafsym[first]) | ((0x8000u | sm.leafsym[first + 1]) << 16);
-      else { cc = 0x80008000u; fdk[k] = D; }
+      group = true;
+      slot = sm.fc[d] + r + sm.kb[d];
+      lo = sm.lb[d] + lv;
+      hi = lo + (1u << D);
+      cc = 0x80008000u;
+      fd = D >= 2 ? D : 0u;
     } else {
       const uint32_t p = sm.fc[d] + sm.ci[d] + (r - sm.gn[d]);
       const uint32_t d1 = d + 1;
-      const uint32_t leaf0 = sm.lbase[d1] + (shape ? (sm.cnt[d1] & ~1u) : 0u);
+      slot = p + sm.kb[d];
       for (int bb = 0; bb < 2; ++bb) {
         const uint32_t q = 2 * p + bb;
         const uint32_t rq = q - sm.fc[d1];
         const uint32_t ch = rq < sm.gn[d1] ? sm.lvl[d1] + rq
-                            : rq < sm.ci[d1] ? 0x8000u | sm.leafsym[leaf0 + rq - sm.gn[d1]]
+                            : rq < sm.ci[d1] ? 0x8000u
                                              : sm.lvl[d1] + sm.gn[d1] + (q - sm.fc[d1] - sm.ci[d1]);
         cc |= ch << (16 * bb);
       }
+      // the first leaf: the item that the leftmost path under p ends in
+      for (uint32_t e = d1; e <= 16; ++e) {
+        const uint32_t x = (p << (e - d)) - sm.fc[e];
+        if (x >= sm.ci[e]) continue;
+        lo = sm.lb[e];
+        if (shape == 0) {
+          lo += x;
+        } else {
+          uint32_t left = x;
+          for (uint32_t g = 8; left; --g)
+            if (e + g <= 15 && ((sm.cnt[e + g] >> g) & 1)) { lo += 1u << g; --left; }
+        }
+        break;
+      }
     }
-    *reinterpret_cast<uint32_t *>(E.child[i]) = cc;
-    E.fd[i] = static_cast<uint8_t>(fdk[k]);
+    sm.lo[t] = static_cast<uint16_t>(lo);
   }
-  // lane owns nodes 4 lane .. 4 lane + 3: kind, sizes and their prefixes
+  __syncthreads();
+  uint32_t nv = 0, nr = 0, mk = 0, kd = 0;
+  if (node) {
+    if (!group) hi = t + 1 < sm.lvl[d + 1] ? sm.lo[t + 1] : nleaf;
+    const uint32_t c1 = cc >> 16;
+    const uint32_t mid = fd ? hi : (c1 & 0x8000) ? hi - 1 : sm.lo[c1];
+    nv = sm.pc[hi] - sm.pc[lo];
+    nr = sm.pc[hi] - sm.pc[mid];
+    *reinterpret_cast<uint32_t *>(E.child[t]) = cc;
+    E.lo[t] = static_cast<uint16_t>(lo);
+    E.mid[t] = static_cast<uint16_t>(mid);
+    E.hi[t] = static_cast<uint16_t>(hi);
+    E.depth[t] = static_cast<uint8_t>(d);
+    E.fd[t] = static_cast<uint8_t>(fd);
+    E.slot[t] = static_cast<uint16_t>(slot);
+    if (!fd) {
+      if (ans_mode == 3) mk = fse_marker(nv, nr, d, fse_dmax);
+      kd = (ans_mode == 3 ? mk != 0 : select_ans(ans_mode, nv, nr)) ? 1u : 0u;
+    }
+  }
+  // sizes of the node's parts and their prefixes
   const uint32_t C = 1u << chunk_log2;
-  uint32_t kd[4], rb[4], aw[4], ch[4], sl[4], nvk[4], nrk[4], mk[4];
-  uint32_t lraw = 0, lans = 0, lrn = 0, lch = 0, lsl = 0;
+  const uint32_t nch = kd ? (nv + C - 1) >> chunk_log2 : 0u;
+  const uint32_t rem = nv - (nch ? (nch - 1) * C : 0u);
+  const uint64_t bits = static_cast<uint64_t>(nv) * (fd ? fd : 1u);
+  const uint32_t part[5] = {kd || !node ? 0u : static_cast<uint32_t>((bits + 7) / 8), kd ? (nv + 31) / 32 : 0u, kd, nch,
+                            nch ? ((nch - 1) * slot_size(C) + slot_size(rem)) / 16 : 0u};   // slots in 16-byte units
+  uint32_t ex[5], all[5];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const uint32_t i = 4 * lane + k;
-    nvk[k] = i < I ? sm.nv[i] : 0u;
-    nrk[k] = i < I ? sm.nr[i] : 0u;
-    mk[k] = i < I && !fdk[k] && ans_mode == 3 ? fse_marker(nvk[k], nrk[k], dk[k], fse_dmax) : 0u;
-    kd[k] = i < I && !fdk[k] && (ans_mode == 3 ? mk[k] != 0 : select_ans(ans_mode, nvk[k], nrk[k])) ? 1u : 0u;
-    const uint32_t nch = kd[k] ? (nvk[k] + C - 1) / C : 0u;
-    const uint32_t rem = nvk[k] - (nch ? (nch - 1) * C : 0u);
-    const uint64_t bits = static_cast<uint64_t>(nvk[k]) * (fdk[k] ? fdk[k] : 1u);
-    rb[k] = lraw; aw[k] = lans; ch[k] = lch; sl[k] = lsl;
-    lraw += kd[k] || i >= I ? 0u : static_cast<uint32_t>((bits + 7) / 8);
-    lans += kd[k] ? (nvk[k] + 31) / 32 : 0u;
-    lch += nch;
-    lsl += nch ? ((nch - 1) * slot_size(C) + slot_size(rem)) / 16 : 0u;   // 16-byte units
-    lrn += kd[k];
+  for (int q = 0; q < 5; ++q) {
+    ex[q] = wave_incl_scan(part[q]);
+    if (lane == kWaveE - 1) sm.wsum[q][wave] = ex[q];
   }
-  const uint32_t iraw = wave_incl_scan(lraw), ians = wave_incl_scan(lans), irn = wave_incl_scan(lrn);
-  const uint32_t ich = wave_incl_scan(lch), isl = wave_incl_scan(lsl);
-  uint32_t rn = irn - lrn;
-  uint32_t nib = 0;
+  __syncthreads();
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const uint32_t i = 4 * lane + k;
-    nib |= kd[k] << k;
-    if (i >= I) continue;
-    const uint32_t raw_off = iraw - lraw + rb[k], rword = ians - lans + aw[k];
-    E.bit[i] = kd[k] ? rword : raw_off;
-    if (kd[k]) {
-      RansNode r;
-      r.rword = rword;
-      r.nv = nvk[k];
-      r.p1q = ans_mode == 3 ? mk[k] : p1q_of(nvk[k], nrk[k]);
-      r.ch0 = ich - lch + ch[k];
-      r.sl0 = 16ull * (isl - lsl + sl[k]);
-      r.blen = 0;
-      r.boff = 0;
-      rnodes[255ull * b + rn] = r;
-      ++rn;
-    }
+  for (int q = 0; q < 5; ++q) ex[q] += waves_before(sm.wsum[q], wave, &all[q]) - part[q];
+  if (node) E.bit[t] = kd ? ex[1] : ex[0];
+  if (kd) {
+    RansNode r;
+    r.rword = ex[1];
+    r.nv = nv;
+    r.p1q = ans_mode == 3 ? mk : p1q_of(nv, nr);
+    r.ch0 = ex[3];
+    r.sl0 = 16ull * ex[4];
+    r.blen = 0;
+    r.boff = 0;
+    rnodes[255ull * b + ex[2]] = r;
   }
   // header: code lengths (two nibbles a byte, symbol 2j low), kind bits, counts of 1 bits
   const uint32_t kb = (I + 7) / 8;
-  H[12 + 2 * lane] = static_cast<uint8_t>(l[0] | (l[1] << 4));
-  H[12 + 2 * lane + 1] = static_cast<uint8_t>(l[2] | (l[3] << 4));
-  const uint32_t nib_hi = __shfl_down(nib, 1, kWaveE);
-  if ((lane & 1) == 0 && lane / 2 < kb) H[140 + lane / 2] = static_cast<uint8_t>(nib | (nib_hi << 4));
-  const uint64_t bm[4] = {__ballot(kd[0]), __ballot(kd[1]), __ballot(kd[2]), __ballot(kd[3])};
-  if (lane < 8) {                        // kind mask word: nodes 32 lane .. 32 lane + 31
-    uint32_t w = 0;
-    for (uint32_t j = 0; j < 32; ++j) w |= static_cast<uint32_t>((bm[j & 3] >> (8 * lane + j / 4)) & 1) << j;
-    E.kind[lane] = w;
+  const uint32_t l_next = __shfl_down(l, 1, kWaveE);
+  if ((t & 1) == 0) H[12 + t / 2] = static_cast<uint8_t>(l | (l_next << 4));
+  const uint64_t km = __ballot(kd);
+  if (lane < 2) E.kind[2 * wave + lane] = static_cast<uint32_t>(km >> (32 * lane));
+  if (lane < 8 && 8 * wave + lane < kb) H[140 + 8 * wave + lane] = static_cast<uint8_t>(km >> (8 * lane));
+  if (node) {
+    uint8_t *q = H + 140 + kb + cw * t;
+    q[0] = static_cast<uint8_t>(nr);
+    q[1] = static_cast<uint8_t>(nr >> 8);
+    if (cw == 4) { q[2] = static_cast<uint8_t>(nr >> 16); q[3] = static_cast<uint8_t>(nr >> 24); }
   }
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const uint32_t i = 4 * lane + k;
-    if (i >= I) continue;
-    uint8_t *q = H + 140 + kb + cw * i;
-    q[0] = static_cast<uint8_t>(nrk[k]);
-    q[1] = static_cast<uint8_t>(nrk[k] >> 8);
-    if (cw == 4) { q[2] = static_cast<uint8_t>(nrk[k] >> 16); q[3] = static_cast<uint8_t>(nrk[k] >> 24); }
-  }
-  if (lane == kWaveE - 1) {
+  if (t == 0) {
     Lb.hlen = 140 + kb + cw * I;
-    Lb.raw_bytes = iraw;
-    Lb.ans_words = ians;
-    Lb.n_rnodes = irn;
-    Lb.n_chunks = ich;
-    Lb.slot_bytes = 16ull * isl;
+    Lb.raw_bytes = all[0];
+    Lb.ans_words = all[1];
+    Lb.n_rnodes = all[2];
+    Lb.n_chunks = all[3];
+    Lb.slot_bytes = 16ull * all[4];
   }
 }
 
@@ -802,157 +817,349 @@ __global__ __launch_bounds__(kScanNT) void k_scan(BlockLay *lay, uint32_t nb, To
   }
 }
 
-static_assert(kSplitNT == 256, "the split kernel's prefix walk has one thread per symbol");
-static_assert(kHistSlice % kSplitT == 0, "split tiles never cross a slice");
+// LDS-only workgroup barrier (the split kernel's waves share nothing else).
+__device__ __forceinline__ void lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
 
+static_assert(kMaxLenGpu <= 12, "code bits of a symbol");
+constexpr int kSplitCh = 16;             // 64-symbol chunks of one wave, at most
+constexpr uint32_t kEndsHere = 0x7F00;   // SplitSmem::K of a leaf: past every place
+
+template <int NT>
 struct SplitSmem {
-  EncBlock B;
-  uint32_t cur[256];      // symbols of the node in earlier tiles
-  uint32_t tv[256];       // node's symbols in this tile
-  uint32_t seg[256];      // node's segment in its level buffer
-  uint32_t top[16];
-  uint32_t hist[256];
-  uint32_t fw[kSplitNT / kWaveE][20];   // per wave: a flat node's packed values (64 x D bits + 31)
-  uint8_t buf[2][kSplitT];
+  static constexpr uint32_t S = 16 * NT;
+  uint16_t buf[S + 64 * 4];            // a level's codes, in its nodes' order (groups of 4 chunks read past its end)
+  union {
+    uint32_t bits[13 * S / 32 + 2 * 16 + 4];   // every level's bits, then the flat nodes' fields
+    struct {                           // before the levels only
+      uint32_t P[257], C[257];         // symbols of the slice / of earlier slices before each leaf
+      uint32_t T[257], O[257];         // symbols / 1 bits of the nodes before each node
+    };
+  };
+  int16_t K[2 * 272];                  // node in slot i: [2i] where its 0 symbols go, [2i + 1] its 1 symbols (see k_split)
+  uint32_t F[272];                     // flat node, by slot: where its fields go | D << 24
+  uint32_t wx[257];                    // output words of the nodes before each node
+  uint32_t src[256], len[256];         // node's first bit in `bits`; bits | rANS << 31
+  uint64_t q[256];                     // node's first bit in its area
+  uint16_t pay[256];
+  uint32_t lvl[18], fbits;             // levels' first nodes; flat fields' bits
+  uint32_t wsum[2][NT / kWaveE];
+  uint32_t part[4][NT / kWaveE];
 };
 
-// One workgroup per slice of kHistSlice symbols of a block (slice k of block
-// b is workgroup b * spb + k), so that large blocks are split by many
-// workgroups.  A node's bits from this slice start at the number of the
-// block's symbols before the slice that pass the node: the sum, over the
-// symbols on whose path the node lies, of their counts before the slice
-// (the slice's row of the prefix histograms).  A raw node's bitmap is
-// written at its byte offset in the block's raw image (the stream layout),
-// a rANS node's at its word in the block's rANS bitmap words.  Slices and
-// neighbouring nodes share words at their edges: every word is written with
-// atomicOr into zeroed memory.
-__global__ __launch_bounds__(kSplitNT) void k_split(const uint8_t *in, const EncBlock *blocks,
-                                                    const BlockLay *lay, uint32_t nblocks, uint32_t spb,
-                                                    const uint32_t *pre, uint32_t *img, uint32_t *rbm) {
-  __shared__ SplitSmem sm;
-  const int tid = threadIdx.x;
-  const int wave = tid >> 6;
-  const uint32_t lane = __lane_id();
+// 32 bits from bit x of an LDS word array.
+__device__ __forceinline__ uint32_t bits32(const uint32_t *w, uint32_t x) {
+  return __builtin_amdgcn_alignbit(w[(x >> 5) + 1], w[x >> 5], x & 31);
+}
+
+// One workgroup per slice of 16 NT symbols of a block (slice k of block b is
+// workgroup b * spb + k).
+//   Nodes: the slice's counts (from the prefix histograms) summed in leaf
+// order give every node's symbols and 1 bits in the slice, and the symbols
+// of earlier slices where its bits go on; scans over the nodes place each
+// node in its level.
+//   Levels: a level's symbols lie in one array, nodes in breadth-first order
+// and stream order inside a node, so each wave takes an equal share of it in
+// 64-symbol chunks whatever the nodes' sizes.  A chunk's bits are one ballot,
+// stored as 64 bits of the level's bit array; R(p), the 1 bits of the level
+// before position p, is the ballots' running count, and a symbol at p goes to
+// p - R(p) + K (0 bit) or R(p) + K (1 bit): K, by the code's bits so far, holds the child's
+// place less the node's own terms, and for a leaf (the symbol ends there) a
+// value past every place.  The symbols of a flat node end in it and store their D-bit
+// index at D times their place.
+//   Output: the nodes' bits are copied out of the level arrays word by word,
+// at the bit where the node's earlier slices end.  A raw node goes to its
+// byte offset in the block's raw image (the stream layout), a rANS node to its
+// word among the block's rANS bitmap words.  A word that this slice does not
+// fill is ORed into zeroed memory, the others are stored.
+// Bound by vector instructions, about 17 per 64 symbols and level, and by the
+// latency of the small levels (two barriers each).  256 MiB Zipf(1.1) in 64
+// KiB blocks: 1.52 ms where one wave per node (the root's 4096 symbols on one
+// wave of four) took 4.15 ms; one 64 KiB block: 22 us, was 86.  LDS holds one
+// level buffer (a level is in registers before it moves) and no more tables
+// than the levels need, for 6 workgroups of 256 threads on a CU: with two
+// buffers and the tables beside them (4 workgroups) and the block's tables
+// read in a chain it took 2.7 ms.
+template <int NT, bool FLAT>
+__global__ __launch_bounds__(NT) void k_split(const uint8_t *in, const EncBlock *blocks,
+                                              const BlockLay *lay, uint32_t nblocks, uint32_t spb,
+                                              const uint32_t *pre, const uint32_t *hist, uint32_t *img,
+                                              uint32_t *rbm) {
+  constexpr uint32_t kSlice = 16 * NT;
+  constexpr int kSplitNT = NT, kSplitNW = NT / kWaveE;
+  static_assert(kSlice <= 16384, "places and leaf marks in 16 signed bits");
+  __shared__ __attribute__((aligned(16))) SplitSmem<NT> sm;
+  const uint32_t tid = threadIdx.x, lane = __lane_id();
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t b = blockIdx.x / spb, slice = blockIdx.x % spb;
   if (b >= nblocks) return;
+  const EncBlock &B = blocks[b];
+  const uint32_t I = B.I, n = B.n, s_lo = slice * kSlice;
+  if (I == 0 || s_lo >= n) return;
+  const uint32_t S = n - s_lo < kSlice ? n - s_lo : kSlice;
+  const uint32_t levels = B.maxlen;
+  // everything the slice needs from memory, in one round trip: its symbols
+  // (16 consecutive ones a thread, no alignment), the symbol's and the node's
+  // row of the block's tables, the levels' values (one level a lane)
+  const uint8_t *src = in + B.in_off + s_lo;
+  uint32_t sy[4] = {0, 0, 0, 0};
+  if (16 * tid + 16 <= S) {
+    __builtin_memcpy(sy, src + 16 * tid, 16);
+  } else {
+#pragma unroll
+    for (uint32_t e = 0; e < 16; ++e)
+      if (16 * tid + e < S) sy[e >> 2] |= static_cast<uint32_t>(src[16 * tid + e]) << (8 * (e & 3));
+  }
+  uint32_t cnt = 0, bef = 0, leaf = 0, lo = 0, mid = 0, hi = 0, cc = 0, d = 0, slot = 0, fd = 0, nbit = 0, pay = 0;
+  bool rans = false;
+  const bool first256 = NT == 256 || tid < 256;
+  if (first256) {
+    const uint32_t *row = pre + static_cast<uint64_t>(blockIdx.x) * 256 + tid;
+    bef = slice ? row[0] : 0u;
+    cnt = slice + 1 < spb ? row[256] : hist[256ull * b + tid];
+    leaf = B.leaf[tid];
+    pay = B.pay[tid];
+    lo = B.lo[tid];
+    mid = B.mid[tid];
+    hi = B.hi[tid];
+    cc = *reinterpret_cast<const uint32_t *>(B.child[tid]);
+    d = B.depth[tid];
+    slot = B.slot[tid];
+    if (FLAT) fd = B.fd[tid];
+    nbit = B.bit[tid];
+    rans = (B.kind[tid >> 5] >> (tid & 31)) & 1;
+  }
+  const uint64_t img_off = lay[b].img_off, rbm_off = lay[b].rbm_off;
+  const uint32_t lvl_l = B.lvl[lane < 18 ? lane : 0u], kb_l = static_cast<uint32_t>(B.kbase[lane & 15]);
+  const uint32_t nfl_l = FLAT ? B.nfl[lane & 15] : 0u;
+  if (first256) {
+    cnt -= bef;
+    sm.pay[tid] = static_cast<uint16_t>(pay);
+    sm.P[leaf] = cnt;
+    sm.C[leaf] = bef;
+  }
+  if (tid < 18) sm.lvl[tid] = lvl_l;
+  lds_sync();
+  // counts in leaf order become prefix sums (entries past the last leaf are
+  // not written above and change no prefix that is read)
+  if (wave < 4) {
+    cnt = sm.P[tid & 255];
+    bef = sm.C[tid & 255];
+    const uint32_t ic = wave_incl_scan(cnt), ib = wave_incl_scan(bef);
+    cnt = ic - cnt;
+    bef = ib - bef;
+    if (lane == kWaveE - 1) { sm.part[0][wave] = ic; sm.part[1][wave] = ib; }
+  }
+  // the root level: every symbol's code
   {
-    const uint4 *src = reinterpret_cast<const uint4 *>(&blocks[b]);
-    uint4 *dst = reinterpret_cast<uint4 *>(&sm.B);
-    for (uint32_t i = tid; i < sizeof(EncBlock) / 16; i += kSplitNT) dst[i] = src[i];
+    uint32_t w[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const uint32_t x = (sy[e >> 1] >> (16 * (e & 1))) & 255, y = (sy[e >> 1] >> (16 * (e & 1) + 8)) & 255;
+      w[e] = sm.pay[x] | (static_cast<uint32_t>(sm.pay[y]) << 16);
+    }
+    uint4 *dst = reinterpret_cast<uint4 *>(sm.buf) + 2 * tid;
+    dst[0] = make_uint4(w[0], w[1], w[2], w[3]);
+    dst[1] = make_uint4(w[4], w[5], w[6], w[7]);
   }
-  __syncthreads();
-  const EncBlock &B = sm.B;
-  const uint32_t s_lo = slice * kHistSlice;
-  if (B.I == 0 || s_lo >= B.n) return;
-  const uint32_t s_hi = B.n - s_lo < kHistSlice ? B.n : s_lo + kHistSlice;
-  const uint64_t img_bit = 8ull * lay[b].img_off, rbm_bit = 32ull * lay[b].rbm_off;
-  for (uint32_t i = tid; i < 256; i += kSplitNT) sm.cur[i] = 0;
-  __syncthreads();
-  if (slice) {   // symbols of each node before this slice
-    const uint32_t s = tid;
-    const uint32_t c = pre[static_cast<uint64_t>(blockIdx.x) * 256 + s];
-    const uint32_t cl = B.code[s];
-    if (c && cl)
-      for (uint32_t d = 0; d < path_len(cl); ++d) atomicAdd(&sm.cur[path_node(B.lvl, B.off, cl, d)], c);
-    __syncthreads();
+  lds_sync();
+  if (wave < 4) {
+    uint32_t ac, ab;
+    cnt += waves_before(sm.part[0], wave, &ac);
+    bef += waves_before(sm.part[1], wave, &ab);
+    sm.P[tid] = cnt;
+    sm.C[tid] = bef;
+    if (tid == 0) { sm.P[256] = ac; sm.C[256] = ab; }
   }
-  const uint8_t *bin = in + B.in_off;
-  for (uint32_t t0 = s_lo; t0 < s_hi; t0 += kSplitT) {
-    const uint32_t tn = s_hi - t0 < kSplitT ? s_hi - t0 : kSplitT;
-    for (uint32_t i = tid; i < 256; i += kSplitNT) { sm.tv[i] = 0; sm.hist[i] = 0; }
-    if (tid < 16) sm.top[tid] = 0;
-    __syncthreads();
-    for (uint32_t i = tid; i < tn; i += kSplitNT) {
-      const uint8_t s = bin[t0 + i];
-      sm.buf[0][i] = s;
-      atomicAdd(&sm.hist[s], 1u);
+  lds_sync();
+  // node tid
+  const bool node = tid < I;
+  uint32_t tv = 0, ones = 0, nw = 0, fx = 0;
+  if (wave < 4) {
+    uint32_t fb = 0;
+    if (node) {
+      tv = sm.P[hi] - sm.P[lo];
+      ones = sm.P[hi] - sm.P[mid];
+      const uint32_t cur = sm.C[hi] - sm.C[lo], D = FLAT && fd ? fd : 1u;
+      const uint64_t q = (rans ? 32 * (rbm_off + nbit) : 8 * (img_off + nbit)) + static_cast<uint64_t>(D) * cur;
+      const uint32_t len = D * tv;
+      nw = len ? (static_cast<uint32_t>(q & 31) + len + 31) / 32 : 0u;
+      fb = FLAT && fd ? len : 0u;
+      sm.q[tid] = q;
+      sm.len[tid] = len | (rans ? 0x80000000u : 0u);
     }
-    __syncthreads();
-    // symbols of the tile passing each node: walk each present symbol's path
-    {
-      const uint32_t s = tid;
-      const uint32_t c = sm.hist[s];
-      const uint32_t cl = B.code[s];
-      if (c && cl)
-        for (uint32_t d = 0; d < path_len(cl); ++d) atomicAdd(&sm.tv[path_node(B.lvl, B.off, cl, d)], c);
+    const uint32_t it = wave_incl_scan(tv), io = wave_incl_scan(ones), iw = wave_incl_scan(nw);
+    const uint32_t jf = FLAT ? wave_incl_scan(fb) : 0u;
+    if (lane == kWaveE - 1) {
+      sm.part[0][wave] = it; sm.part[1][wave] = io; sm.part[2][wave] = iw; sm.part[3][wave] = jf;
     }
-    __syncthreads();
-    for (uint32_t i = tid; i < B.I; i += kSplitNT) {
-      uint32_t d = 0;
-      while (B.lvl[d + 1] <= i) ++d;
-      sm.seg[i] = sm.tv[i] ? atomicAdd(&sm.top[d], sm.tv[i]) : 0u;
-    }
-    __syncthreads();
-    for (uint32_t d = 0; d < B.maxlen; ++d) {
-      const uint8_t *lb = sm.buf[d & 1];
-      uint8_t *cb = sm.buf[(d + 1) & 1];
-      for (uint32_t v = B.lvl[d] + wave; v < B.lvl[d + 1]; v += kSplitNT / kWaveE) {
-        const uint32_t tvv = sm.tv[v];
-        const uint32_t seg = sm.seg[v];
-        const uint16_t c0 = B.child[v][0], c1 = B.child[v][1];
-        uint32_t r0 = (c0 & 0x8000) ? 0u : sm.seg[c0];
-        uint32_t r1 = (c1 & 0x8000) ? 0u : sm.seg[c1];
-        const bool rans = (B.kind[v >> 5] >> (v & 31)) & 1;
-        uint32_t *area = rans ? rbm : img;
-        const uint32_t D = B.fd[v];
-        if (D) {
-          // a flat node: each symbol's index in the node's group (its code's
-          // last D bits), as D-bit fields in stream order, gathered per 64
-          // symbols in LDS and ORed into the image word by word
-          const uint64_t base = img_bit + 8ull * B.bit[v] + static_cast<uint64_t>(D) * sm.cur[v];
-          uint32_t *fw = sm.fw[wave];
-          for (uint32_t c = 0; c < tvv; c += kWaveE) {
-            const bool act = c + lane < tvv;
-            const uint32_t s = act ? lb[seg + c + lane] : 0u;
-            const uint32_t q = B.code[s] & ((1u << D) - 1);
-            const uint64_t P = base + static_cast<uint64_t>(D) * c;
-            const uint32_t a = static_cast<uint32_t>(P & 31);
-            const uint32_t nw = (a + D * kWaveE + 31) >> 5;
-            if (lane < 20) fw[lane] = 0;
-            wave_sync();
-            if (act && q) {
-              const uint32_t bp = a + D * lane;
-              atomicOr(&fw[bp >> 5], q << (bp & 31));
-              if ((bp & 31) + D > 32) atomicOr(&fw[(bp >> 5) + 1], q >> (32 - (bp & 31)));
-            }
-            wave_sync();
-            if (lane < nw && fw[lane]) atomicOr(&area[(P >> 5) + lane], fw[lane]);
-            wave_sync();
-          }
-          continue;
+    tv = it - tv;
+    ones = io - ones;
+    nw = iw - nw;
+    fx = jf - fb;
+  }
+  lds_sync();
+  if (wave < 4) {
+    uint32_t at, ao, aw, af = 0;
+    tv += waves_before(sm.part[0], wave, &at);        // from here on the sums before this node
+    ones += waves_before(sm.part[1], wave, &ao);
+    nw += waves_before(sm.part[2], wave, &aw);
+    if (FLAT) fx += waves_before(sm.part[3], wave, &af);
+    sm.T[tid] = tv;
+    sm.O[tid] = ones;
+    sm.wx[tid] = nw;
+    if (tid == 0) { sm.T[256] = at; sm.O[256] = ao; sm.wx[256] = aw; sm.fbits = af; }
+  }
+  lds_sync();
+  // per level, in lane d of every wave: symbols, those in flat nodes, first
+  // 64-bit word of its bits
+  uint32_t ln_l = 0, lf_l = 0;
+  if (lane < levels) {
+    const uint32_t t0 = sm.T[lvl_l];
+    ln_l = sm.T[sm.lvl[lane + 1]] - t0;
+    if (FLAT) lf_l = sm.T[lvl_l + nfl_l] - t0;
+  }
+  const uint32_t w64 = (ln_l + 63) / 64, lw_i = wave_incl_scan(w64), lw_l = lw_i - w64;
+  const uint32_t all64 = __builtin_amdgcn_readlane(lw_i, 63), fbits = FLAT ? sm.fbits : 0u;
+  const uint32_t lw_d = __shfl(lw_l, static_cast<int>(d), kWaveE);   // every lane takes part
+  if (node) {
+    const uint32_t l0 = sm.lvl[d], l1 = sm.lvl[d + 1];
+    const uint32_t seg = tv - sm.T[l0], rs = ones - sm.O[l0], t1 = sm.T[l1];
+    const uint32_t c0 = cc & 0xFFFF, c1 = cc >> 16;
+    const uint32_t k0 = (c0 & 0x8000) ? kEndsHere : (sm.T[c0 & 255] - t1 - seg + rs) & 0xFFFF;
+    const uint32_t k1 = (c1 & 0x8000) ? kEndsHere : (sm.T[c1 & 255] - t1 - rs) & 0xFFFF;
+    reinterpret_cast<uint32_t *>(sm.K)[slot] = k0 | (k1 << 16);
+    const uint32_t sb = FLAT && fd ? 64 * all64 + fx : 64 * lw_d + seg;
+    if (FLAT) sm.F[slot] = ((sb - fd * seg) & 0xFFFFFF) | (fd << 24);   // bit sb + D (p - seg)
+    sm.src[tid] = sb;
+  }
+  lds_sync();
+  // the flat fields are ORed in, from the second half of the root level on
+  if (FLAT)
+    for (uint32_t i = tid; i < (fbits + 31) / 32; i += kSplitNT) sm.bits[2 * all64 + i] = 0;
+  for (uint32_t lev = 0; lev < levels; ++lev) {
+    const uint32_t ln = __builtin_amdgcn_readlane(ln_l, lev);
+    if (ln == 0) break;
+    const uint32_t lf = FLAT ? __builtin_amdgcn_readlane(lf_l, lev) : 0u;
+    const uint32_t next = __builtin_amdgcn_readlane(ln_l, lev + 1);
+    const uint32_t nch = (ln + 63) / 64, per = (nch + kSplitNW - 1) / kSplitNW;
+    const uint32_t ch0 = wave * per, ch1 = ch0 + per < nch ? ch0 + per : nch;
+    uint16_t *buf = sm.buf;              // every symbol is in registers before any moves
+    uint2 *lbits = reinterpret_cast<uint2 *>(sm.bits) + __builtin_amdgcn_readlane(lw_l, lev);
+    const uint32_t lim = 64 * ch1 < ln ? 64 * ch1 : ln;   // this wave's positions end here
+    const uint32_t p0 = 64 * ch0 + lane;
+    uint32_t pl[kSplitCh], run = 0;
+    uint64_t m[kSplitCh];
+    // groups of 4 chunks; a group inside the wave's share (and past the
+    // level's flat nodes) needs no test per symbol
+#pragma unroll
+    for (uint32_t g = 0; g < kSplitCh; g += 4) {
+      if (g >= per) break;
+#pragma unroll
+      for (uint32_t i = g; i < g + 4; ++i) pl[i] = buf[p0 + 64 * i];
+      if (64 * (ch0 + g + 4) <= lim && (!FLAT || 64 * (ch0 + g) >= lf)) {
+#pragma unroll
+        for (uint32_t i = g; i < g + 4; ++i) m[i] = __ballot(pl[i] & (0x8000u >> lev));
+        if (lane == 0) {
+#pragma unroll
+          for (uint32_t i = g; i < g + 4; ++i)
+            lbits[ch0 + i] = make_uint2(static_cast<uint32_t>(m[i]), static_cast<uint32_t>(m[i] >> 32));
         }
-        const uint64_t base_bit = (rans ? rbm_bit + 32ull * B.bit[v] : img_bit + 8ull * B.bit[v]) + sm.cur[v];
-        for (uint32_t c = 0; c < tvv; c += kWaveE) {
-          const bool act = c + lane < tvv;
-          const uint32_t s = act ? lb[seg + c + lane] : 0u;
-          const uint32_t cl = B.code[s], len = (cl >> 16) & 15, code = cl & 0xFFFF;
-          const bool bit = act && ((code >> (len - 1 - d)) & 1);
-          const uint64_t m1 = __ballot(bit);
-          const uint64_t m0 = __ballot(act && !bit);
-          const uint64_t lt = (1ull << lane) - 1;
-          // bitmap: 64 bits at bit position base_bit + c
-          const uint64_t P = base_bit + c;
-          const uint64_t q = P >> 5;
-          const uint32_t sh = static_cast<uint32_t>(P & 31);
-          const uint32_t lo = static_cast<uint32_t>(m1), hi = static_cast<uint32_t>(m1 >> 32);
-          uint32_t wv = 0;
-          if (lane == 0) wv = lo << sh;
-          if (lane == 1) wv = sh ? (lo >> (32 - sh)) | (hi << sh) : hi;
-          if (lane == 2) wv = sh ? hi >> (32 - sh) : 0u;
-          if (lane < 3 && wv) atomicOr(&area[q + lane], wv);
-          // stable partition of the symbols into the children's segments
-          if (act) {
-            if (bit && !(c1 & 0x8000)) cb[r1 + __popcll(m1 & lt)] = static_cast<uint8_t>(s);
-            if (!bit && !(c0 & 0x8000)) cb[r0 + __popcll(m0 & lt)] = static_cast<uint8_t>(s);
-          }
-          r1 += __popcll(m1);
-          r0 += __popcll(m0);
+      } else {
+#pragma unroll
+        for (uint32_t i = g; i < g + 4; ++i) {
+          const uint32_t p = p0 + 64 * i;
+          m[i] = __ballot((pl[i] & (0x8000u >> lev)) && p < lim && (!FLAT || p >= lf));
+          if (lane == 0 && ch0 + i < ch1)
+            lbits[ch0 + i] = make_uint2(static_cast<uint32_t>(m[i]), static_cast<uint32_t>(m[i] >> 32));
         }
       }
-      __syncthreads();
+#pragma unroll
+      for (uint32_t i = g; i < g + 4; ++i) run += static_cast<uint32_t>(__popcll(m[i]));
     }
-    for (uint32_t i = tid; i < B.I; i += kSplitNT) sm.cur[i] += sm.tv[i];
-    __syncthreads();
+    if (next == 0 && lf == 0) break;         // every symbol ends here
+    if (lane == 0) sm.wsum[lev & 1][wave] = run;
+    lds_sync();
+    uint32_t R = 0;
+    if (kSplitNW <= 4) {
+#pragma unroll
+      for (uint32_t w = 0; w < kSplitNW; ++w) R += w < wave ? sm.wsum[lev & 1][w] : 0u;
+    } else {
+      R = __builtin_amdgcn_readlane(wave_incl_scan(lane < wave ? sm.wsum[lev & 1][lane & (kSplitNW - 1)] : 0u), 63);
+    }
+    R = __builtin_amdgcn_readfirstlane(R);
+    const int32_t kbase = static_cast<int32_t>(__builtin_amdgcn_readlane(kb_l, lev));
+    const int16_t *Kl = sm.K + 2 * kbase;    // by the code's first lev + 1 bits
+#pragma unroll
+    for (uint32_t g = 0; g < kSplitCh; g += 4) {
+      if (g >= per) break;
+      if (64 * (ch0 + g + 4) <= lim && (!FLAT || 64 * (ch0 + g) >= lf)) {
+        int32_t k[4];
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) k[i] = Kl[pl[g + i] >> (15 - lev)];
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) {
+          const uint64_t mm = m[g + i];
+          const uint32_t r = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mm >> 32),
+                                                       __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mm), R));
+          R += static_cast<uint32_t>(__popcll(mm));
+          const uint32_t x = __builtin_amdgcn_inverse_ballot_w64(mm) ? r : p0 + 64 * (g + i) - r;
+          const uint32_t at = x + k[i];
+          if (at < kSlice) buf[at] = static_cast<uint16_t>(pl[g + i]);
+        }
+      } else {
+        uint32_t v[4];
+        int32_t k[4];
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) {
+          const uint32_t p = p0 + 64 * (g + i), pre_d = pl[g + i] >> (16 - lev);
+          v[i] = p < lim ? pre_d + kbase : 0u;
+          k[i] = sm.K[2 * v[i] + ((pl[g + i] >> (15 - lev)) & 1)];
+        }
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) {
+          const uint32_t p = p0 + 64 * (g + i), c = pl[g + i];
+          const uint64_t mm = m[g + i];
+          const uint32_t r = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mm >> 32),
+                                                       __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mm), R));
+          R += static_cast<uint32_t>(__popcll(mm));
+          if (p >= lim) continue;
+          if (FLAT && p < lf) {              // D-bit field: the code's last D bits
+            const uint32_t F = sm.F[v[i]], D = F >> 24, x = (F + D * p) & 0xFFFFFF;
+            const uint32_t f = ((c << lev) & 0xFFFF) >> (16 - D);
+            atomicOr(&sm.bits[x >> 5], f << (x & 31));
+            if ((x & 31) + D > 32) atomicOr(&sm.bits[(x >> 5) + 1], f >> (32 - (x & 31)));
+          } else {
+            const uint32_t at = (__builtin_amdgcn_inverse_ballot_w64(mm) ? r : p - r) + k[i];
+            if (at < kSlice) buf[at] = static_cast<uint16_t>(c);
+          }
+        }
+      }
+    }
+    lds_sync();
+  }
+  lds_sync();
+  // output words
+  const uint32_t words = sm.wx[256];
+  for (uint32_t j = tid; j < words; j += kSplitNT) {
+    uint32_t v = 0;                          // the last node whose words start at or before j
+#pragma unroll
+    for (uint32_t st = 128; st; st >>= 1) v += sm.wx[v + st] <= j ? st : 0u;
+    const uint32_t k = j - sm.wx[v], lr = sm.len[v], len = lr & 0x7FFFFFFF;
+    const uint64_t q = sm.q[v];
+    const uint32_t sft = static_cast<uint32_t>(q & 31);
+    uint32_t w = k ? bits32(sm.bits, sm.src[v] + 32 * k - sft) : bits32(sm.bits, sm.src[v]) << sft;
+    const uint32_t end = sft + len - 32 * k;
+    if (end < 32) w &= (1u << end) - 1;
+    uint32_t *dst = ((lr >> 31) ? rbm : img) + (q >> 5) + k;
+    if (end < 32 || (k == 0 && sft)) {
+      if (w) atomicOr(dst, w);
+    } else {
+      *dst = w;
+    }
   }
 }
 
@@ -1320,6 +1527,29 @@ bool opts_ok(const pivco_encode_opts *o) {
          o->tree_shape <= 1 && o->reserved == 0;
 }
 
+// Large inputs fill the chip with either slice; the larger halves the
+// histogram rows and the words that two slices share (256 MiB Zipf: 4 Ki / 8 Ki
+// / 16 Ki 2.24 / 2.27 / 2.24 ms a call; 64 MiB very skewed 0.661 / 0.653 /
+// 0.667 ms).  Below 8 MiB (1024 large slices, 4 a CU) the smaller one gives
+// more workgroups: one 64 KiB block is 16 of them.
+uint32_t slice_of(uint64_t n, uint32_t block_size) {
+  return n >= (8ull << 20) && block_size >= kSliceLarge ? kSliceLarge : kSliceSmall;
+}
+
+template <class... A>
+void launch_split(uint32_t slice, bool flat, uint32_t grid, hipStream_t s, A... a) {
+  const dim3 g(grid), t(slice / 16);
+  if (slice == kSliceSmall) {
+    constexpr int NT = kSliceSmall / 16;
+    if (flat) hipLaunchKernelGGL((k_split<NT, true>), g, t, 0, s, a...);
+    else hipLaunchKernelGGL((k_split<NT, false>), g, t, 0, s, a...);
+  } else {
+    constexpr int NT = kSliceLarge / 16;
+    if (flat) hipLaunchKernelGGL((k_split<NT, true>), g, t, 0, s, a...);
+    else hipLaunchKernelGGL((k_split<NT, false>), g, t, 0, s, a...);
+  }
+}
+
 struct WsLayout {
   uint64_t hist, slh, lenm, modes, eb, lay, rnodes, hdr, img, rbm, jobs, sizes, slots, tot, stat, total;
 };
@@ -1329,7 +1559,7 @@ struct WsLayout {
 WsLayout ws_layout(uint64_t n, const pivco_encode_opts *o) {
   WsLayout L{};
   const uint64_t nb = div_up(n, o->block_size);
-  const uint64_t spb = div_up(o->block_size, kHistSlice);
+  const uint64_t spb = div_up(o->block_size, slice_of(n, o->block_size));
   const uint64_t C = 1ull << o->rans_chunk_log2;
   const uint64_t bits = n * o->max_len;
   const uint64_t chunks = o->ans_mode ? bits / C + nb * 255 + 1 : 0;
@@ -1386,7 +1616,8 @@ pivco_status encode_enqueue(const void *d_in, uint64_t n, void *d_out, uint64_t 
   if (o->tree && !tree_is_complete(o->tree->code_len, o->max_len)) return PIVCO_E_ARG;
   const uint64_t bs = o->block_size;
   const uint64_t nb64 = div_up(n, bs);
-  const uint64_t spb64 = div_up(bs, kHistSlice);
+  const uint32_t slice = slice_of(n, o->block_size);
+  const uint64_t spb64 = div_up(bs, slice);
   if (nb64 > 0xFFFFFFFFull || nb64 * spb64 > 0x7FFFFFFFull) return PIVCO_E_ARG;
   const uint32_t nb = static_cast<uint32_t>(nb64), spb = static_cast<uint32_t>(spb64);
   const uint32_t flags = o->ans_mode == 3 ? 1u : 0u;
@@ -1425,7 +1656,7 @@ pivco_status encode_enqueue(const void *d_in, uint64_t n, void *d_out, uint64_t 
   hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, derr, 1u);
   hipLaunchKernelGGL(k_fill_zero, dim3(std::min<uint64_t>(4096, div_up(nb64 * 256, 256))), dim3(256), 0, s,
                      dh, nb64 * 256);
-  hipLaunchKernelGGL(k_hist, dim3(nb * spb), dim3(256), 0, s, in, n, static_cast<uint32_t>(bs), spb, dh, dslh);
+  hipLaunchKernelGGL(k_hist, dim3(nb * spb), dim3(256), 0, s, in, n, static_cast<uint32_t>(bs), slice, spb, dh, dslh);
   HIPCHK(hipGetLastError());
   if (spb > 1) hipLaunchKernelGGL(k_slice_prefix, dim3(nb), dim3(256), 0, s, dslh, spb, dh);
 
@@ -1438,7 +1669,7 @@ pivco_status encode_enqueue(const void *d_in, uint64_t n, void *d_out, uint64_t 
 
   // 3.-4. layout and offsets
   const uint32_t gl = (nb + kLayoutWaves - 1) / kLayoutWaves;
-  hipLaunchKernelGGL(k_layout, dim3(gl), dim3(kWaveE * kLayoutWaves), 0, s, dlenm, dmodes, dh, nb, n,
+  hipLaunchKernelGGL(k_layout, dim3(nb), dim3(256), 0, s, dlenm, dmodes, dh, nb, n,
                      static_cast<uint32_t>(bs), o->ans_mode, o->rans_chunk_log2, o->tree_shape,
                      ft ? ft->dmax : nullptr, deb, dlay, drn, ws + L.hdr);
   hipLaunchKernelGGL(k_scan, dim3(1), dim3(kScanNT), 0, s, dlay, nb, dtot);
@@ -1448,7 +1679,7 @@ pivco_status encode_enqueue(const void *d_in, uint64_t n, void *d_out, uint64_t 
   HIPCHK(hipGetLastError());
 
   // 5. bitmaps
-  hipLaunchKernelGGL(k_split, dim3(nb * spb), dim3(kSplitNT), 0, s, in, deb, dlay, nb, spb, dslh, dimg, drbm);
+  launch_split(slice, o->tree_shape != 0, nb * spb, s, in, deb, dlay, nb, spb, dslh, dh, dimg, drbm);
   HIPCHK(hipGetLastError());
 
   // 6. entropy-coded chunks
