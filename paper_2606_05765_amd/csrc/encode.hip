@@ -8,30 +8,28 @@
 //   1. k_hist        symbol histogram of every block and of every slice of it (end-to-end encode time is dominated by this
 //                    count, Sec. 4); k_slice_prefix turns the slice counts
 //                    into per-slice prefixes;
-//   2. k_tree        optimal length-limited lengths per block (package-merge,
-//                    one wave per block, the host's tie rules), or the
-//                    supplied tree;
-//   3. k_layout      per block, from its lengths and histogram: canonical
-//                    codes, breadth-first node table, n_v and n_right, the
-//                    rANS selection rule, body sizes and offsets, and the
-//                    block header bytes;
-//   4. k_scan        offsets of every block's areas (exclusive scans);
-//   5. k_split       per slice of a block: per level, every wave turns 64
+//   2. k_code        per block: optimal length-limited lengths (package-merge,
+//                    the host's tie rules) or the supplied tree, then from the
+//                    lengths and the histogram canonical codes, breadth-first
+//                    node table, n_v and n_right, the rANS selection rule,
+//                    body sizes and offsets, and the block header bytes;
+//   3. k_scan        offsets of every block's areas (exclusive scans);
+//   4. k_split       per slice of a block: per level, every wave turns 64
 //                    symbols at a time of the level's array into a 64-bit
 //                    ballot of code bits (LSB first = stream order) and moves
 //                    them to the children's places in LDS (stable); then the
 //                    nodes' bits go out word by word -- raw nodes straight
 //                    into the block's byte-packed raw image, rANS nodes into
 //                    word-aligned scratch;
-//   6. k_chunks      the entropy-coded chunk jobs; k_rans_enc codes them
+//   5. k_chunks      the entropy-coded chunk jobs; k_rans_enc codes them
 //                    (32-lane interleaved binary rANS, one wave per chunk,
 //                    steps in reverse order), or k_fse_enc (byte tANS);
-//   7. k_sizes       block sizes from the rANS body sizes; k_scan2 the block
+//   6. k_sizes       block sizes from the rANS body sizes; k_scan2 the block
 //                    offsets and the stream size;
-//   8. k_assemble    stream header, offset tables, block headers and raw
+//   7. k_assemble    stream header, offset tables, block headers and raw
 //                    images (aligned 4-byte words); k_assemble_rans the rANS
 //                    bodies.
-//   9. k_finish      the stream length and the call's status into device
+//   8. k_finish      the stream length and the call's status into device
 //                    memory.
 // Nothing waits on the host: pivco_encode_async leaves the length and status
 // in device memory; pivco_encode reads them back.
@@ -61,7 +59,7 @@ constexpr uint32_t kScanNT = 1024;
 constexpr uint32_t kErrArg = 1;          // a block's tree: PIVCO_E_ARG
 constexpr uint32_t kErrUnsupported = 2;  // a tANS cursor stream past its 16-bit length: PIVCO_E_UNSUPPORTED
 
-// Per-block description for the split kernel, written by k_layout.  Leaves
+// Per-block description for the split kernel, written by k_code.  Leaves
 // are numbered in code order (of the left-justified codes), so the symbols
 // that pass a node are the leaves of one interval.
 struct EncBlock {
@@ -90,7 +88,7 @@ struct EncBlock {
 };
 static_assert(sizeof(EncBlock) % 16 == 0, "EncBlock areas stay 16-byte aligned");
 
-// Per-block layout (k_layout), offsets (k_scan) and size (k_sizes, k_scan2).
+// Per-block layout (k_code), offsets (k_scan) and size (k_sizes, k_scan2).
 struct BlockLay {
   uint32_t n;             // symbols
   uint32_t hlen;          // header bytes
@@ -109,7 +107,7 @@ struct BlockLay {
   uint32_t pad;
 };
 
-// A rANS-coded node of a block, in node order (k_layout; blen and boff by
+// A rANS-coded node of a block, in node order (k_code; blen and boff by
 // k_sizes).
 struct RansNode {
   uint32_t rword;         // first word of its bitmap among the block's rANS words
@@ -281,199 +279,118 @@ __global__ __launch_bounds__(256) void k_slice_prefix(uint32_t *slh, uint32_t sp
   hist[static_cast<uint64_t>(blockIdx.x) * 256 + threadIdx.x] = run;
 }
 
-// Code lengths of every block on the device (one wave per block), the same
+// Code lengths of a block on the device (one thread per symbol), the same
 // package-merge and determinism rules as the host's lengths_from_counts
 // (items by weight; on equal weight a single before a package, symbols by
 // id, packages in creation order; the multiset of lengths handed out again
 // ascending to the symbols by (count desc, id asc)), in parallel form:
 //   * the present symbols are ranked by (count, id) by counting over all 256
-//     keys (a broadcast LDS read each), which also gives each symbol's run of
-//     equal counts;
-//   * row L holds the first min(m, 2m - 2) singles; row r - 1 merges the m
-//     singles with the packages (sums of consecutive pairs) of row r: single
-//     i lands at i + #(packages lighter than it), package j at j + #(singles
-//     no heavier), both by binary search, and positions past 2m - 2 are
-//     dropped.  Each row keeps the positions of its singles;
+//     keys (a broadcast LDS read each);
+//   * row L holds the m singles in that order; row r - 1 merges the singles
+//     with the packages (sums of consecutive pairs) of row r: single i lands
+//     at i + #(packages lighter than it), package j at j + #(singles no
+//     heavier), both by binary search, and positions past 2m - 2 are dropped.
+//     Each row keeps the positions of its singles;
 //   * buying the first k = 2m - 2 items of row 1 buys the singles placed
-//     below k and 2 (k - singles) items of the next row, and so on; a
-//     symbol's length is the number of rows in which it was bought.
-// A block with one symbol becomes a constant block; a supplied tree is
-// copied (a present symbol without a code is an argument error).  A block
-// in error gets the constant mode (nothing to split) and sets *err.
+//     below k and 2 (k - singles) items of the next row, and so on; single i
+//     is as deep as the rows that bought more than i singles, so the depths
+//     fall with i and the symbol that is the j-th by (count desc, id asc) gets
+//     the depth of single m - 1 - j.
+// A row costs two barriers and one round of searches (9 dependent LDS reads):
+// its latency, not work, is the kernel's time.  One block of 64 KiB: 24 us
+// with the layout, where one wave per block took 100 + 6; 4096 blocks 87 us,
+// was 312 + 22.  W is the weights' type: a
+// package's weight is at most the code length limit times the block's size,
+// and a key is a count and 8 bits of id, so 32 bits hold both below 2^24 symbols.
 constexpr uint32_t kTreeRows = kMaxLenGpu + 1;
 struct TreeSmem {
-  uint64_t key[256];          // (count << 8 | symbol); ~0 for an absent symbol
+  uint64_t key[256];          // (count << 8 | symbol); all ones for an absent symbol
   uint64_t w[256];            // counts in (count, id) order
   uint64_t row[2][512];       // item weights of two rows
   uint64_t pk[256];           // packages of the row below
   uint16_t spos[kTreeRows][256];   // row r: position of single i (0xFFFF: not in the row)
-  uint32_t rlen[kTreeRows];
 };
 
-__global__ __launch_bounds__(kWaveE) void k_tree(const uint32_t *hist, uint32_t nb, uint32_t L,
-                                                 pivco_tree tree, uint32_t use_tree, uint8_t *lenm,
-                                                 uint32_t *modes, uint32_t *err) {
-  __shared__ TreeSmem sm;
-  const uint32_t b = blockIdx.x, lane = __lane_id();
-  if (b >= nb) return;
-  uint32_t c[4];
-  bool pres[4];
-  uint32_t nsym = 0;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    c[e] = hist[256ull * b + 4 * lane + e];
-    pres[e] = c[e] != 0;
+template <class W>
+__device__ uint32_t tree_lengths(TreeSmem &sm, uint32_t c, uint32_t m, uint32_t L, bool *bad) {
+  const uint32_t t = threadIdx.x, lane = __lane_id();
+  W *key = reinterpret_cast<W *>(sm.key), *w = reinterpret_cast<W *>(sm.w), *pk = reinterpret_cast<W *>(sm.pk);
+  W *row[2] = {reinterpret_cast<W *>(sm.row[0]), reinterpret_cast<W *>(sm.row[1])};
+  const W mine = (static_cast<W>(c) << 8) | t;
+  key[t] = c ? mine : ~static_cast<W>(0);
+  __syncthreads();
+  uint32_t rank = 0;
+#pragma unroll 16
+  for (uint32_t i = 0; i < 256; ++i) rank += key[i] < mine ? 1u : 0u;
+  if (c) {
+    w[rank] = c;
+    row[L & 1][rank] = c;
   }
-  uint64_t bal[4];
+  sm.spos[L][t] = t < m ? static_cast<uint16_t>(t) : 0xFFFFu;
+  const uint32_t cap = 2 * m - 2;
+  uint32_t rl = m, rl_l = m;               // items of row r; lane r keeps its row's
+  __syncthreads();
+  const W x = w[t < m ? t : 0u];           // single t
+  // this symbol's run of equal counts: [lt, le)
+  uint32_t lt = 0, le = 0;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    bal[e] = __ballot(pres[e]);
-    nsym += static_cast<uint32_t>(__popcll(bal[e]));
+  for (uint32_t st = 256; st; st >>= 1) {
+    const uint32_t a = lt + st, b = le + st;
+    const W wa = w[a <= m ? a - 1 : 0u], wb = w[b <= m ? b - 1 : 0u];
+    lt = a <= m && wa < c ? a : lt;
+    le = b <= m && wb <= c ? b : le;
   }
-  const uint32_t m = nsym;
-  uint8_t *lb = lenm + 256ull * b;
-  if (use_tree) {
-    bool bad = false;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const uint8_t l = tree.code_len[4 * lane + e];
-      bad |= pres[e] && l == 0;
-      lb[4 * lane + e] = l;
-    }
-    const bool any = __ballot(bad) != 0;
-    if (lane == 0) {
-      modes[b] = any ? 1u : 0u;
-      if (any) atomicCAS(err, 0u, kErrArg);
-    }
-    return;
-  }
-  if (m == 1 || m == 0 || (m > (1u << L))) {   // constant block, or no code of this length exists
-    uint32_t sym = 256;                   // the smallest present symbol (the same in every lane)
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (bal[e]) {
-        const uint32_t cand = 4 * static_cast<uint32_t>(__ffsll(static_cast<long long>(bal[e])) - 1) + e;
-        sym = cand < sym ? cand : sym;
-      }
-    sym &= 255;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) lb[4 * lane + e] = 0;
-    if (lane == 0) {
-      modes[b] = 1u | (sym << 8);
-      if (m != 1) atomicCAS(err, 0u, kErrArg);
-    }
-    return;
-  }
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const uint32_t sy = 4 * lane + e;
-    sm.key[sy] = pres[e] ? (static_cast<uint64_t>(c[e]) << 8) | sy : ~0ull;
-  }
-  wave_sync();
-  // rank by (count, id), and the run of equal counts: [lt, le)
-  uint32_t rank[4] = {0, 0, 0, 0}, lt[4] = {0, 0, 0, 0}, le[4] = {0, 0, 0, 0};
-  for (uint32_t t = 0; t < 256; ++t) {
-    const uint64_t kt = sm.key[t];
-    const bool pt = kt != ~0ull;
-    const uint64_t ct = kt >> 8;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const uint64_t ke = (static_cast<uint64_t>(c[e]) << 8) | (4 * lane + e);
-      rank[e] += pt && kt < ke ? 1u : 0u;
-      lt[e] += pt && ct < c[e] ? 1u : 0u;
-      le[e] += pt && ct <= c[e] ? 1u : 0u;
-    }
-  }
-#pragma unroll
-  for (int e = 0; e < 4; ++e)
-    if (pres[e]) sm.w[rank[e]] = c[e];
-  const uint32_t cap = 2 * m - 2, top = m < cap ? m : cap;
-  for (uint32_t i = lane; i < 256; i += kWaveE) sm.spos[L][i] = i < top ? static_cast<uint16_t>(i) : 0xFFFFu;
-  if (lane == 0) sm.rlen[L] = top;
-  wave_sync();
-  for (uint32_t i = lane; i < top; i += kWaveE) sm.row[L & 1][i] = sm.w[i];
-  wave_sync();
-  uint32_t rl = top;
   for (uint32_t r = L; r > 1; --r) {
-    const uint64_t *cur = sm.row[r & 1];
-    uint64_t *nxt = sm.row[(r - 1) & 1];
+    const W *cur = row[r & 1];
+    W *nxt = row[(r - 1) & 1];
     const uint32_t np = rl / 2;
-    for (uint32_t j = lane; j < np; j += kWaveE) sm.pk[j] = cur[2 * j] + cur[2 * j + 1];
-    wave_sync();
+    W y = 0;
+    if (t < np) {
+      y = cur[2 * t] + cur[2 * t + 1];
+      pk[t] = y;
+    }
+    __syncthreads();
     const uint32_t total = m + np < cap ? m + np : cap;
-    for (uint32_t i = lane; i < m; i += kWaveE) {      // singles: packages strictly lighter come first
-      const uint64_t x = sm.w[i];
-      uint32_t lo = 0, hi = np;
-      while (lo < hi) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (sm.pk[mid] < x) lo = mid + 1; else hi = mid;
-      }
-      const uint32_t pos = i + lo;
-      if (pos < total) nxt[pos] = x;
-      sm.spos[r - 1][i] = pos < total ? static_cast<uint16_t>(pos) : 0xFFFFu;
+    uint32_t lo = 0, hi = 0;               // packages lighter than single t; singles no heavier than package t
+#pragma unroll
+    for (uint32_t st = 256; st; st >>= 1) {
+      const uint32_t a = lo + st, b = hi + st;
+      const W pa = pk[a <= np ? a - 1 : 0u], wb = w[b <= m ? b - 1 : 0u];
+      lo = a <= np && pa < x ? a : lo;
+      hi = b <= m && wb <= y ? b : hi;
     }
-    for (uint32_t j = lane; j < np; j += kWaveE) {     // packages: singles no heavier come first
-      const uint64_t y = sm.pk[j];
-      uint32_t lo = 0, hi = m;
-      while (lo < hi) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (sm.w[mid] <= y) lo = mid + 1; else hi = mid;
-      }
-      const uint32_t pos = j + lo;
-      if (pos < total) nxt[pos] = y;
-    }
-    if (lane == 0) sm.rlen[r - 1] = total;
+    const uint32_t ps = t + lo, pp = t + hi;
+    if (t < m && ps < total) nxt[ps] = x;
+    if (t < np && pp < total) nxt[pp] = y;
+    sm.spos[r - 1][t] = t < m && ps < total ? static_cast<uint16_t>(ps) : 0xFFFFu;
     rl = total;
-    wave_sync();
+    if (lane == r - 1) rl_l = rl;
+    __syncthreads();
   }
-  // bought items, row by row
-  uint32_t depth[4] = {0, 0, 0, 0};
-  bool bad = false;
-  uint32_t k = cap;
+  // bought items, row by row (every wave by itself, 4 singles a lane)
+  const uint32_t pd = (m - le) + (rank - lt), single = m - 1 - pd;
+  uint32_t len = 0, k = cap;
+  bool ok = false, over = false;
   for (uint32_t r = 1; r <= L && k; ++r) {
-    if (k > sm.rlen[r]) { bad = true; break; }
+    if (k > static_cast<uint32_t>(__builtin_amdgcn_readlane(rl_l, r))) { over = true; break; }
     uint32_t sg = 0;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const uint32_t i = 4 * lane + e;
-      sg += static_cast<uint32_t>(__popcll(__ballot(i < m && sm.spos[r][i] < k)));
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) depth[e] += 4 * lane + e < sg ? 1u : 0u;
+    for (uint32_t e = 0; e < 4; ++e) sg += static_cast<uint32_t>(__popcll(__ballot(sm.spos[r][64 * e + lane] < k)));
+    len += sg > single ? 1u : 0u;
+    ok |= sg >= m;
     k = 2 * (k - sg);
   }
-  // lengths: the ascending multiset to the symbols by (count desc, id asc)
-  uint32_t cum[kTreeRows + 1];
-  cum[0] = 0;
-  for (uint32_t l = 1; l <= L; ++l) {
-    uint32_t nl = 0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) nl += static_cast<uint32_t>(__popcll(__ballot(4 * lane + e < m && depth[e] == l)));
-    cum[l] = cum[l - 1] + nl;
-  }
-#pragma unroll
-  for (int e = 0; e < 4; ++e)
-    if (4 * lane + e < m && (depth[e] < 1 || depth[e] > L)) bad = true;
-  bad = __ballot(bad) != 0 || cum[L] != m;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    uint32_t len = 0;
-    if (pres[e]) {
-      const uint32_t pd = (m - le[e]) + (rank[e] - lt[e]);
-      for (uint32_t l = 1; l <= L; ++l)
-        if (len == 0 && cum[l] > pd) len = l;
-    }
-    lb[4 * lane + e] = bad ? 0 : static_cast<uint8_t>(len);
-  }
-  if (lane == 0) {
-    modes[b] = bad ? 1u : 0u;
-    if (bad) atomicCAS(err, 0u, kErrArg);
-  }
+  *bad = over || !ok;
+  return c && !*bad ? len : 0u;
 }
 
-// Layout of one block per workgroup, a thread per symbol, leaf or node.
-// lenm holds, per block, its 256 code lengths; modes its mode (0 coded, 1 |
-// symbol << 8 constant).  The code is canonical: with cnt(L) codes of length
+// Code of one block per workgroup, a thread per symbol, leaf or node: its
+// lengths (package-merge, or the supplied tree), then its layout.  A block
+// with one symbol becomes a constant block; a present symbol without a code
+// in the supplied tree is an argument error, and so are more symbols than
+// codes of the limit's length; a block in error gets the constant mode
+// (nothing to split) and sets *err.
+// The code is canonical: with cnt(L) codes of length
 // L and fc(L) the first of them, fc(L+1) = 2 (fc(L) + cnt(L)); a symbol's
 // code is fc(len) plus its rank among the symbols of its length; the internal
 // nodes at depth d are the prefixes [fc(d) + cnt(d), 2^d) numbered
@@ -486,11 +403,17 @@ __global__ __launch_bounds__(kWaveE) void k_tree(const uint32_t *hist, uint32_t 
 // depth's internal nodes.  A node's counts are differences of the counts'
 // prefix sums in leaf order at the ends of its leaf interval.
 struct LayoutSmem {
+  union {
+  TreeSmem tree;
+  struct {
   uint32_t wc[4][16];      // per wave: symbols of each length
   uint32_t cnt[18], ci[18], gn[18], fc[18], lvl[18], lb[18], kb[18];   // lb: leaves above depth d
   uint32_t pc[257];        // counts before each leaf
   uint16_t lo[256];
   uint32_t wsum[5][4];
+  };
+  };
+  uint64_t present[4];     // per wave: its present symbols
 };
 
 // Sum of the values of the waves before this one, and of all, for the five
@@ -507,12 +430,13 @@ __device__ __forceinline__ uint32_t waves_before(const uint32_t *w, uint32_t wav
   return b;
 }
 
-__global__ __launch_bounds__(256) void k_layout(
-    const uint8_t *lenm, const uint32_t *modes, const uint32_t *hist, uint32_t nb, uint64_t n,
-    uint32_t bs, uint32_t ans_mode, uint32_t chunk_log2, uint32_t shape, const uint8_t *fse_dmax,
-    EncBlock *eb, BlockLay *lay, RansNode *rnodes, uint8_t *hdr) {
+__global__ __launch_bounds__(256) void k_code(
+    const uint32_t *hist, uint32_t nb, uint64_t n, uint32_t bs, uint32_t max_len, pivco_tree tree,
+    uint32_t use_tree, uint32_t ans_mode, uint32_t chunk_log2, uint32_t shape, const uint8_t *fse_dmax,
+    EncBlock *eb, BlockLay *lay, RansNode *rnodes, uint8_t *hdr, uint32_t *err) {
   __shared__ LayoutSmem sm;
-  const uint32_t t = threadIdx.x, wave = t >> 6, lane = __lane_id();
+  const uint32_t t = threadIdx.x, lane = __lane_id();
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const uint32_t b = blockIdx.x;
   EncBlock &E = eb[b];
   BlockLay &Lb = lay[b];
@@ -520,7 +444,36 @@ __global__ __launch_bounds__(256) void k_layout(
   const uint64_t start = static_cast<uint64_t>(b) * bs;
   const uint32_t nblk = static_cast<uint32_t>(n - start < bs ? n - start : bs);
   const uint32_t cw = nblk <= 65535 ? 2u : 4u;
-  const uint32_t mode = modes[b];
+  const uint32_t c = hist[256ull * b + t];   // the symbol's count
+  // its length l, and the block's mode (0 coded, 1 | symbol << 8 constant)
+  uint32_t mode = 0, l = 0;
+  {
+    const uint64_t bal = __ballot(c != 0);
+    if (lane == 0) sm.present[wave] = bal;
+    __syncthreads();
+    uint32_t m = 0, sym = 0;
+#pragma unroll
+    for (int w = 3; w >= 0; --w) {
+      const uint64_t p = sm.present[w];
+      m += static_cast<uint32_t>(__popcll(p));
+      if (p) sym = 64 * w + static_cast<uint32_t>(__ffsll(static_cast<long long>(p))) - 1;
+    }
+    bool bad = false;
+    if (use_tree) {
+      l = tree.code_len[t];
+      bad = __syncthreads_or(c && l == 0);
+      mode = bad ? 1u : 0u;
+    } else if (m <= 1 || m > (1u << max_len)) {   // constant block, or no code of this length exists
+      mode = 1u | (sym << 8);
+      bad = m != 1;
+    } else {
+      l = nblk < (1u << 24) ? tree_lengths<uint32_t>(sm.tree, c, m, max_len, &bad)
+                            : tree_lengths<uint64_t>(sm.tree, c, m, max_len, &bad);
+      mode = bad ? 1u : 0u;
+      __syncthreads();                       // the tables of the layout take the same memory
+    }
+    if (bad && t == 0) atomicCAS(err, 0u, kErrArg);
+  }
   if (t == 0) {
     E.in_off = start;
     E.n = nblk;
@@ -541,8 +494,7 @@ __global__ __launch_bounds__(256) void k_layout(
     }
     return;
   }
-  // the symbol's length, count and rank among the symbols of its length
-  const uint32_t l = lenm[256ull * b + t], c = hist[256ull * b + t];
+  // the symbol's rank among the symbols of its length
   uint32_t rank = 0, wcl = 0;
 #pragma unroll
   for (uint32_t L = 1; L <= 15; ++L) {
@@ -1551,7 +1503,7 @@ void launch_split(uint32_t slice, bool flat, uint32_t grid, hipStream_t s, A... 
 }
 
 struct WsLayout {
-  uint64_t hist, slh, lenm, modes, eb, lay, rnodes, hdr, img, rbm, jobs, sizes, slots, tot, stat, total;
+  uint64_t hist, slh, eb, lay, rnodes, hdr, img, rbm, jobs, sizes, slots, tot, stat, total;
 };
 
 // Sizes from n and the options alone (the data is not known yet): every
@@ -1566,8 +1518,6 @@ WsLayout ws_layout(uint64_t n, const pivco_encode_opts *o) {
   uint64_t x = 0;
   L.hist = x; x = align_up(x + nb * 1024 + 16, 256);
   L.slh = x; x = align_up(x + nb * spb * 1024 + 16, 256);
-  L.lenm = x; x = align_up(x + nb * 256 + 16, 256);
-  L.modes = x; x = align_up(x + nb * 4 + 16, 256);
   L.eb = x; x = align_up(x + nb * sizeof(EncBlock), 256);
   L.lay = x; x = align_up(x + nb * sizeof(BlockLay), 256);
   L.rnodes = x; x = align_up(x + (o->ans_mode ? nb * 255 * sizeof(RansNode) : 0), 256);
@@ -1647,8 +1597,6 @@ pivco_status encode_enqueue(const void *d_in, uint64_t n, void *d_out, uint64_t 
   RansJob *djobs = reinterpret_cast<RansJob *>(ws + L.jobs);
   uint32_t *dsizes = reinterpret_cast<uint32_t *>(ws + L.sizes);
   uint32_t *derr = reinterpret_cast<uint32_t *>(ws + L.stat);
-  uint8_t *dlenm = ws + L.lenm;
-  uint32_t *dmodes = reinterpret_cast<uint32_t *>(ws + L.modes);
 
   // 1. histograms of the blocks and of their slices
   uint32_t *dh = reinterpret_cast<uint32_t *>(ws + L.hist);
@@ -1660,18 +1608,12 @@ pivco_status encode_enqueue(const void *d_in, uint64_t n, void *d_out, uint64_t 
   HIPCHK(hipGetLastError());
   if (spb > 1) hipLaunchKernelGGL(k_slice_prefix, dim3(nb), dim3(256), 0, s, dslh, spb, dh);
 
-  // 2. code lengths (package-merge per block, or the supplied tree)
+  // 2.-3. code lengths (package-merge per block, or the supplied tree), layout
   pivco_tree tree{};
   if (o->tree) tree = *o->tree;
-  hipLaunchKernelGGL(k_tree, dim3(nb), dim3(kWaveE), 0, s, dh, nb, o->max_len, tree, o->tree ? 1u : 0u,
-                     dlenm, dmodes, derr);
-  HIPCHK(hipGetLastError());
-
-  // 3.-4. layout and offsets
-  const uint32_t gl = (nb + kLayoutWaves - 1) / kLayoutWaves;
-  hipLaunchKernelGGL(k_layout, dim3(nb), dim3(256), 0, s, dlenm, dmodes, dh, nb, n,
-                     static_cast<uint32_t>(bs), o->ans_mode, o->rans_chunk_log2, o->tree_shape,
-                     ft ? ft->dmax : nullptr, deb, dlay, drn, ws + L.hdr);
+  hipLaunchKernelGGL(k_code, dim3(nb), dim3(256), 0, s, dh, nb, n, static_cast<uint32_t>(bs), o->max_len, tree,
+                     o->tree ? 1u : 0u, o->ans_mode, o->rans_chunk_log2, o->tree_shape,
+                     ft ? ft->dmax : nullptr, deb, dlay, drn, ws + L.hdr, derr);
   hipLaunchKernelGGL(k_scan, dim3(1), dim3(kScanNT), 0, s, dlay, nb, dtot);
   uint32_t *dimg = reinterpret_cast<uint32_t *>(ws + L.img);
   uint32_t *drbm = reinterpret_cast<uint32_t *>(ws + L.rbm);
@@ -1685,7 +1627,7 @@ pivco_status encode_enqueue(const void *d_in, uint64_t n, void *d_out, uint64_t 
   // 6. entropy-coded chunks
   const bool ans = o->ans_mode != 0;
   if (ans) {
-    hipLaunchKernelGGL(k_chunks, dim3(gl), dim3(kWaveE * kLayoutWaves), 0, s, dlay, drn, nb,
+    hipLaunchKernelGGL(k_chunks, dim3(div_up(nb, kLayoutWaves)), dim3(kWaveE * kLayoutWaves), 0, s, dlay, drn, nb,
                        o->rans_chunk_log2, djobs);
     if (ft)
       hipLaunchKernelGGL(k_fse_enc, dim3(2048), dim3(kFseEncNT), 0, s, djobs, dtot, drbm, ft->enc,

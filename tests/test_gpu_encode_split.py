@@ -46,3 +46,9 @@ def test_small_slices(kind, n, bs, flat):
 def test_large_slices(bs, ans, flat):
     x = _source("zipf", (8 << 20) + 4321, bs)
     _check(x, bs, ans, flat)
+
+
+def test_block_of_2_24_symbols():
+    """Counts past 24 bits take the 64-bit weights of the code lengths."""
+    x = _source("zipf", (1 << 24) + 5, 3)
+    _check(x, x.size, 0, False)
