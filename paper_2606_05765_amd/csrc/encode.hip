@@ -13,24 +13,25 @@
 //                    lengths and the histogram canonical codes, breadth-first
 //                    node table, n_v and n_right, the rANS selection rule,
 //                    body sizes and offsets, and the block header bytes;
-//   3. k_scan        offsets of every block's areas (exclusive scans);
+//   3. k_scan        offsets of every block's areas (exclusive scans); a call
+//                    of one block finds them in k_code;
 //   4. k_split       per slice of a block: per level, every wave turns 64
 //                    symbols at a time of the level's array into a 64-bit
 //                    ballot of code bits (LSB first = stream order) and moves
 //                    them to the children's places in LDS (stable); then the
-//                    nodes' bits go out word by word -- raw nodes straight
-//                    into the block's byte-packed raw image, rANS nodes into
-//                    word-aligned scratch;
-//   5. k_chunks      the entropy-coded chunk jobs; k_rans_enc codes them
-//                    (32-lane interleaved binary rANS, one wave per chunk,
-//                    steps in reverse order), or k_fse_enc (byte tANS);
+//                    nodes' bits go out word by word.
+// Without entropy-coded nodes the blocks' places in the stream are known by
+// then: k_head writes the headers and k_split the bodies.  With them k_split
+// fills a byte-packed raw image per block and word-aligned rANS bitmaps, and
+//   5. k_rans_enc    codes the chunks (32-lane interleaved binary rANS, one wave
+//                    per chunk, steps in reverse order), or k_fse_enc (byte
+//                    tANS);
 //   6. k_sizes       block sizes from the rANS body sizes; k_scan2 the block
-//                    offsets and the stream size;
-//   7. k_assemble    stream header, offset tables, block headers and raw
-//                    images (aligned 4-byte words); k_assemble_rans the rANS
-//                    bodies.
-//   8. k_finish      the stream length and the call's status into device
-//                    memory.
+//                    offsets and the stream size (and the sizes of few
+//                    blocks);
+//   7. k_assemble    stream header, offset tables, block headers, raw images
+//                    (aligned 4-byte words) and rANS bodies.
+// The stream length and the call's status go to device memory with the sizes.
 // Nothing waits on the host: pivco_encode_async leaves the length and status
 // in device memory; pivco_encode reads them back.
 #include <hip/hip_runtime.h>
@@ -48,12 +49,11 @@ bool tree_is_complete(const uint8_t len[256], uint32_t max_len);
 namespace {
 
 constexpr int kWaveE = 64;
-// Symbols of a slice (a histogram row, a split workgroup): 16 per thread of
-// the split kernel.
+// Symbols of a slice (a histogram row, a split workgroup).
 constexpr uint32_t kSliceSmall = 1u << 12, kSliceLarge = 1u << 13;
 constexpr uint32_t kHdrStride = 1216;   // block header bytes: 12 + 128 + 32 + 4 * 255 <= this
-constexpr uint32_t kLayoutWaves = 4;
-constexpr uint32_t kAsmSeg = 16384;     // output words per assembling workgroup
+constexpr uint32_t kAsmSeg = 2048;      // output words per assembling workgroup: 8 a thread
+constexpr uint32_t kTailBlocks = 64;    // blocks whose sizes and offsets one workgroup finds
 constexpr uint32_t kScanNT = 1024;
 // Error word of one encode (in its status area); the first error wins.
 constexpr uint32_t kErrArg = 1;          // a block's tree: PIVCO_E_ARG
@@ -88,7 +88,8 @@ struct EncBlock {
 };
 static_assert(sizeof(EncBlock) % 16 == 0, "EncBlock areas stay 16-byte aligned");
 
-// Per-block layout (k_code), offsets (k_scan) and size (k_sizes, k_scan2).
+// Per-block layout (k_code), offsets (k_scan) and size (without entropy-coded
+// nodes k_code, else k_sizes and k_scan2).
 struct BlockLay {
   uint32_t n;             // symbols
   uint32_t hlen;          // header bytes
@@ -97,7 +98,8 @@ struct BlockLay {
   uint32_t n_rnodes;      // rANS-coded nodes
   uint32_t n_chunks;      // their chunks
   uint64_t slot_bytes;    // output slot bytes of its chunks
-  uint64_t img_off;       // its raw image in the image area (bytes, 16-aligned)
+  uint64_t img_off;       // its raw image in the image area (bytes, 16-aligned); without
+                          // entropy-coded nodes in the stream itself
   uint64_t rbm_off;       // its rANS bitmaps in the rANS bitmap area (words)
   uint64_t chunk0;        // its first chunk job
   uint64_t slot0;         // its first slot byte
@@ -107,16 +109,13 @@ struct BlockLay {
   uint32_t pad;
 };
 
-// A rANS-coded node of a block, in node order (k_code; blen and boff by
-// k_sizes).
+// A rANS-coded node of a block, in node order (k_code).
 struct RansNode {
   uint32_t rword;         // first word of its bitmap among the block's rANS words
   uint32_t nv;            // bits
   uint32_t p1q;           // 12-bit probability of a 1 bit (ans_mode 3: the tANS marker)
   uint32_t ch0;           // its first chunk among the block's chunks
   uint64_t sl0;           // its first slot byte among the block's slots
-  uint32_t blen;          // body bytes (all its chunks)
-  uint32_t boff;          // offset of its 8-byte body header in the block
 };
 
 struct RansJob {
@@ -199,65 +198,67 @@ __host__ __device__ __forceinline__ uint32_t slot_size(uint32_t nbits) {
 // ---------------------------------------------------------------------------
 // kernels
 // ---------------------------------------------------------------------------
-__global__ void k_fill_zero(uint32_t *p, uint64_t nwords) {
-  for (uint64_t i = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; i < nwords;
-       i += static_cast<uint64_t>(gridDim.x) * blockDim.x)
-    p[i] = 0;
+// 16 bytes at a time; n16 of them.
+__device__ __forceinline__ void fill_zero16(uint4 *p, uint64_t n16, uint64_t t, uint64_t step) {
+  for (uint64_t i = t; i < n16; i += step) p[i] = make_uint4(0, 0, 0, 0);
 }
 
 // Zeroes the image and rANS bitmap areas up to the sizes k_scan found (the
-// split kernel ORs bits into them).
-__global__ void k_zero_areas(uint32_t *img, uint32_t *rbm, const Totals *tot) {
-  const uint64_t ni = tot->img_bytes / 4, nr = tot->rbm_words;
-  const uint64_t step = static_cast<uint64_t>(gridDim.x) * blockDim.x;
-  for (uint64_t i = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; i < ni + nr; i += step) {
-    if (i < ni) img[i] = 0;
-    else rbm[i - ni] = 0;
-  }
+// split kernel ORs bits into them).  Both areas are 256-byte aligned with
+// slack past their ends.
+__global__ __launch_bounds__(256) void k_zero_areas(uint32_t *img, uint32_t *rbm, const Totals *tot) {
+  const uint64_t t = blockIdx.x * 256ull + threadIdx.x, step = gridDim.x * 256ull;
+  fill_zero16(reinterpret_cast<uint4 *>(img), (tot->img_bytes + 15) / 16, t, step);
+  fill_zero16(reinterpret_cast<uint4 *>(rbm), (tot->rbm_words + 3) / 4, t, step);
 }
 
-// Histogram of every block, one workgroup per slice:
-// the slice's counts go to its own row of slh (the split kernel's slices
-// start at the same boundaries); a block of one slice also writes them to
-// its row of hist (k_slice_prefix writes the totals of larger blocks).
+// Histogram of every block, one workgroup per slice: the slice's counts go to
+// its own row of slh (the split kernel's slices start at the same
+// boundaries); a block of one slice also writes them to its row of hist
+// (k_slice_prefix writes the totals of larger blocks).  Lanes of equal
+// symbols count in kHistCopies places, so that a frequent symbol does not
+// serialise the LDS atomics (64 MiB with one symbol at 0.9: 207 -> 31 us,
+// 256 MiB Zipf 206 -> 92 us).  The call's error word and, where zero16 is
+// not 0, the areas that the split kernel ORs into are cleared here too.
+constexpr int kHistCopies = 16;
 __global__ __launch_bounds__(256) void k_hist(const uint8_t *in, uint64_t n, uint32_t bs, uint32_t slice,
-                                              uint32_t spb, uint32_t *hist, uint32_t *slh) {
-  __shared__ uint32_t h[4][256];
-  const int tid = threadIdx.x, w = tid >> 6;
-  for (int i = tid; i < 1024; i += 256) (&h[0][0])[i] = 0;
+                                              uint32_t spb, uint32_t *hist, uint32_t *slh, uint32_t *err,
+                                              uint4 *areas, uint64_t zero16) {
+  __shared__ uint32_t h[kHistCopies][257];
+  const uint32_t tid = threadIdx.x;
+  if (blockIdx.x == 0 && tid == 0) *err = 0;
+  fill_zero16(areas, zero16, blockIdx.x * 256ull + tid, gridDim.x * 256ull);
+  for (uint32_t i = tid; i < kHistCopies * 257; i += 256) (&h[0][0])[i] = 0;
   __syncthreads();
   const uint64_t b = blockIdx.x / spb, sl = blockIdx.x % spb;
   const uint64_t bstart = b * bs;
   const uint64_t bend = bstart + bs < n ? bstart + bs : n;
   const uint64_t s0 = bstart + sl * slice;
-  const uint64_t s1 = s0 + slice < bend ? s0 + slice : bend;
-  if (s0 < s1) {
-    // aligned middle with dword loads, byte loads at the edges
-    const uint64_t a0 = (s0 + 3) & ~3ull, a1 = s1 & ~3ull;
-    for (uint64_t i = s0 + tid; i < s1 && i < a0; i += 256) atomicAdd(&h[w][in[i]], 1u);
-    if (a0 < a1) {
-      const uint32_t *in4 = reinterpret_cast<const uint32_t *>(in + a0);
-      const uint64_t nd = (a1 - a0) >> 2;
-      for (uint64_t i = tid; i < nd; i += 256) {
-        const uint32_t v = in4[i];
-        atomicAdd(&h[w][v & 255], 1u);
-        atomicAdd(&h[w][(v >> 8) & 255], 1u);
-        atomicAdd(&h[w][(v >> 16) & 255], 1u);
-        atomicAdd(&h[w][v >> 24], 1u);
-      }
+  const uint32_t len = s0 >= bend ? 0u : bend - s0 < slice ? static_cast<uint32_t>(bend - s0) : slice;
+  const uint8_t *p = in + s0;
+  uint32_t *hc = h[tid % kHistCopies];
+  for (uint32_t i = 16 * tid; i < len; i += 16 * 256) {
+    if (i + 16 <= len) {
+      uint32_t w[4];
+      __builtin_memcpy(w, p + i, 16);         // no alignment
+#pragma unroll
+      for (int e = 0; e < 16; ++e) atomicAdd(&hc[(w[e >> 2] >> (8 * (e & 3))) & 255], 1u);
+    } else {
+      for (uint32_t e = i; e < len; ++e) atomicAdd(&hc[p[e]], 1u);
     }
-    for (uint64_t i = (a1 > a0 ? a1 : a0) + tid; i < s1; i += 256) atomicAdd(&h[w][in[i]], 1u);
   }
   __syncthreads();
-  const uint32_t v = h[0][tid] + h[1][tid] + h[2][tid] + h[3][tid];
+  uint32_t v = 0;
+#pragma unroll
+  for (int j = 0; j < kHistCopies; ++j) v += h[j][tid];
   slh[static_cast<uint64_t>(blockIdx.x) * 256 + tid] = v;
   if (spb == 1) hist[b * 256 + tid] = v;
 }
 
 // Per block, the slice histograms become exclusive prefixes: row k holds the
 // count of each symbol in the block's slices before slice k, and the block's
-// row of hist the totals (one thread per symbol, one workgroup per block;
-// 16 rows read before any is rewritten).
+// row of hist the totals.  Few rows: a workgroup per block, a thread per
+// symbol, 16 rows read before any is rewritten.
 __global__ __launch_bounds__(256) void k_slice_prefix(uint32_t *slh, uint32_t spb, uint32_t *hist) {
   uint32_t *row = slh + static_cast<uint64_t>(blockIdx.x) * spb * 256 + threadIdx.x;
   uint32_t run = 0, k = 0;
@@ -278,6 +279,95 @@ __global__ __launch_bounds__(256) void k_slice_prefix(uint32_t *slh, uint32_t sp
   }
   hist[static_cast<uint64_t>(blockIdx.x) * 256 + threadIdx.x] = run;
 }
+
+// Many rows (past kPrefixRows): one workgroup cannot draw a block's rows fast
+// enough (1024 rows, 1 MiB: 38 us), so a block has 16 workgroups of 16
+// symbols, and 64 shares of the rows in each; a share is summed, then
+// rewritten from the sums of the shares before it.
+constexpr uint32_t kPrefixRows = 48;
+__global__ __launch_bounds__(1024) void k_slice_prefix_wide(uint32_t *slh, uint32_t spb, uint32_t *hist) {
+  __shared__ uint32_t sums[64][17];
+  const uint32_t b = blockIdx.x >> 4, sym = 16 * (blockIdx.x & 15) + (threadIdx.x & 15), g = threadIdx.x >> 4;
+  uint32_t *row = slh + static_cast<uint64_t>(b) * spb * 256 + sym;
+  const uint32_t per = (spb + 63) / 64;
+  const uint32_t r0 = g * per < spb ? g * per : spb, r1 = r0 + per < spb ? r0 + per : spb;
+  constexpr uint32_t kB = 16;
+  uint32_t c[kB], run = 0;
+  for (uint32_t r = r0; r < r1; r += kB) {
+#pragma unroll
+    for (uint32_t j = 0; j < kB; ++j) c[j] = r + j < r1 ? row[256ull * (r + j)] : 0u;
+#pragma unroll
+    for (uint32_t j = 0; j < kB; ++j) run += c[j];
+  }
+  sums[g][threadIdx.x & 15] = run;
+  __syncthreads();
+  if (threadIdx.x < 16) {
+    uint32_t at = 0;
+    for (uint32_t i = 0; i < 64; ++i) {
+      const uint32_t v = sums[i][threadIdx.x];
+      sums[i][threadIdx.x] = at;
+      at += v;
+    }
+    hist[256ull * b + sym] = at;
+  }
+  __syncthreads();
+  run = sums[g][threadIdx.x & 15];
+  for (uint32_t r = r0; r < r1; r += kB) {
+    if (per > kB) {                          // else they are still here
+#pragma unroll
+      for (uint32_t j = 0; j < kB; ++j) c[j] = r + j < r1 ? row[256ull * (r + j)] : 0u;
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < kB; ++j)
+      if (r + j < r1) {
+        row[256ull * (r + j)] = run;
+        run += c[j];
+      }
+  }
+}
+
+// The call's result on the device: the stream length (also when it exceeds
+// out_cap, in which case nothing is written) and a status.  One thread, after
+// every kernel that may set the error word.
+struct Result {
+  uint64_t out_cap;
+  uint64_t *d_len;
+  int32_t *d_status;
+};
+__device__ void finish(uint64_t n, uint32_t *err, const Result &r) {
+  const uint32_t e = atomicAdd(err, 0u);
+  *r.d_len = n;
+  *r.d_status = e == kErrArg ? PIVCO_E_ARG : e ? PIVCO_E_UNSUPPORTED : n > r.out_cap ? PIVCO_E_CAPACITY : PIVCO_OK;
+}
+
+// Exclusive sum over a workgroup of kScanNT threads; *all gets the sum.
+__device__ __forceinline__ uint64_t block_excl_scan(uint64_t v, uint64_t *part, uint64_t *all) {
+  const uint32_t wave = threadIdx.x >> 6, lane = __lane_id();
+  uint64_t x = v;
+#pragma unroll
+  for (int o = 1; o < kWaveE; o <<= 1) {
+    const uint64_t y = __shfl_up(x, o, kWaveE);
+    if (lane >= static_cast<uint32_t>(o)) x += y;
+  }
+  if (lane == kWaveE - 1) part[wave] = x;
+  __syncthreads();
+  uint64_t before = 0, sum = 0;
+  for (uint32_t w = 0; w < kScanNT / kWaveE; ++w) {
+    const uint64_t q = part[w];
+    before += w < wave ? q : 0u;
+    sum += q;
+  }
+  *all = sum;
+  __syncthreads();
+  return before + x - v;
+}
+
+__host__ __device__ __forceinline__ uint64_t stream_tables(uint64_t nb) { return kHeaderBytes + 16 * (nb + 1); }
+
+// Area of a block's raw image (16-aligned, with 16 bytes of slack) and of its
+// rANS bitmap words.
+__device__ __forceinline__ uint64_t img_area(const BlockLay &L) { return (static_cast<uint64_t>(L.raw_bytes) + 16 + 15) & ~15ull; }
+__device__ __forceinline__ uint64_t rbm_area(const BlockLay &L) { return (static_cast<uint64_t>(L.ans_words) + 3) & ~3ull; }
 
 // Code lengths of a block on the device (one thread per symbol), the same
 // package-merge and determinism rules as the host's lengths_from_counts
@@ -430,10 +520,37 @@ __device__ __forceinline__ uint32_t waves_before(const uint32_t *w, uint32_t wav
   return b;
 }
 
+// The end of a block's layout (one thread).  Without entropy-coded nodes its
+// size is known here; a call of one block places it here too, what k_scan
+// does for more.
+__device__ void block_done(uint32_t ans_mode, uint32_t nb, BlockLay &L, uint8_t *H, uint32_t *err, Totals *tot,
+                           const Result &res) {
+  if (ans_mode == 0) {
+    L.comp = L.hlen + L.raw_bytes;
+    *reinterpret_cast<uint32_t *>(H) = L.comp;
+  }
+  if (nb != 1) return;
+  L.ans0 = 0;
+  if (ans_mode == 0) {
+    L.out_off = stream_tables(1);
+    L.img_off = L.out_off + L.hlen;
+    tot->ans_words = 0;
+    tot->out_bytes = L.out_off + ((static_cast<uint64_t>(L.comp) + 3) & ~3ull);
+    finish(tot->out_bytes, err, res);
+  } else {
+    L.img_off = L.rbm_off = L.chunk0 = L.slot0 = 0;
+    tot->img_bytes = img_area(L);
+    tot->rbm_words = rbm_area(L);
+    tot->chunks = L.n_chunks;
+    tot->slot_bytes = L.slot_bytes;
+    tot->ans_words = L.ans_words;
+  }
+}
+
 __global__ __launch_bounds__(256) void k_code(
     const uint32_t *hist, uint32_t nb, uint64_t n, uint32_t bs, uint32_t max_len, pivco_tree tree,
     uint32_t use_tree, uint32_t ans_mode, uint32_t chunk_log2, uint32_t shape, const uint8_t *fse_dmax,
-    EncBlock *eb, BlockLay *lay, RansNode *rnodes, uint8_t *hdr, uint32_t *err) {
+    EncBlock *eb, BlockLay *lay, RansNode *rnodes, uint8_t *hdr, uint32_t *err, Totals *tot, Result res) {
   __shared__ LayoutSmem sm;
   const uint32_t t = threadIdx.x, lane = __lane_id();
   const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -491,6 +608,7 @@ __global__ __launch_bounds__(256) void k_code(
       Lb.hlen = kBlockFixed;
       Lb.raw_bytes = Lb.ans_words = Lb.n_rnodes = Lb.n_chunks = 0;
       Lb.slot_bytes = 0;
+      block_done(ans_mode, nb, Lb, H, err, tot, res);
     }
     return;
   }
@@ -692,8 +810,6 @@ __global__ __launch_bounds__(256) void k_code(
     r.p1q = ans_mode == 3 ? mk : p1q_of(nv, nr);
     r.ch0 = ex[3];
     r.sl0 = 16ull * ex[4];
-    r.blen = 0;
-    r.boff = 0;
     rnodes[255ull * b + ex[2]] = r;
   }
   // header: code lengths (two nibbles a byte, symbol 2j low), kind bits, counts of 1 bits
@@ -716,56 +832,65 @@ __global__ __launch_bounds__(256) void k_code(
     Lb.n_rnodes = all[2];
     Lb.n_chunks = all[3];
     Lb.slot_bytes = 16ull * all[4];
+    block_done(ans_mode, nb, Lb, H, err, tot, res);
   }
 }
 
-// Exclusive scans over the blocks (one workgroup): image bytes (16-aligned,
-// with 16 bytes of slack), rANS bitmap words (multiples of 4), chunk jobs,
-// slot bytes and scratch words; their totals.
-__global__ __launch_bounds__(kScanNT) void k_scan(BlockLay *lay, uint32_t nb, Totals *tot) {
-  __shared__ uint64_t part[5][kScanNT];
+// Exclusive scans over the blocks (one workgroup, a block per thread): with
+// entropy-coded nodes image bytes, rANS bitmap words, chunk jobs, slot bytes
+// and scratch words, and their totals; without them the blocks' places in the
+// stream, and the call's result.
+__global__ __launch_bounds__(kScanNT) void k_scan(BlockLay *lay, uint32_t nb, uint32_t ans_mode, Totals *tot,
+                                                  uint32_t *err, Result res) {
+  __shared__ uint64_t part[kScanNT / kWaveE];
   const uint32_t tid = threadIdx.x;
-  const uint32_t per = (nb + kScanNT - 1) / kScanNT;
-  const uint32_t b0 = tid * per, b1 = b0 + per < nb ? b0 + per : nb;
-  uint64_t v[5] = {0, 0, 0, 0, 0};
-  for (uint32_t b = b0; b < b1; ++b) {
-    const BlockLay &L = lay[b];
-    v[0] += (static_cast<uint64_t>(L.raw_bytes) + 16 + 15) & ~15ull;
-    v[1] += (static_cast<uint64_t>(L.ans_words) + 3) & ~3ull;
-    v[2] += L.n_chunks;
-    v[3] += L.slot_bytes;
-    v[4] += L.ans_words;
+  uint64_t run[5] = {ans_mode ? 0ull : stream_tables(nb), 0, 0, 0, 0};
+  for (uint64_t b0 = 0; b0 < nb; b0 += kScanNT) {
+    const uint64_t b = b0 + tid;
+    uint64_t v[5] = {0, 0, 0, 0, 0}, x[5], all[5];
+    if (b < nb) {
+      const BlockLay &L = lay[b];
+      if (ans_mode) {
+        v[0] = img_area(L);
+        v[1] = rbm_area(L);
+        v[2] = L.n_chunks;
+        v[3] = L.slot_bytes;
+        v[4] = L.ans_words;
+      } else {
+        v[0] = (static_cast<uint64_t>(L.comp) + 3) & ~3ull;
+      }
+    }
+    for (int q = 0; q < 5; ++q) {
+      if (q && !ans_mode) break;
+      x[q] = run[q] + block_excl_scan(v[q], part, &all[q]);
+      run[q] += all[q];
+    }
+    if (b < nb) {
+      BlockLay &L = lay[b];
+      if (ans_mode) {
+        L.img_off = x[0];
+        L.rbm_off = x[1];
+        L.chunk0 = x[2];
+        L.slot0 = x[3];
+        L.ans0 = x[4];
+      } else {
+        L.out_off = x[0];
+        L.img_off = x[0] + L.hlen;
+        L.ans0 = 0;
+      }
+    }
   }
-  for (int q = 0; q < 5; ++q) part[q][tid] = v[q];
-  __syncthreads();
-  for (uint32_t off = 1; off < kScanNT; off <<= 1) {   // inclusive scan (Hillis-Steele)
-    uint64_t a[5];
-    for (int q = 0; q < 5; ++q) a[q] = tid >= off ? part[q][tid - off] : 0ull;
-    __syncthreads();
-    for (int q = 0; q < 5; ++q) part[q][tid] += a[q];
-    __syncthreads();
-  }
-  uint64_t run[5];
-  for (int q = 0; q < 5; ++q) run[q] = part[q][tid] - v[q];
-  for (uint32_t b = b0; b < b1; ++b) {
-    BlockLay &L = lay[b];
-    L.img_off = run[0];
-    L.rbm_off = run[1];
-    L.chunk0 = run[2];
-    L.slot0 = run[3];
-    L.ans0 = run[4];
-    run[0] += (static_cast<uint64_t>(L.raw_bytes) + 16 + 15) & ~15ull;
-    run[1] += (static_cast<uint64_t>(L.ans_words) + 3) & ~3ull;
-    run[2] += L.n_chunks;
-    run[3] += L.slot_bytes;
-    run[4] += L.ans_words;
-  }
-  if (tid == kScanNT - 1) {
-    tot->img_bytes = part[0][tid];
-    tot->rbm_words = part[1][tid];
-    tot->chunks = part[2][tid];
-    tot->slot_bytes = part[3][tid];
-    tot->ans_words = part[4][tid];
+  if (tid != 0) return;
+  if (ans_mode) {
+    tot->img_bytes = run[0];
+    tot->rbm_words = run[1];
+    tot->chunks = run[2];
+    tot->slot_bytes = run[3];
+    tot->ans_words = run[4];
+  } else {
+    tot->ans_words = 0;
+    tot->out_bytes = run[0];
+    finish(run[0], err, res);
   }
 }
 
@@ -777,12 +902,32 @@ __device__ __forceinline__ void lds_sync() {
 }
 
 static_assert(kMaxLenGpu <= 12, "code bits of a symbol");
-constexpr int kSplitCh = 16;             // 64-symbol chunks of one wave, at most
+// The chunk jobs of a block's rANS nodes, a node per thread of nt.
+__device__ void chunk_jobs(const BlockLay &L, const RansNode *rnodes, uint32_t b, uint32_t chunk_log2, uint32_t nt,
+                           RansJob *jobs) {
+  const uint32_t C = 1u << chunk_log2;
+  for (uint32_t r = threadIdx.x; r < L.n_rnodes; r += nt) {
+    const RansNode rn = rnodes[r];
+    uint32_t k = 0;
+    for (uint64_t st = 0; st < rn.nv; st += C, ++k) {
+      RansJob j;
+      j.bmp_word = L.rbm_off + rn.rword + st / 32;
+      j.slot = L.slot0 + rn.sl0 + static_cast<uint64_t>(k) * slot_size(C);
+      j.nbits = rn.nv - st < C ? static_cast<uint32_t>(rn.nv - st) : C;
+      j.p1q = rn.p1q;
+      j.block = b;
+      j.rnode = r;
+      j.first = st == 0;
+      j.dst = 0;
+      jobs[L.chunk0 + rn.ch0 + k] = j;
+    }
+  }
+}
+
 constexpr uint32_t kEndsHere = 0x7F00;   // SplitSmem::K of a leaf: past every place
 
-template <int NT>
+template <int NT, uint32_t S>
 struct SplitSmem {
-  static constexpr uint32_t S = 16 * NT;
   uint16_t buf[S + 64 * 4];            // a level's codes, in its nodes' order (groups of 4 chunks read past its end)
   union {
     uint32_t bits[13 * S / 32 + 2 * 16 + 4];   // every level's bits, then the flat nodes' fields
@@ -807,7 +952,7 @@ __device__ __forceinline__ uint32_t bits32(const uint32_t *w, uint32_t x) {
   return __builtin_amdgcn_alignbit(w[(x >> 5) + 1], w[x >> 5], x & 31);
 }
 
-// One workgroup per slice of 16 NT symbols of a block (slice k of block b is
+// One workgroup per slice of kSlice symbols of a block (slice k of block b is
 // workgroup b * spb + k).
 //   Nodes: the slice's counts (from the prefix histograms) summed in leaf
 // order give every node's symbols and 1 bits in the slice, and the symbols
@@ -825,45 +970,51 @@ __device__ __forceinline__ uint32_t bits32(const uint32_t *w, uint32_t x) {
 //   Output: the nodes' bits are copied out of the level arrays word by word,
 // at the bit where the node's earlier slices end.  A raw node goes to its
 // byte offset in the block's raw image (the stream layout), a rANS node to its
-// word among the block's rANS bitmap words.  A word that this slice does not
-// fill is ORed into zeroed memory, the others are stored.
+// word among the block's rANS bitmap words; without entropy-coded nodes
+// (direct: the stream's totals) img is the stream itself, where the blocks'
+// places are known and k_head has zeroed the bodies.  A word that this slice
+// does not fill is ORed into zeroed memory, the others are stored.
+//   The first slice's workgroup also lists the block's chunk jobs.
 // Bound by vector instructions, about 17 per 64 symbols and level, and by the
 // latency of the small levels (two barriers each).  256 MiB Zipf(1.1) in 64
-// KiB blocks: 1.52 ms where one wave per node (the root's 4096 symbols on one
-// wave of four) took 4.15 ms; one 64 KiB block: 22 us, was 86.  LDS holds one
+// KiB blocks: 1.38 ms where one wave per node (the root's 4096 symbols on one
+// wave of four) took 4.15 ms; one 64 KiB block: 18 us, was 86.  LDS holds one
 // level buffer (a level is in registers before it moves) and no more tables
 // than the levels need, for 6 workgroups of 256 threads on a CU: with two
 // buffers and the tables beside them (4 workgroups) and the block's tables
 // read in a chain it took 2.7 ms.
-template <int NT, bool FLAT>
+template <int NT, uint32_t kSlice, bool FLAT>
 __global__ __launch_bounds__(NT) void k_split(const uint8_t *in, const EncBlock *blocks,
                                               const BlockLay *lay, uint32_t nblocks, uint32_t spb,
                                               const uint32_t *pre, const uint32_t *hist, uint32_t *img,
-                                              uint32_t *rbm) {
-  constexpr uint32_t kSlice = 16 * NT;
+                                              uint32_t *rbm, const Totals *direct, uint64_t out_cap,
+                                              const RansNode *rnodes, uint32_t chunk_log2, RansJob *jobs) {
   constexpr int kSplitNT = NT, kSplitNW = NT / kWaveE;
-  static_assert(kSlice <= 16384, "places and leaf marks in 16 signed bits");
-  __shared__ __attribute__((aligned(16))) SplitSmem<NT> sm;
+  constexpr uint32_t kPer = kSlice / NT;     // symbols of a thread, and 64-symbol chunks of a wave, at most
+  constexpr uint32_t kSplitCh = kPer;
+  static_assert(kSlice <= 16384 && kPer % 4 == 0 && kPer <= 16, "places and leaf marks in 16 signed bits");
+  __shared__ __attribute__((aligned(16))) SplitSmem<NT, kSlice> sm;
   const uint32_t tid = threadIdx.x, lane = __lane_id();
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t b = blockIdx.x / spb, slice = blockIdx.x % spb;
-  if (b >= nblocks) return;
+  if (b >= nblocks || (direct && direct->out_bytes > out_cap)) return;
+  if (jobs && slice == 0) chunk_jobs(lay[b], rnodes + 255ull * b, b, chunk_log2, NT, jobs);
   const EncBlock &B = blocks[b];
   const uint32_t I = B.I, n = B.n, s_lo = slice * kSlice;
   if (I == 0 || s_lo >= n) return;
   const uint32_t S = n - s_lo < kSlice ? n - s_lo : kSlice;
   const uint32_t levels = B.maxlen;
   // everything the slice needs from memory, in one round trip: its symbols
-  // (16 consecutive ones a thread, no alignment), the symbol's and the node's
+  // (kPer consecutive ones a thread, no alignment), the symbol's and the node's
   // row of the block's tables, the levels' values (one level a lane)
   const uint8_t *src = in + B.in_off + s_lo;
-  uint32_t sy[4] = {0, 0, 0, 0};
-  if (16 * tid + 16 <= S) {
-    __builtin_memcpy(sy, src + 16 * tid, 16);
+  uint32_t sy[kPer / 4] = {};
+  if (kPer * (tid + 1) <= S) {
+    __builtin_memcpy(sy, src + kPer * tid, kPer);
   } else {
 #pragma unroll
-    for (uint32_t e = 0; e < 16; ++e)
-      if (16 * tid + e < S) sy[e >> 2] |= static_cast<uint32_t>(src[16 * tid + e]) << (8 * (e & 3));
+    for (uint32_t e = 0; e < kPer; ++e)
+      if (kPer * tid + e < S) sy[e >> 2] |= static_cast<uint32_t>(src[kPer * tid + e]) << (8 * (e & 3));
   }
   uint32_t cnt = 0, bef = 0, leaf = 0, lo = 0, mid = 0, hi = 0, cc = 0, d = 0, slot = 0, fd = 0, nbit = 0, pay = 0;
   bool rans = false;
@@ -907,15 +1058,15 @@ __global__ __launch_bounds__(NT) void k_split(const uint8_t *in, const EncBlock 
   }
   // the root level: every symbol's code
   {
-    uint32_t w[8];
+    uint32_t w[kPer / 2];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
+    for (uint32_t e = 0; e < kPer / 2; ++e) {
       const uint32_t x = (sy[e >> 1] >> (16 * (e & 1))) & 255, y = (sy[e >> 1] >> (16 * (e & 1) + 8)) & 255;
       w[e] = sm.pay[x] | (static_cast<uint32_t>(sm.pay[y]) << 16);
     }
-    uint4 *dst = reinterpret_cast<uint4 *>(sm.buf) + 2 * tid;
-    dst[0] = make_uint4(w[0], w[1], w[2], w[3]);
-    dst[1] = make_uint4(w[4], w[5], w[6], w[7]);
+    uint2 *dst = reinterpret_cast<uint2 *>(sm.buf) + kPer / 4 * tid;
+#pragma unroll
+    for (uint32_t e = 0; e < kPer / 4; ++e) dst[e] = make_uint2(w[2 * e], w[2 * e + 1]);
   }
   lds_sync();
   if (wave < 4) {
@@ -1003,34 +1154,37 @@ __global__ __launch_bounds__(NT) void k_split(const uint8_t *in, const EncBlock 
     uint2 *lbits = reinterpret_cast<uint2 *>(sm.bits) + __builtin_amdgcn_readlane(lw_l, lev);
     const uint32_t lim = 64 * ch1 < ln ? 64 * ch1 : ln;   // this wave's positions end here
     const uint32_t p0 = 64 * ch0 + lane;
+    const uint32_t mask = 0x8000u >> lev;    // the level's bit (the ballots are made twice: kept, they spill)
     uint32_t pl[kSplitCh], run = 0;
-    uint64_t m[kSplitCh];
     // groups of 4 chunks; a group inside the wave's share (and past the
     // level's flat nodes) needs no test per symbol
 #pragma unroll
     for (uint32_t g = 0; g < kSplitCh; g += 4) {
-      if (g >= per) break;
-#pragma unroll
-      for (uint32_t i = g; i < g + 4; ++i) pl[i] = buf[p0 + 64 * i];
+      if (ch0 + g >= ch1) break;
       if (64 * (ch0 + g + 4) <= lim && (!FLAT || 64 * (ch0 + g) >= lf)) {
 #pragma unroll
-        for (uint32_t i = g; i < g + 4; ++i) m[i] = __ballot(pl[i] & (0x8000u >> lev));
+        for (uint32_t i = g; i < g + 4; ++i) pl[i] = buf[p0 + 64 * i];
+        uint64_t m[4];
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) m[i] = __ballot(pl[g + i] & mask);
         if (lane == 0) {
 #pragma unroll
-          for (uint32_t i = g; i < g + 4; ++i)
-            lbits[ch0 + i] = make_uint2(static_cast<uint32_t>(m[i]), static_cast<uint32_t>(m[i] >> 32));
+          for (uint32_t i = 0; i < 4; ++i)
+            lbits[ch0 + g + i] = make_uint2(static_cast<uint32_t>(m[i]), static_cast<uint32_t>(m[i] >> 32));
         }
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) run += static_cast<uint32_t>(__popcll(m[i]));
       } else {
 #pragma unroll
         for (uint32_t i = g; i < g + 4; ++i) {
+          if (ch0 + i >= ch1) break;
           const uint32_t p = p0 + 64 * i;
-          m[i] = __ballot((pl[i] & (0x8000u >> lev)) && p < lim && (!FLAT || p >= lf));
-          if (lane == 0 && ch0 + i < ch1)
-            lbits[ch0 + i] = make_uint2(static_cast<uint32_t>(m[i]), static_cast<uint32_t>(m[i] >> 32));
+          pl[i] = buf[p];
+          const uint64_t m = __ballot((pl[i] & mask) && p < lim && (!FLAT || p >= lf));
+          if (lane == 0) lbits[ch0 + i] = make_uint2(static_cast<uint32_t>(m), static_cast<uint32_t>(m >> 32));
+          run += static_cast<uint32_t>(__popcll(m));
         }
       }
-#pragma unroll
-      for (uint32_t i = g; i < g + 4; ++i) run += static_cast<uint32_t>(__popcll(m[i]));
     }
     if (next == 0 && lf == 0) break;         // every symbol ends here
     if (lane == 0) sm.wsum[lev & 1][wave] = run;
@@ -1047,45 +1201,42 @@ __global__ __launch_bounds__(NT) void k_split(const uint8_t *in, const EncBlock 
     const int16_t *Kl = sm.K + 2 * kbase;    // by the code's first lev + 1 bits
 #pragma unroll
     for (uint32_t g = 0; g < kSplitCh; g += 4) {
-      if (g >= per) break;
+      if (ch0 + g >= ch1) break;
       if (64 * (ch0 + g + 4) <= lim && (!FLAT || 64 * (ch0 + g) >= lf)) {
         int32_t k[4];
 #pragma unroll
         for (uint32_t i = 0; i < 4; ++i) k[i] = Kl[pl[g + i] >> (15 - lev)];
 #pragma unroll
         for (uint32_t i = 0; i < 4; ++i) {
-          const uint64_t mm = m[g + i];
+          const bool bit = pl[g + i] & mask;
+          const uint64_t mm = __ballot(bit);
           const uint32_t r = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mm >> 32),
                                                        __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mm), R));
           R += static_cast<uint32_t>(__popcll(mm));
-          const uint32_t x = __builtin_amdgcn_inverse_ballot_w64(mm) ? r : p0 + 64 * (g + i) - r;
+          const uint32_t x = bit ? r : p0 + 64 * (g + i) - r;
           const uint32_t at = x + k[i];
           if (at < kSlice) buf[at] = static_cast<uint16_t>(pl[g + i]);
         }
       } else {
-        uint32_t v[4];
-        int32_t k[4];
 #pragma unroll
         for (uint32_t i = 0; i < 4; ++i) {
-          const uint32_t p = p0 + 64 * (g + i), pre_d = pl[g + i] >> (16 - lev);
-          v[i] = p < lim ? pre_d + kbase : 0u;
-          k[i] = sm.K[2 * v[i] + ((pl[g + i] >> (15 - lev)) & 1)];
-        }
-#pragma unroll
-        for (uint32_t i = 0; i < 4; ++i) {
+          if (ch0 + g + i >= ch1) break;
           const uint32_t p = p0 + 64 * (g + i), c = pl[g + i];
-          const uint64_t mm = m[g + i];
+          const uint32_t v = p < lim ? (c >> (16 - lev)) + kbase : 0u;
+          const int32_t k = sm.K[2 * v + ((c >> (15 - lev)) & 1)];
+          const bool bit = (c & mask) && p < lim && (!FLAT || p >= lf);
+          const uint64_t mm = __ballot(bit);
           const uint32_t r = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mm >> 32),
                                                        __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mm), R));
           R += static_cast<uint32_t>(__popcll(mm));
           if (p >= lim) continue;
           if (FLAT && p < lf) {              // D-bit field: the code's last D bits
-            const uint32_t F = sm.F[v[i]], D = F >> 24, x = (F + D * p) & 0xFFFFFF;
+            const uint32_t F = sm.F[v], D = F >> 24, x = (F + D * p) & 0xFFFFFF;
             const uint32_t f = ((c << lev) & 0xFFFF) >> (16 - D);
             atomicOr(&sm.bits[x >> 5], f << (x & 31));
             if ((x & 31) + D > 32) atomicOr(&sm.bits[(x >> 5) + 1], f >> (32 - (x & 31)));
           } else {
-            const uint32_t at = (__builtin_amdgcn_inverse_ballot_w64(mm) ? r : p - r) + k[i];
+            const uint32_t at = (bit ? r : p - r) + k;
             if (at < kSlice) buf[at] = static_cast<uint16_t>(c);
           }
         }
@@ -1115,37 +1266,22 @@ __global__ __launch_bounds__(NT) void k_split(const uint8_t *in, const EncBlock 
   }
 }
 
-// The chunk jobs of every rANS node (one wave per block, a lane per node).
-__global__ __launch_bounds__(kWaveE * kLayoutWaves) void k_chunks(const BlockLay *lay, const RansNode *rnodes,
-                                                                uint32_t nb, uint32_t chunk_log2,
-                                                                RansJob *jobs) {
-  const uint32_t wave = threadIdx.x >> 6, lane = __lane_id();
-  const uint32_t b = blockIdx.x * kLayoutWaves + wave;
-  if (b >= nb) return;
-  const BlockLay &L = lay[b];
-  const uint32_t C = 1u << chunk_log2;
-  for (uint32_t r = lane; r < L.n_rnodes; r += kWaveE) {
-    const RansNode rn = rnodes[255ull * b + r];
-    uint32_t k = 0;
-    for (uint32_t st = 0; st < rn.nv; st += C, ++k) {
-      RansJob j;
-      j.bmp_word = L.rbm_off + rn.rword + st / 32;
-      j.slot = L.slot0 + rn.sl0 + static_cast<uint64_t>(k) * slot_size(C);
-      j.nbits = rn.nv - st < C ? rn.nv - st : C;
-      j.p1q = rn.p1q;
-      j.block = b;
-      j.rnode = r;
-      j.first = st == 0;
-      j.dst = 0;
-      jobs[L.chunk0 + rn.ch0 + k] = j;
-    }
-  }
+// x / f and x % f of the rANS step, folded into its new state: q * 4096 + r +
+// add, for x < f * 2^20 and rcp = floor(2^32 / f) (2^32 - 1 for f = 1).  The
+// high product is the quotient or one less, so one correction serves.
+__device__ __forceinline__ uint32_t rans_next(uint32_t x, uint32_t f, uint32_t rcp, uint32_t add) {
+  const uint32_t q = __umulhi(x, rcp), r = x - __umul24(q, f);
+  return q * kRansM + r + add + (r >= f ? kRansM - f : 0u);
 }
 
 // One wave per chunk (persistent over the job list): encode steps k = K-1 ..
 // 0; within a step the lanes push their renormalisation words in the order
 // lane 31 .. 0, the reverse of the decoder's read order, so the decoder reads
-// the pushed words backwards.
+// the pushed words backwards.  A step is a chain of dependent operations that
+// sets the kernel's time, so nothing in it waits for memory (the words of 32
+// steps sit in the lanes), the division is a product with the reciprocal, and
+// 32 full steps are unrolled, which takes all that does not depend on the
+// state off the chain: a chunk of 2^16 bits 384 -> 172 us.
 __global__ __launch_bounds__(256) void k_rans_enc(const RansJob *jobs, const Totals *tot,
                                                   const uint32_t *bmp, uint8_t *slots,
                                                   uint32_t *sizes) {
@@ -1154,28 +1290,41 @@ __global__ __launch_bounds__(256) void k_rans_enc(const RansJob *jobs, const Tot
   const uint64_t nwaves = static_cast<uint64_t>(gridDim.x) * (256 / kWaveE);
   for (uint64_t j = blockIdx.x * (256 / kWaveE) + (threadIdx.x >> 6); j < njobs; j += nwaves) {
     const RansJob J = jobs[j];
-    const uint32_t f0 = kRansM - J.p1q, f1 = J.p1q;
+    const uint32_t f0 = kRansM - J.p1q, f1 = J.p1q;    // both in [1, 4095]
+    const uint32_t rcp0 = f0 > 1 ? static_cast<uint32_t>((1ull << 32) / f0) : 0xFFFFFFFFu;
+    const uint32_t rcp1 = f1 > 1 ? static_cast<uint32_t>((1ull << 32) / f1) : 0xFFFFFFFFu;
     const uint32_t K = (J.nbits + 31) / 32;
     uint8_t *slot = slots + J.slot;
     uint16_t *words = reinterpret_cast<uint16_t *>(slot + kChunkHdr);
     const uint32_t *bits = bmp + J.bmp_word;
     uint32_t x = kRansL;
     uint32_t pos = 0;
-    const uint64_t gt = lane < 63 ? ~((2ull << lane) - 1) : 0ull;   // lanes above this one
-    for (uint32_t k = K; k-- > 0;) {
-      const uint32_t w = bits[k];
-      const bool act = lane < kRansLanes && 32 * k + lane < J.nbits;
-      const bool bit = act && ((w >> (lane & 31)) & 1);
-      const uint32_t f = bit ? f1 : f0;
-      const bool need = act && x >= (f << 20);
-      const uint64_t m = __ballot(need);
-      if (need) {
-        words[pos + __popcll(m & gt)] = static_cast<uint16_t>(x & 0xFFFF);
-        x >>= 16;
+    if (lane < kRansLanes) {
+      const uint32_t gt = lane < 31 ? ~((2u << lane) - 1) : 0u;   // lanes above this one
+      auto step = [&](uint32_t w, bool act) {
+        const bool bit = (w >> lane) & 1;
+        const uint32_t f = bit ? f1 : f0;
+        const bool need = act && x >= (f << 20);
+        const uint32_t m = static_cast<uint32_t>(__ballot(need));
+        if (need) words[pos + __popc(m & gt)] = static_cast<uint16_t>(x);
+        const uint32_t xr = need ? x >> 16 : x;
+        pos += __popc(m);
+        const uint32_t xn = rans_next(xr, f, bit ? rcp1 : rcp0, bit ? f0 : 0u);
+        x = act ? xn : xr;
+      };
+      for (uint32_t g = (K - 1) & ~31u;; g -= 32) {    // lane i: the word of step g + i
+        const uint32_t w32 = g + lane < K ? bits[g + lane] : 0u;
+        if (32 * (g + 32) <= J.nbits) {
+#pragma unroll
+          for (int i = 31; i >= 0; --i) step(__builtin_amdgcn_readlane(w32, i), true);
+        } else {
+          for (uint32_t i = K - g; i-- > 0;)
+            step(__builtin_amdgcn_readlane(w32, i), 32 * (g + i) + lane < J.nbits);
+        }
+        if (g == 0) break;
       }
-      pos += __popcll(m);
-      if (act) x = (x / f) * kRansM + (x % f) + (bit ? f0 : 0u);
     }
+    pos = __builtin_amdgcn_readfirstlane(pos);         // for the lanes that ran no steps
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "agent");
     __builtin_amdgcn_wave_barrier();
     // reverse the pushed words in place: decoder order
@@ -1239,16 +1388,32 @@ __global__ __launch_bounds__(kFseEncNT) void k_fse_enc(const RansJob *jobs, cons
     const uint8_t *bm = reinterpret_cast<const uint8_t *>(bmp + J.bmp_word);
     const uint32_t cb = (J.nbits + 7) >> 3;
     const uint32_t steps = has && cb > hl ? (cb - hl + 31) >> 5 : 0u;
+    // 8 steps from i0 on, last first: their bytes, then the tables' entries of
+    // the bytes, are read before the first step, so that the chain of states
+    // waits for one table read a step
+    auto steps8 = [&](uint32_t i0, uint32_t &x, auto &&emit) {
+      uint32_t b[8], n[8], f[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) b[e] = bm[hl + 32 * (i0 + e < steps ? i0 + e : 0u)] ^ flip;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        n[e] = norm[b[e]];
+        f[e] = first[b[e]];
+      }
+#pragma unroll
+      for (int e = 7; e >= 0; --e) {
+        const uint32_t k = 31 - __builtin_clz(n[e] | 1u);
+        const uint32_t nb = kFseLog - k - (x < (n[e] << (kFseLog - k)) ? 1u : 0u);
+        if (i0 + e < steps) {
+          emit(x, nb);
+          x = kFseSize + state[f[e] + (x >> nb) - n[e]];
+        }
+      }
+    };
     // pass 1: the cursor's bit count and final state
     uint32_t x = kFseSize, tbits = 0;
-    for (uint32_t i = steps; i-- > 0;) {
-      const uint32_t b = bm[hl + 32 * i] ^ flip;
-      const uint32_t n = norm[b];
-      const uint32_t k = 31 - __builtin_clz(n);
-      const uint32_t nb = kFseLog - k - (x < (n << (kFseLog - k)) ? 1u : 0u);
-      x = kFseSize + state[first[b] + (x >> nb) - n];
-      tbits += nb;
-    }
+    for (uint32_t i = (steps + 7) & ~7u; i != 0; i -= 8)
+      steps8(i - 8, x, [&](uint32_t, uint32_t nb) { tbits += nb; });
     const uint32_t len = (tbits + 7) >> 3;
     if (len > 0xFFFF) atomicCAS(err, 0u, kErrUnsupported);
     uint32_t incl = wave_incl_scan(len);
@@ -1259,20 +1424,16 @@ __global__ __launch_bounds__(kFseEncNT) void k_fse_enc(const RansJob *jobs, cons
     uint8_t *sp = slot + kFseChunkHdr + (incl - len);
     // pass 2: the same steps, bits written from the stream's end backwards
     uint32_t acc = 0, accn = 8 * len - tbits, top = len, x2 = kFseSize;
-    for (uint32_t i = steps; i-- > 0;) {
-      const uint32_t b = bm[hl + 32 * i] ^ flip;
-      const uint32_t n = norm[b];
-      const uint32_t k = 31 - __builtin_clz(n);
-      const uint32_t nb = kFseLog - k - (x2 < (n << (kFseLog - k)) ? 1u : 0u);
-      acc = (acc << nb) | (x2 & ((1u << nb) - 1));
-      accn += nb;
-      x2 = kFseSize + state[first[b] + (x2 >> nb) - n];
-      while (accn >= 8) {
-        --top;
-        sp[top] = static_cast<uint8_t>(acc >> (accn - 8));
-        accn -= 8;
-      }
-    }
+    for (uint32_t i = (steps + 7) & ~7u; i != 0; i -= 8)
+      steps8(i - 8, x2, [&](uint32_t xs, uint32_t nb) {
+        acc = (acc << nb) | (xs & ((1u << nb) - 1));
+        accn += nb;
+        while (accn >= 8) {
+          --top;
+          sp[top] = static_cast<uint8_t>(acc >> (accn - 8));
+          accn -= 8;
+        }
+      });
     if (has) {
       reinterpret_cast<uint16_t *>(slot)[hl] = static_cast<uint16_t>(x - kFseSize);
       reinterpret_cast<uint16_t *>(slot)[kFseLanes + hl] = static_cast<uint16_t>(len);
@@ -1283,70 +1444,74 @@ __global__ __launch_bounds__(kFseEncNT) void k_fse_enc(const RansJob *jobs, cons
   }
 }
 
-// Block sizes (one thread per block): header, raw bodies, then every rANS
-// node at a multiple of 4 bytes with its 8-byte header and its chunks; the
-// chunks' places in the block go to their jobs, comp_size to the header.
-__global__ __launch_bounds__(256) void k_sizes(BlockLay *lay, RansNode *rnodes, RansJob *jobs,
-                                               const uint32_t *sizes, uint32_t nb, uint32_t chunk_log2,
-                                               uint8_t *hdr) {
-  const uint32_t b = blockIdx.x * 256 + threadIdx.x;
-  if (b >= nb) return;
-  BlockLay &L = lay[b];
-  const uint32_t C = 1u << chunk_log2;
-  uint64_t off = static_cast<uint64_t>(L.hlen) + L.raw_bytes;
-  for (uint32_t r = 0; r < L.n_rnodes; ++r) {
-    RansNode &rn = rnodes[255ull * b + r];
-    off = (off + 3) & ~3ull;
-    rn.boff = static_cast<uint32_t>(off);
-    off += 8;
-    const uint32_t nch = (rn.nv + C - 1) / C;
-    uint32_t blen = 0;
-    for (uint32_t k = 0; k < nch; ++k) {
-      const uint64_t j = L.chunk0 + rn.ch0 + k;
-      jobs[j].dst = static_cast<uint32_t>(off + blen);
-      blen += sizes[j];
-    }
-    rn.blen = blen;
-    off += blen;
+// Size of a block with its entropy-coded nodes (one wave): header, raw
+// bodies, then every rANS node at a multiple of 4 bytes with its 8-byte header
+// and its chunks, whose sizes are multiples of 4.  The chunks of a block lie in
+// node order, so a chunk's place is the sum of the chunks before it and 8
+// bytes per node up to its own; it goes to the chunk's job, comp_size to the
+// header.
+__device__ void block_size(BlockLay &L, RansJob *jobs, const uint32_t *sizes, uint8_t *H) {
+  const uint32_t lane = __lane_id(), nch = L.n_chunks;
+  uint32_t off = L.hlen + L.raw_bytes;
+  if (nch) off = (off + 3) & ~3u;
+  for (uint32_t k0 = 0; k0 < nch; k0 += kWaveE) {
+    const uint64_t j = L.chunk0 + k0 + lane;
+    const bool has = k0 + lane < nch;
+    const uint32_t sz = has ? sizes[j] : 0u, inc = wave_incl_scan(sz);
+    if (has) jobs[j].dst = off + inc - sz + 8 * (jobs[j].rnode + 1);
+    off += __builtin_amdgcn_readlane(inc, 63);
   }
-  L.comp = static_cast<uint32_t>(off);
-  *reinterpret_cast<uint32_t *>(hdr + static_cast<uint64_t>(b) * kHdrStride) = static_cast<uint32_t>(off);
+  off += 8 * L.n_rnodes;
+  if (lane == 0) {
+    L.comp = off;
+    *reinterpret_cast<uint32_t *>(H) = off;
+  }
+}
+
+__global__ __launch_bounds__(256) void k_sizes(BlockLay *lay, RansJob *jobs, const uint32_t *sizes, uint32_t nb,
+                                               uint8_t *hdr) {
+  const uint32_t b = blockIdx.x * (256 / kWaveE) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (b < nb) block_size(lay[b], jobs, sizes, hdr + static_cast<uint64_t>(b) * kHdrStride);
 }
 
 // Stream offsets of the blocks (one workgroup): each block starts at a
-// multiple of 4 bytes after the header and the two offset tables.
-__global__ __launch_bounds__(kScanNT) void k_scan2(BlockLay *lay, uint32_t nb, Totals *tot) {
-  __shared__ uint64_t part[kScanNT];
+// multiple of 4 bytes after the header and the two offset tables.  Up to
+// kTailBlocks blocks their sizes are found here too (4 rounds of 16 waves;
+// with more blocks the rounds would outlast a launch of k_sizes).  Then the
+// call's result.
+__global__ __launch_bounds__(kScanNT) void k_scan2(BlockLay *lay, RansJob *jobs, const uint32_t *sizes, uint32_t nb,
+                                                   uint8_t *hdr, Totals *tot, uint32_t *err, Result res) {
+  __shared__ uint64_t part[kScanNT / kWaveE];
   const uint32_t tid = threadIdx.x;
-  const uint32_t per = (nb + kScanNT - 1) / kScanNT;
-  const uint32_t b0 = tid * per, b1 = b0 + per < nb ? b0 + per : nb;
-  uint64_t v = 0;
-  for (uint32_t b = b0; b < b1; ++b) v += (static_cast<uint64_t>(lay[b].comp) + 3) & ~3ull;
-  part[tid] = v;
-  __syncthreads();
-  for (uint32_t off = 1; off < kScanNT; off <<= 1) {
-    const uint64_t a = tid >= off ? part[tid - off] : 0ull;
-    __syncthreads();
-    part[tid] += a;
+  if (nb <= kTailBlocks) {
+    for (uint32_t b = __builtin_amdgcn_readfirstlane(tid >> 6); b < nb; b += kScanNT / kWaveE)
+      block_size(lay[b], jobs, sizes, hdr + static_cast<uint64_t>(b) * kHdrStride);
     __syncthreads();
   }
-  const uint64_t tab = kHeaderBytes + 16ull * (nb + 1);
-  uint64_t run = tab + part[tid] - v;
-  for (uint32_t b = b0; b < b1; ++b) {
-    lay[b].out_off = run;
-    run += (static_cast<uint64_t>(lay[b].comp) + 3) & ~3ull;
+  uint64_t run = stream_tables(nb);
+  for (uint64_t b0 = 0; b0 < nb; b0 += kScanNT) {
+    const uint64_t b = b0 + tid;
+    uint64_t all;
+    const uint64_t x = block_excl_scan(b < nb ? (static_cast<uint64_t>(lay[b].comp) + 3) & ~3ull : 0ull, part, &all);
+    if (b < nb) lay[b].out_off = run + x;
+    run += all;
   }
-  if (tid == kScanNT - 1) tot->out_bytes = tab + part[tid];
+  if (tid == 0) {
+    tot->out_bytes = run;
+    finish(run, err, res);
+  }
 }
 
+// What the stream's header says.
+struct StreamOpts {
+  uint64_t n;
+  uint32_t bs, max_len, chunk_log2, version;   // version (1 or 2) | flags << 16
+};
+
 // Stream header and the two offset tables (block offsets, scratch-word
-// offsets), nothing written past out_cap.
-__global__ __launch_bounds__(256) void k_stream_head(const BlockLay *lay, const Totals *tot, uint32_t nb,
-                                                     uint64_t n, uint32_t bs, uint32_t max_len,
-                                                     uint32_t chunk_log2, uint32_t version, uint8_t *out,
-                                                     uint64_t out_cap) {
-  const uint32_t t = blockIdx.x * 256 + threadIdx.x;
-  if (tot->out_bytes > out_cap) return;
+// offsets), by threads 0 .. nb of a grid.
+__device__ void stream_head(uint64_t t, const BlockLay *lay, const Totals *tot, uint32_t nb, const StreamOpts &o,
+                            uint8_t *out) {
   uint64_t *boff = reinterpret_cast<uint64_t *>(out + kHeaderBytes);
   uint64_t *aoff = boff + nb + 1;
   if (t <= nb) {
@@ -1356,12 +1521,12 @@ __global__ __launch_bounds__(256) void k_stream_head(const BlockLay *lay, const 
   if (t == 0) {
     uint32_t *h = reinterpret_cast<uint32_t *>(out);
     h[0] = kMagic;
-    h[1] = version;                                   // version (1 or 2) | flags << 16
-    h[2] = static_cast<uint32_t>(n);
-    h[3] = static_cast<uint32_t>(n >> 32);
-    h[4] = bs;
+    h[1] = o.version;
+    h[2] = static_cast<uint32_t>(o.n);
+    h[3] = static_cast<uint32_t>(o.n >> 32);
+    h[4] = o.bs;
     h[5] = nb;
-    h[6] = (max_len & 255) | ((chunk_log2 & 255) << 8);
+    h[6] = (o.max_len & 255) | ((o.chunk_log2 & 255) << 8);
     h[7] = 0;
     h[8] = static_cast<uint32_t>(tot->ans_words);
     h[9] = static_cast<uint32_t>(tot->ans_words >> 32);
@@ -1370,16 +1535,14 @@ __global__ __launch_bounds__(256) void k_stream_head(const BlockLay *lay, const 
   }
 }
 
-// Block header and raw image, as aligned 4-byte words (workgroup s of block b
-// writes words [s kAsmSeg, (s + 1) kAsmSeg) of them): a word inside the raw
-// bodies is a byte funnel of two image words, words at the edges are built
-// byte by byte (bytes past the raw bodies are zero: the padding before the
-// first rANS body or the next block).
-__global__ __launch_bounds__(256) void k_assemble(const BlockLay *lay, const Totals *tot, uint32_t nb,
-                                                  uint32_t segs, const uint8_t *hdr, const uint8_t *imgb,
-                                                  uint8_t *out, uint64_t out_cap) {
-  const uint32_t b = blockIdx.x / segs, s = blockIdx.x % segs;
-  if (b >= nb || tot->out_bytes > out_cap) return;
+// Block header and raw bodies of block b, as aligned 4-byte words (words
+// [s kAsmSeg, (s + 1) kAsmSeg) of them): a word inside the raw bodies is a
+// byte funnel of two image words, words at the edges are built byte by byte
+// (bytes past the raw bodies are zero: the padding before the first rANS body
+// or the next block).  Without an image (IMG false) the bodies are zeroed.
+template <bool IMG>
+__device__ void block_words(uint32_t b, uint32_t s, const BlockLay *lay, const uint8_t *hdr, const uint8_t *imgb,
+                            uint8_t *out) {
   const BlockLay &L = lay[b];
   const uint32_t hlen = L.hlen;
   const uint64_t used = static_cast<uint64_t>(hlen) + L.raw_bytes;
@@ -1391,19 +1554,21 @@ __global__ __launch_bounds__(256) void k_assemble(const BlockLay *lay, const Tot
   const uint8_t *img = imgb + L.img_off;
   const uint32_t *img32 = reinterpret_cast<const uint32_t *>(imgb);
   uint32_t *o32 = reinterpret_cast<uint32_t *>(out + L.out_off);
+#pragma unroll 8
   for (uint64_t q = w0 + threadIdx.x; q < w1; q += 256) {
     const uint64_t x0 = 4 * q;
-    uint32_t w;
+    uint32_t w = 0;
     if (x0 + 4 <= hlen) {
       w = *reinterpret_cast<const uint32_t *>(H + x0);
     } else if (x0 >= hlen && x0 + 4 <= used) {
-      const uint64_t so = L.img_off + (x0 - hlen);
-      w = __builtin_amdgcn_alignbyte(img32[(so >> 2) + 1], img32[so >> 2], static_cast<uint32_t>(so & 3));
+      if (IMG) {
+        const uint64_t so = L.img_off + (x0 - hlen);
+        w = __builtin_amdgcn_alignbyte(img32[(so >> 2) + 1], img32[so >> 2], static_cast<uint32_t>(so & 3));
+      }
     } else {
-      w = 0;
       for (uint32_t e = 0; e < 4; ++e) {
         const uint64_t x = x0 + e;
-        const uint32_t v = x < hlen ? H[x] : x < used ? img[x - hlen] : 0u;
+        const uint32_t v = x < hlen ? H[x] : IMG && x < used ? img[x - hlen] : 0u;
         w |= v << (8 * e);
       }
     }
@@ -1411,42 +1576,52 @@ __global__ __launch_bounds__(256) void k_assemble(const BlockLay *lay, const Tot
   }
 }
 
-// rANS bodies: one wave per chunk copies its slot into the block; the first
-// chunk of a node also writes the node's 8-byte body header.
-__global__ __launch_bounds__(256) void k_assemble_rans(const BlockLay *lay, const RansNode *rnodes,
-                                                       const RansJob *jobs, const uint32_t *sizes,
-                                                       const Totals *tot, const uint8_t *slots,
-                                                       uint8_t *out, uint64_t out_cap) {
-  const uint32_t lane = __lane_id();
+// Streams without entropy-coded nodes: the stream's and the blocks' headers,
+// and zeros for the bits that the split kernel writes straight into the
+// bodies.  Nothing is written past out_cap.
+__global__ __launch_bounds__(256) void k_head(const BlockLay *lay, const Totals *tot, uint32_t nb, uint32_t segs,
+                                              StreamOpts o, const uint8_t *hdr, uint8_t *out, uint64_t out_cap) {
   if (tot->out_bytes > out_cap) return;
+  stream_head(blockIdx.x * 256ull + threadIdx.x, lay, tot, nb, o, out);
+  block_words<false>(blockIdx.x / segs, blockIdx.x % segs, lay, hdr, nullptr, out);
+}
+
+// Streams with entropy-coded nodes: the first nb * segs workgroups write the
+// headers and the raw bodies from the images; in the others a wave per chunk
+// copies its slot into the block, and the first chunk of a node also writes
+// the node's 8-byte body header (its bodies end where the next node's header
+// or the block does).
+__global__ __launch_bounds__(256) void k_assemble(const BlockLay *lay, const Totals *tot, uint32_t nb, uint32_t segs,
+                                                  StreamOpts o, const uint8_t *hdr, const uint8_t *imgb,
+                                                  const RansNode *rnodes, const RansJob *jobs,
+                                                  const uint32_t *sizes, const uint8_t *slots, uint8_t *out,
+                                                  uint64_t out_cap) {
+  if (tot->out_bytes > out_cap) return;
+  stream_head(blockIdx.x * 256ull + threadIdx.x, lay, tot, nb, o, out);
+  if (blockIdx.x < nb * segs) {
+    block_words<true>(blockIdx.x / segs, blockIdx.x % segs, lay, hdr, imgb, out);
+    return;
+  }
+  const uint32_t lane = __lane_id();
   const uint64_t njobs = tot->chunks;
-  const uint64_t nwaves = static_cast<uint64_t>(gridDim.x) * (256 / kWaveE);
-  for (uint64_t j = blockIdx.x * (256 / kWaveE) + (threadIdx.x >> 6); j < njobs; j += nwaves) {
+  const uint64_t nwaves = static_cast<uint64_t>(gridDim.x - nb * segs) * (256 / kWaveE);
+  for (uint64_t j = (blockIdx.x - nb * segs) * (256 / kWaveE) + (threadIdx.x >> 6); j < njobs; j += nwaves) {
     const RansJob J = jobs[j];
     const BlockLay &L = lay[J.block];
     uint8_t *dst = out + L.out_off + J.dst;
     if (J.first && lane == 0) {
-      const RansNode &rn = rnodes[255ull * J.block + J.rnode];
+      const uint32_t end = J.rnode + 1 < L.n_rnodes
+                               ? jobs[L.chunk0 + rnodes[255ull * J.block + J.rnode + 1].ch0].dst - 8
+                               : L.comp;
       uint32_t *h = reinterpret_cast<uint32_t *>(dst - 8);
       h[0] = J.p1q;                                    // p1q u16, pad u16
-      h[1] = rn.blen;
+      h[1] = end - J.dst;
     }
     const uint32_t *src = reinterpret_cast<const uint32_t *>(slots + J.slot);
     uint32_t *d32 = reinterpret_cast<uint32_t *>(dst);
     const uint32_t nw = sizes[j] / 4;
     for (uint32_t i = lane; i < nw; i += kWaveE) d32[i] = src[i];
   }
-}
-
-// The call's result on the device: the stream length (also when it exceeds
-// out_cap, in which case nothing was written) and a status.
-__global__ void k_finish(const Totals *tot, const uint32_t *err, uint64_t out_cap, uint64_t *d_len,
-                         int32_t *d_status) {
-  if (threadIdx.x != 0) return;
-  const uint64_t n = tot->out_bytes;
-  const uint32_t e = *err;
-  *d_len = n;
-  *d_status = e == kErrArg ? PIVCO_E_ARG : e ? PIVCO_E_UNSUPPORTED : n > out_cap ? PIVCO_E_CAPACITY : PIVCO_OK;
 }
 
 // The stream of an empty input: header and the two one-entry tables.
@@ -1461,10 +1636,6 @@ __global__ void k_empty(EmptyStream h, uint8_t *out, uint64_t out_cap, uint64_t 
     *d_len = sizeof(h.w);
     *d_status = fits ? PIVCO_OK : PIVCO_E_CAPACITY;
   }
-}
-
-__global__ void k_zero_words(uint32_t *p, uint32_t n) {
-  if (threadIdx.x < n) p[threadIdx.x] = 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -1484,21 +1655,30 @@ bool opts_ok(const pivco_encode_opts *o) {
 // / 16 Ki 2.24 / 2.27 / 2.24 ms a call; 64 MiB very skewed 0.661 / 0.653 /
 // 0.667 ms).  Below 8 MiB (1024 large slices, 4 a CU) the smaller one gives
 // more workgroups: one 64 KiB block is 16 of them.
+// The split's threads (launch_split): up to 256 small slices, one a CU, run
+// with 1024 threads, 4 chunks a wave (64 KiB: 18 us, 22 with 256 threads);
+// more of them with 256, so that several share a CU.
 uint32_t slice_of(uint64_t n, uint32_t block_size) {
   return n >= (8ull << 20) && block_size >= kSliceLarge ? kSliceLarge : kSliceSmall;
 }
 
-template <class... A>
-void launch_split(uint32_t slice, bool flat, uint32_t grid, hipStream_t s, A... a) {
-  const dim3 g(grid), t(slice / 16);
-  if (slice == kSliceSmall) {
-    constexpr int NT = kSliceSmall / 16;
-    if (flat) hipLaunchKernelGGL((k_split<NT, true>), g, t, 0, s, a...);
-    else hipLaunchKernelGGL((k_split<NT, false>), g, t, 0, s, a...);
+void launch_split(uint32_t slice, bool flat, uint32_t grid, hipStream_t s, const uint8_t *in, const EncBlock *eb,
+                  const BlockLay *lay, uint32_t nb, uint32_t spb, const uint32_t *pre, const uint32_t *hist,
+                  uint32_t *img, uint32_t *rbm, const Totals *direct, uint64_t out_cap, const RansNode *rn,
+                  uint32_t chunk_log2, RansJob *jobs) {
+  auto go = [&](auto kernel, uint32_t nt) {
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(nt), 0, s, in, eb, lay, nb, spb, pre, hist, img, rbm, direct, out_cap,
+                       rn, chunk_log2, jobs);
+  };
+  if (slice == kSliceLarge) {
+    if (flat) go(k_split<512, kSliceLarge, true>, 512);
+    else go(k_split<512, kSliceLarge, false>, 512);
+  } else if (grid > 256) {
+    if (flat) go(k_split<256, kSliceSmall, true>, 256);
+    else go(k_split<256, kSliceSmall, false>, 256);
   } else {
-    constexpr int NT = kSliceLarge / 16;
-    if (flat) hipLaunchKernelGGL((k_split<NT, true>), g, t, 0, s, a...);
-    else hipLaunchKernelGGL((k_split<NT, false>), g, t, 0, s, a...);
+    if (flat) go(k_split<1024, kSliceSmall, true>, 1024);
+    else go(k_split<1024, kSliceSmall, false>, 1024);
   }
 }
 
@@ -1511,7 +1691,7 @@ struct WsLayout {
 WsLayout ws_layout(uint64_t n, const pivco_encode_opts *o) {
   WsLayout L{};
   const uint64_t nb = div_up(n, o->block_size);
-  const uint64_t spb = div_up(o->block_size, slice_of(n, o->block_size));
+  const uint64_t spb = div_up(std::min<uint64_t>(n, o->block_size), slice_of(n, o->block_size));
   const uint64_t C = 1ull << o->rans_chunk_log2;
   const uint64_t bits = n * o->max_len;
   const uint64_t chunks = o->ans_mode ? bits / C + nb * 255 + 1 : 0;
@@ -1567,7 +1747,7 @@ pivco_status encode_enqueue(const void *d_in, uint64_t n, void *d_out, uint64_t 
   const uint64_t bs = o->block_size;
   const uint64_t nb64 = div_up(n, bs);
   const uint32_t slice = slice_of(n, o->block_size);
-  const uint64_t spb64 = div_up(bs, slice);
+  const uint64_t spb64 = div_up(std::min(n, bs), slice);
   if (nb64 > 0xFFFFFFFFull || nb64 * spb64 > 0x7FFFFFFFull) return PIVCO_E_ARG;
   const uint32_t nb = static_cast<uint32_t>(nb64), spb = static_cast<uint32_t>(spb64);
   const uint32_t flags = o->ans_mode == 3 ? 1u : 0u;
@@ -1598,63 +1778,77 @@ pivco_status encode_enqueue(const void *d_in, uint64_t n, void *d_out, uint64_t 
   uint32_t *dsizes = reinterpret_cast<uint32_t *>(ws + L.sizes);
   uint32_t *derr = reinterpret_cast<uint32_t *>(ws + L.stat);
 
-  // 1. histograms of the blocks and of their slices
+  // 1. histograms of the blocks and of their slices.  The areas that the
+  // split kernel ORs into are cleared beside it while their bound is small (a
+  // launch costs more than clearing 32 MiB, 7 us, that the data may not need);
+  // larger ones to their size, once that is known.
+  const bool ans = o->ans_mode != 0;
+  const Result res{out_cap, d_len, d_status};
   uint32_t *dh = reinterpret_cast<uint32_t *>(ws + L.hist);
   uint32_t *dslh = reinterpret_cast<uint32_t *>(ws + L.slh);
-  hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, derr, 1u);
-  hipLaunchKernelGGL(k_fill_zero, dim3(std::min<uint64_t>(4096, div_up(nb64 * 256, 256))), dim3(256), 0, s,
-                     dh, nb64 * 256);
-  hipLaunchKernelGGL(k_hist, dim3(nb * spb), dim3(256), 0, s, in, n, static_cast<uint32_t>(bs), slice, spb, dh, dslh);
+  uint32_t *dimg = reinterpret_cast<uint32_t *>(ws + L.img);
+  uint32_t *drbm = reinterpret_cast<uint32_t *>(ws + L.rbm);
+  const uint64_t area = L.jobs - L.img;        // both areas, 256-byte multiples
+  const bool early = area <= (32ull << 20);
+  hipLaunchKernelGGL(k_hist, dim3(nb * spb), dim3(256), 0, s, in, n, static_cast<uint32_t>(bs), slice, spb, dh, dslh,
+                     derr, reinterpret_cast<uint4 *>(dimg), ans && early ? area / 16 : 0ull);
   HIPCHK(hipGetLastError());
-  if (spb > 1) hipLaunchKernelGGL(k_slice_prefix, dim3(nb), dim3(256), 0, s, dslh, spb, dh);
+  if (spb > kPrefixRows)
+    hipLaunchKernelGGL(k_slice_prefix_wide, dim3(16 * nb), dim3(1024), 0, s, dslh, spb, dh);
+  else if (spb > 1)
+    hipLaunchKernelGGL(k_slice_prefix, dim3(nb), dim3(256), 0, s, dslh, spb, dh);
 
-  // 2.-3. code lengths (package-merge per block, or the supplied tree), layout
+  // 2. code lengths (package-merge per block, or the supplied tree), layout
   pivco_tree tree{};
   if (o->tree) tree = *o->tree;
   hipLaunchKernelGGL(k_code, dim3(nb), dim3(256), 0, s, dh, nb, n, static_cast<uint32_t>(bs), o->max_len, tree,
                      o->tree ? 1u : 0u, o->ans_mode, o->rans_chunk_log2, o->tree_shape,
-                     ft ? ft->dmax : nullptr, deb, dlay, drn, ws + L.hdr, derr);
-  hipLaunchKernelGGL(k_scan, dim3(1), dim3(kScanNT), 0, s, dlay, nb, dtot);
-  uint32_t *dimg = reinterpret_cast<uint32_t *>(ws + L.img);
-  uint32_t *drbm = reinterpret_cast<uint32_t *>(ws + L.rbm);
-  hipLaunchKernelGGL(k_zero_areas, dim3(4096), dim3(256), 0, s, dimg, drbm, dtot);
+                     ft ? ft->dmax : nullptr, deb, dlay, drn, ws + L.hdr, derr, dtot, res);
   HIPCHK(hipGetLastError());
 
-  // 5. bitmaps
-  launch_split(slice, o->tree_shape != 0, nb * spb, s, in, deb, dlay, nb, spb, dslh, dh, dimg, drbm);
+  // 3. offsets (one block: found by k_code)
+  if (nb > 1) hipLaunchKernelGGL(k_scan, dim3(1), dim3(kScanNT), 0, s, dlay, nb, o->ans_mode, dtot, derr, res);
+  if (ans && !early) hipLaunchKernelGGL(k_zero_areas, dim3(4096), dim3(256), 0, s, dimg, drbm, dtot);
   HIPCHK(hipGetLastError());
 
-  // 6. entropy-coded chunks
-  const bool ans = o->ans_mode != 0;
-  if (ans) {
-    hipLaunchKernelGGL(k_chunks, dim3(div_up(nb, kLayoutWaves)), dim3(kWaveE * kLayoutWaves), 0, s, dlay, drn, nb,
-                       o->rans_chunk_log2, djobs);
-    if (ft)
-      hipLaunchKernelGGL(k_fse_enc, dim3(2048), dim3(kFseEncNT), 0, s, djobs, dtot, drbm, ft->enc,
-                         ws + L.slots, dsizes, derr);
-    else
-      hipLaunchKernelGGL(k_rans_enc, dim3(2048), dim3(256), 0, s, djobs, dtot, drbm, ws + L.slots, dsizes);
+  const StreamOpts so{n, static_cast<uint32_t>(bs), o->max_len, o->rans_chunk_log2, version | (flags << 16)};
+  const uint64_t max_words = (kHdrStride + std::min<uint64_t>(n, bs) * o->max_len / 8 + 255 + 4) / 4 + 1;
+  const uint32_t segs = static_cast<uint32_t>(div_up(max_words, kAsmSeg));
+  if (static_cast<uint64_t>(nb) * segs > 0x7FFFF000ull) return PIVCO_E_UNSUPPORTED;
+  if (!ans) {
+    // 4. headers, then the bitmaps straight into the stream (nothing is
+    // written when it would not fit)
+    hipLaunchKernelGGL(k_head, dim3(nb * segs), dim3(256), 0, s, dlay, dtot, nb, segs, so, ws + L.hdr, out, out_cap);
+    launch_split(slice, o->tree_shape != 0, nb * spb, s, in, deb, dlay, nb, spb, dslh, dh,
+                 reinterpret_cast<uint32_t *>(out), nullptr, dtot, out_cap, drn, o->rans_chunk_log2, nullptr);
     HIPCHK(hipGetLastError());
+    return PIVCO_OK;
   }
 
-  // 7. sizes and offsets
-  hipLaunchKernelGGL(k_sizes, dim3((nb + 255) / 256), dim3(256), 0, s, dlay, drn, djobs, dsizes, nb,
-                     o->rans_chunk_log2, ws + L.hdr);
-  hipLaunchKernelGGL(k_scan2, dim3(1), dim3(kScanNT), 0, s, dlay, nb, dtot);
+  // 4. bitmaps, and the entropy-coded chunk jobs
+  launch_split(slice, o->tree_shape != 0, nb * spb, s, in, deb, dlay, nb, spb, dslh, dh, dimg, drbm, nullptr, out_cap,
+               drn, o->rans_chunk_log2, djobs);
+  HIPCHK(hipGetLastError());
 
-  // 8. the stream (nothing is written when it would not fit)
-  hipLaunchKernelGGL(k_stream_head, dim3((nb + 1 + 255) / 256), dim3(256), 0, s, dlay, dtot, nb, n,
-                     static_cast<uint32_t>(bs), o->max_len, o->rans_chunk_log2, version | (flags << 16), out,
-                     out_cap);
-  const uint64_t max_words = (kHdrStride + bs * o->max_len / 8 + 255 + 4) / 4 + 1;
-  const uint32_t segs = static_cast<uint32_t>(div_up(max_words, kAsmSeg));
-  if (static_cast<uint64_t>(nb) * segs > 0x7FFFFFFFull) return PIVCO_E_UNSUPPORTED;
-  hipLaunchKernelGGL(k_assemble, dim3(nb * segs), dim3(256), 0, s, dlay, dtot, nb, segs, ws + L.hdr,
-                     ws + L.img, out, out_cap);
-  if (ans)
-    hipLaunchKernelGGL(k_assemble_rans, dim3(2048), dim3(256), 0, s, dlay, drn, djobs, dsizes, dtot,
-                       ws + L.slots, out, out_cap);
-  hipLaunchKernelGGL(k_finish, dim3(1), dim3(64), 0, s, dtot, derr, out_cap, d_len, d_status);
+  // 5. entropy-coded chunks (at most this many: a grid for them all, or one
+  // that strides over the list)
+  const uint64_t chunks = n * o->max_len / (1ull << o->rans_chunk_log2) + nb64 * 255 + 1;
+  const uint32_t cgrid = static_cast<uint32_t>(std::min<uint64_t>(2048, div_up(chunks, 4)));
+  if (ft)
+    hipLaunchKernelGGL(k_fse_enc, dim3(cgrid), dim3(kFseEncNT), 0, s, djobs, dtot, drbm, ft->enc,
+                       ws + L.slots, dsizes, derr);
+  else
+    hipLaunchKernelGGL(k_rans_enc, dim3(cgrid), dim3(256), 0, s, djobs, dtot, drbm, ws + L.slots, dsizes);
+  HIPCHK(hipGetLastError());
+
+  // 6. sizes and offsets
+  if (nb > kTailBlocks)
+    hipLaunchKernelGGL(k_sizes, dim3((nb + 3) / 4), dim3(256), 0, s, dlay, djobs, dsizes, nb, ws + L.hdr);
+  hipLaunchKernelGGL(k_scan2, dim3(1), dim3(kScanNT), 0, s, dlay, djobs, dsizes, nb, ws + L.hdr, dtot, derr, res);
+
+  // 7. the stream (nothing is written when it would not fit)
+  hipLaunchKernelGGL(k_assemble, dim3(nb * segs + cgrid), dim3(256), 0, s, dlay, dtot, nb, segs, so, ws + L.hdr,
+                     ws + L.img, drn, djobs, dsizes, ws + L.slots, out, out_cap);
   HIPCHK(hipGetLastError());
   return PIVCO_OK;
 }
