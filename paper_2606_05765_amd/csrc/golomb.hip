@@ -17,9 +17,9 @@
 // Decode: k_gdecode, one workgroup per block, tiles of kGT values: a
 // top-down count gives each bitmap's share of the tile (the 0 bits of one
 // bitmap's share are the next one's), then the bottom-up merge: a lane makes
-// 16 values from 16 bits, their rank (a workgroup scan), 4-byte windows of
-// the next bitmap's values and one v_perm_b32 per 4 values (selector 0x0C
-// gives the constant 0).
+// 16 values from 16 bits, their rank, 4-byte windows of the next bitmap's
+// values and one v_perm_b32 per 4 values (selector 0x0C gives the constant
+// 0).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -34,7 +34,7 @@ namespace {
 constexpr uint32_t kGMagic = 0x31475650u;   // "PVG1"
 constexpr uint32_t kGHdr = 32;
 constexpr int kGW = 64;
-constexpr int kGNT = 1024;                  // decode workgroup
+constexpr int kGNT = 512;                   // decode workgroup
 constexpr uint32_t kGT = 16 * kGNT;         // values per decode tile
 
 // One Golomb job as the decode kernel sees it.
@@ -384,29 +384,102 @@ __global__ __launch_bounds__(kGEN, 5) void k_gsplit(const uint8_t *in, uint64_t 
 // ---------------------------------------------------------------------------
 // decode kernel
 // ---------------------------------------------------------------------------
+constexpr int kGNW = kGNT / kGW;
+constexpr int kGStat = 4;                   // top levels, all waves, bits in registers
+constexpr int kGDeep = 6;                   // levels below them that one wave takes in registers
+constexpr uint32_t kGWave = 16 * kGW;       // values one wave merges at once
+
 struct GSmem {
   uint32_t nk[257];          // values reaching bitmap k (n_0 = n, n_K = 0)
   uint32_t cur[257];         // of which decoded by earlier tiles
   uint32_t tv[257];          // of which in this tile
   uint64_t boff[256];        // bitmap k's first byte in the stream
-  uint32_t wsum[kGNT / kGW];
+  uint64_t part[kGNW];
+  uint32_t wsum[2][kGNW];
   uint32_t sel[16];
-  uint32_t K, n, err;
+  uint32_t err, depth;
   uint32_t lvl[2][kGT / 4 + 32] __attribute__((aligned(16)));
 };
 
-// 16 bits at bit x of a bitmap (bytes p[0 .. nbytes)), zero past its end.
-__device__ __forceinline__ uint32_t g_bits16(const uint8_t *p, uint64_t nbytes, uint64_t x) {
-  const uint64_t q = x >> 3;
-  uint32_t w = 0;
+// Sum over the workgroup of a wave's inclusive scan `inc` (its last lane's),
+// and of the waves before this one; one barrier, two slots used in turn.
+__device__ __forceinline__ uint32_t g_waves(GSmem &sm, uint32_t slot, uint32_t inc, uint32_t *before) {
+  const uint32_t wave = threadIdx.x >> 6;
+  if (__lane_id() == kGW - 1) sm.wsum[slot][wave] = inc;
+  __syncthreads();
+  uint32_t b = 0, t = 0;
 #pragma unroll
-  for (int e = 0; e < 3; ++e) w |= (q + e < nbytes ? static_cast<uint32_t>(p[q + e]) : 0u) << (8 * e);
-  return (w >> (x & 7)) & 0xFFFF;
+  for (uint32_t w = 0; w < kGNW; ++w) {
+    const uint32_t x = sm.wsum[slot][w];
+    b += w < wave ? x : 0u;
+    t += x;
+  }
+  *before = b;
+  return t;
 }
 
-__global__ __launch_bounds__(kGNT) void k_gdecode(const GJob *jobs, const uint2 *blocks, uint32_t nblocks) {
+// The first n (0 to 16) of 16 bits.
+__device__ __forceinline__ uint32_t g_first(uint32_t bits, uint32_t x, uint32_t n) {
+  return x >= n ? 0u : n - x >= 16 ? bits : bits & ((1u << (n - x)) - 1);
+}
+
+// 16 outputs of a level from 16 bits and the 1 bits before them: 4-byte
+// windows of the next level's values at cb + rank, one v_perm_b32 per 4.
+__device__ __forceinline__ void g_merge16(const GSmem &sm, uint32_t parity, uint32_t x, uint32_t bits, uint32_t r1,
+                                          uint32_t o[4]) {
+  const uint8_t *lds = reinterpret_cast<const uint8_t *>(&sm);
+  uint32_t a[4], s[4], w0[4], w1[4];
+  a[0] = static_cast<uint32_t>(reinterpret_cast<const uint8_t *>(sm.lvl[parity]) - lds) + x - r1;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const uint32_t m = (bits >> (4 * g)) & 15;
+    if (g < 3) a[g + 1] = a[g] + 4 - __popc(m);
+    s[g] = sm.sel[m];
+  }
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const uint32_t *q = reinterpret_cast<const uint32_t *>(lds + (a[g] & ~3u));
+    w0[g] = q[0];
+    w1[g] = q[1];
+  }
+#pragma unroll
+  for (int g = 0; g < 4; ++g) o[g] = __builtin_amdgcn_perm(0u, __builtin_amdgcn_alignbyte(w1[g], w0[g], a[g]), s[g]);
+}
+
+// Values of a level to its buffer, plus one (the level above reads them as
+// "1 + value"); the root's to the output.
+__device__ __forceinline__ void g_put(GSmem &sm, int k, uint32_t x, uint32_t n, const uint32_t o[4], uint8_t *out) {
+  if (x >= n) return;
+  if (k > 0) {
+    *reinterpret_cast<uint4 *>(reinterpret_cast<uint8_t *>(sm.lvl[k & 1]) + x) =
+        make_uint4(o[0] + 0x01010101u, o[1] + 0x01010101u, o[2] + 0x01010101u, o[3] + 0x01010101u);
+  } else if (n - x >= 16) {
+    const uint4 v = make_uint4(o[0], o[1], o[2], o[3]);
+    __builtin_memcpy(out + x, &v, 16);       // blocks start at any byte
+  } else {
+    for (uint32_t e = 0; e < n - x; ++e) out[x + e] = static_cast<uint8_t>(o[e >> 2] >> (8 * (e & 3)));
+  }
+}
+
+// One workgroup per block, tiles of kGT values, 16 a thread.  Top-down, the 0
+// bits of a level's share are the next level's share; bottom-up, the merge.
+// A tile's bits start at the levels' cursors, which are known before it, so
+// the top levels' bits (all threads) and those of the deeper ones (wave 0,
+// which takes every level of at most kGWave values without a barrier) are
+// loaded at once and stay in registers for both directions.  A level of at
+// most 64 values and all below it need no way up: a lane per value follows it
+// down, its place among the values still alive a mbcnt of their ballot, each
+// level's bits a 64-bit scalar.  Levels past those in registers load theirs
+// as they come.
+// Bound by the vector instructions of the levels (about 60 per 1024 values)
+// and the chain of the deep ones: 512 threads a block keep several blocks on
+// a CU.  64 Mi values of mean code length 2 in 64 Ki blocks: 145 us,
+// where 1024 threads with two barriers and two loads from memory per level
+// took 289 us.
+__global__ __launch_bounds__(kGNT, 8) void k_gdecode(const GJob *jobs, const uint2 *blocks, uint32_t nblocks) {
   __shared__ GSmem sm;
-  const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = __lane_id();
+  const uint32_t tid = threadIdx.x, lane = __lane_id();
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (blockIdx.x >= nblocks) return;
   const uint2 jb = blocks[blockIdx.x];
   const GJob &J = jobs[jb.x];
@@ -420,121 +493,215 @@ __global__ __launch_bounds__(kGNT) void k_gdecode(const GJob *jobs, const uint2 
     }
     sm.sel[tid] = s;
   }
-  if (tid == 0) {
-    int32_t err = 0;
-    const uint64_t *tab = reinterpret_cast<const uint64_t *>(J.in + kGHdr);
-    const uint64_t off = tab[b], end = tab[b + 1];
-    const uint64_t want = J.n_total - static_cast<uint64_t>(b) * J.block_size < J.block_size
-                              ? J.n_total - static_cast<uint64_t>(b) * J.block_size : J.block_size;
-    uint32_t K = 0, n = 0;
-    if (off < kGHdr + 8ull * (J.n_blocks + 1) || end < off || end > J.in_len || (off & 3) || end - off < 12) {
-      err = PIVCO_E_CORRUPT;
-    } else {
-      const uint8_t *p = J.in + off;
-      const uint32_t comp = *reinterpret_cast<const uint32_t *>(p);
-      n = *reinterpret_cast<const uint32_t *>(p + 4);
-      K = p[8] | (p[9] << 8);
-      const uint64_t hlen = 12 + 4ull * (K ? K - 1 : 0);
-      if (n != want || p[10] || p[11] || K > 256 || (n == 0) != (K == 0) || comp < hlen ||
-          comp > end - off || ((comp + 3ull) & ~3ull) != end - off) {
-        err = PIVCO_E_CORRUPT;
-      } else {
-        uint64_t o = off + hlen;
-        for (uint32_t k = 0; k < K; ++k) {
-          const uint32_t nk = k ? *reinterpret_cast<const uint32_t *>(p + 12 + 4 * (k - 1)) : n;
-          if (k && nk > sm.nk[k - 1]) err = PIVCO_E_CORRUPT;
-          sm.nk[k] = nk;
-          sm.boff[k] = o;
-          o += (nk + 7) / 8;
-        }
-        if (o != off + comp) err = PIVCO_E_CORRUPT;
-      }
-    }
-    if (err) K = 0;
-    sm.nk[K] = 0;
-    sm.K = K;
-    sm.n = n;
-    sm.err = err;
+  // the block's header, checked by every thread, and bitmap tid's size and place
+  const uint8_t *const in = J.in;
+  const uint64_t *tab = reinterpret_cast<const uint64_t *>(in + kGHdr);
+  const uint64_t off = tab[b], end = tab[b + 1];
+  const uint64_t want = J.n_total - static_cast<uint64_t>(b) * J.block_size < J.block_size
+                            ? J.n_total - static_cast<uint64_t>(b) * J.block_size : J.block_size;
+  bool bad = off < kGHdr + 8ull * (J.n_blocks + 1ull) || end < off || end > J.in_len || (off & 3) || end - off < 12;
+  uint32_t K = 0, n = 0, nk = 0;
+  uint64_t hlen = 12;
+  const uint8_t *p = in + off;
+  uint32_t comp = 0;
+  if (!bad) {
+    const uint32_t *p32 = reinterpret_cast<const uint32_t *>(p);
+    comp = p32[0];
+    n = p32[1];
+    const uint32_t kw = p32[2];
+    K = kw & 0xFFFF;
+    hlen = 12 + 4ull * (K ? K - 1 : 0);
+    bad = n != want || (kw >> 16) || K > 256 || (n == 0) != (K == 0) || comp < hlen || comp > end - off ||
+          ((comp + 3ull) & ~3ull) != end - off;
+    if (!bad && tid < K) nk = tid ? p32[2 + tid] : n;
   }
-  __syncthreads();
-  const uint32_t K = sm.K, n = sm.n;
-  if (sm.err) {
-    if (tid == 0) gset_err(J.status, static_cast<int32_t>(sm.err));
+  if (tid < 256) sm.nk[tid] = nk;
+  if (tid == 0) { sm.nk[256] = 0; sm.err = 0; }
+  uint64_t body;
+  const uint64_t bo = g_block_scan<kGNT>((static_cast<uint64_t>(nk) + 7) / 8, sm.part, &body);
+  if (tid < 256) {
+    sm.boff[tid] = off + hlen + bo;
+    sm.cur[tid] = 0;
+    if (!bad && tid && tid < K && nk > sm.nk[tid - 1]) bad = true;
+  }
+  if (tid == 0) sm.cur[256] = 0;
+  if (!bad && hlen + body != comp) bad = true;
+  if (__syncthreads_or(bad)) {
+    if (tid == 0) gset_err(J.status, PIVCO_E_CORRUPT);
     return;
   }
-  for (uint32_t k = tid; k <= K; k += kGNT) sm.cur[k] = 0;
-  __syncthreads();
   uint8_t *out = J.out + static_cast<uint64_t>(b) * J.block_size;
-  const uint8_t *lds = reinterpret_cast<const uint8_t *>(&sm);
+  // 16 bits of bitmap k, x values after its cursor (zeros where it holds no
+  // more); the block ends at a multiple of 4 bytes, so whole words of it are read
+  const uint32_t *in32 = reinterpret_cast<const uint32_t *>(in);
+  const uint64_t wend = end >> 2;
+  auto fetch = [&](uint32_t k, uint32_t x) -> uint32_t {
+    const uint32_t c = sm.cur[k];
+    if (k >= K || x >= sm.nk[k] - c) return 0u;
+    const uint64_t bit = 8 * sm.boff[k] + c + x, q = bit >> 5;
+    const uint32_t w0 = in32[q], w1 = q + 1 < wend ? in32[q + 1] : 0u;
+    return __builtin_amdgcn_alignbit(w1, w0, static_cast<uint32_t>(bit & 31)) & 0xFFFF;
+  };
+  const uint32_t x = 16 * tid, xl = 16 * lane;
   for (uint32_t t0 = 0; t0 < n; t0 += kGT) {
     const uint32_t S = n - t0 < kGT ? n - t0 : kGT;
-    // count, top-down: the 0 bits of bitmap k's share are bitmap k+1's share
-    if (tid == 0) sm.tv[0] = S;
-    __syncthreads();
-    uint32_t kmax = 0;                       // bitmaps with a share in this tile
-    for (uint32_t k = 0; k < K; ++k) {
-      const uint32_t tvk = sm.tv[k];
-      if (tvk == 0) break;
+    uint32_t top[kGStat], deep[kGDeep];
+#pragma unroll
+    for (int k = 0; k < kGStat; ++k) top[k] = fetch(k, x);
+    uint32_t w_lo = 0, w_hi = 0, rem = 0;    // level lane: its first 64 bits, values left of it
+    auto words64 = [&](uint32_t k) {
+      w_lo = w_hi = rem = 0;
+      if (k >= K) return;
+      const uint32_t c = sm.cur[k];
+      rem = sm.nk[k] - c;
+      if (rem == 0) return;
+      const uint64_t bit = 8 * sm.boff[k] + c, q = bit >> 5;
+      const uint32_t a0 = in32[q], a1 = q + 1 < wend ? in32[q + 1] : 0u, a2 = q + 2 < wend ? in32[q + 2] : 0u;
+      w_lo = __builtin_amdgcn_alignbit(a1, a0, static_cast<uint32_t>(bit & 31));
+      w_hi = __builtin_amdgcn_alignbit(a2, a1, static_cast<uint32_t>(bit & 31));
+    };
+    if (wave == 0) {
+#pragma unroll
+      for (int i = 0; i < kGDeep; ++i) deep[i] = fetch(kGStat + i, xl);
+      words64(lane);
+    }
+    // count: a level's bits and the 1 bits before them, packed
+    uint32_t tv = S, kmax = 0;               // kmax: levels with a share in this tile
+    bool over = false;
+    auto next = [&](uint32_t k, uint32_t ones) {   // level k's share tv is counted
+      if (tid == 0) sm.tv[k] = tv;
       kmax = k + 1;
-      const uint32_t x = 16 * tid;
-      const uint32_t bits = x < tvk ? g_bits16(J.in + sm.boff[k], (sm.nk[k] + 7) / 8, sm.cur[k] + x) &
-                                          (tvk - x >= 16 ? 0xFFFFu : (1u << (tvk - x)) - 1)
-                                    : 0u;
-      const uint32_t inc = g_incl_scan(__popc(bits));
-      if (lane == kGW - 1) sm.wsum[wave] = inc;
-      __syncthreads();
-      if (tid == 0) {
-        uint32_t ones = 0;
-        for (uint32_t w = 0; w < kGNT / kGW; ++w) ones += sm.wsum[w];
-        const uint32_t zeros = tvk - ones;
-        if (sm.cur[k + 1] + zeros > sm.nk[k + 1]) { sm.err = PIVCO_E_CORRUPT; sm.tv[k + 1] = 0; }
-        else sm.tv[k + 1] = zeros;
+      const uint32_t zeros = tv - ones;
+      over |= sm.cur[k + 1] + zeros > sm.nk[k + 1];
+      tv = over ? 0u : zeros;
+    };
+    const uint32_t wave0 = kGWave * wave;    // the wave's first value
+    uint32_t share[kGStat] = {};
+#pragma unroll
+    for (int k = 0; k < kGStat; ++k) {
+      if (tv == 0) break;
+      share[k] = tv;
+      uint32_t bits = 0, pc = 0, inc = 0, before;
+      if (wave0 < tv) {
+        bits = g_first(top[k], x, tv);
+        pc = __popc(bits);
+        inc = g_incl_scan(pc);
+      }
+      const uint32_t ones = g_waves(sm, k & 1, inc, &before);
+      top[k] = bits | ((before + inc - pc) << 16);
+      next(k, ones);
+    }
+    // deeper levels still wider than a wave
+    uint32_t kw = kmax;
+    while (tv > kGWave) {
+      const uint32_t k = kmax;
+      uint32_t inc = 0, before;
+      if (wave0 < tv) inc = g_incl_scan(__popc(g_first(fetch(k, x), x, tv)));
+      next(k, g_waves(sm, k & 1, inc, &before));
+      kw = kmax;
+    }
+    // one wave takes the rest, down and up again
+    if (wave == 0 && tv) {
+      const uint32_t k0 = kmax;
+      const bool regs = k0 == kGStat;
+      auto total = [](uint32_t inc) { return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(inc), kGW - 1)); };
+      if (regs) {
+#pragma unroll
+        for (int i = 0; i < kGDeep; ++i) {
+          if (tv <= kGW) break;
+          const uint32_t bits = g_first(deep[i], xl, tv), pc = __popc(bits), inc = g_incl_scan(pc);
+          deep[i] = bits | ((inc - pc) << 16);
+          next(kGStat + i, total(inc));
+        }
+      }
+      const int kreg = static_cast<int>(kmax);   // levels from kGStat (regs) to here are in registers
+      while (tv > kGW) {
+        const uint32_t bits = g_first(fetch(kmax, xl), xl, tv);
+        next(kmax, total(g_incl_scan(__popc(bits))));
+      }
+      const int kd = static_cast<int>(kmax);
+      if (tv) {                              // at most 64 values: a lane each, straight down
+        bool alive = lane < tv;
+        uint32_t val = 0, tvs = 0;
+        uint32_t k = static_cast<uint32_t>(kd), base = 0;
+        while (tv) {
+          if (k - base >= kGW) {             // the next 64 levels (the first are loaded)
+            if (base + lane >= static_cast<uint32_t>(kd) && base + lane < k) sm.tv[base + lane] = tvs;
+            base = k & ~(kGW - 1u);
+            words64(base + lane);
+          }
+          const uint32_t l = k - base;
+          if (tv > static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(rem), l))) { over = true; break; }
+          const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(w_lo), l);
+          const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(w_hi), l);
+          const uint64_t am = __ballot(alive);
+          const uint32_t idx = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(am >> 32),
+                                                         __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(am), 0u));
+          if (lane == l) tvs = tv;
+          const bool one = alive && (((idx & 32 ? hi : lo) >> (idx & 31)) & 1);
+          if (one) val = k - static_cast<uint32_t>(kd);
+          alive = alive && !one;
+          tv = static_cast<uint32_t>(__popcll(__ballot(alive)));
+          ++k;
+        }
+        kmax = k;
+        if (base + lane >= static_cast<uint32_t>(kd) && base + lane < k) sm.tv[base + lane] = tvs;
+        reinterpret_cast<uint8_t *>(sm.lvl[kd & 1])[lane] = static_cast<uint8_t>(val + 1);
+      }
+      g_wave_sync();
+      for (int k = kd - 1; k >= kreg; --k) {
+        const uint32_t m = sm.tv[k], bits = g_first(fetch(k, xl), xl, m), pc = __popc(bits);
+        uint32_t o[4];
+        g_merge16(sm, (k + 1) & 1, xl, bits, g_incl_scan(pc) - pc, o);
+        g_put(sm, k, xl, m, o, out + t0);
+        g_wave_sync();
+      }
+      if (regs) {
+#pragma unroll
+        for (int i = kGDeep - 1; i >= 0; --i) {
+          if (kGStat + i >= kreg) continue;
+          uint32_t o[4];
+          g_merge16(sm, (kGStat + i + 1) & 1, xl, deep[i] & 0xFFFF, deep[i] >> 16, o);
+          g_put(sm, kGStat + i, xl, sm.tv[kGStat + i], o, out + t0);
+          g_wave_sync();
+        }
+      }
+      if (lane == 0) {
+        sm.depth = kmax;
+        if (over) sm.err = static_cast<uint32_t>(PIVCO_E_CORRUPT);
+      }
+    } else if (tv == 0 && tid == 0) {
+      sm.depth = kmax;
+      if (over) sm.err = static_cast<uint32_t>(PIVCO_E_CORRUPT);
+    }
+    __syncthreads();
+    kmax = sm.depth;
+    if (sm.err) break;
+    for (int k = static_cast<int>(kw) - 1; k >= kGStat; --k) {
+      const uint32_t m = sm.tv[k];
+      uint32_t bits = 0, pc = 0, inc = 0, before;
+      if (wave0 < m) {
+        bits = g_first(fetch(k, x), x, m);
+        pc = __popc(bits);
+        inc = g_incl_scan(pc);
+      }
+      g_waves(sm, k & 1, inc, &before);
+      if (wave0 < m) {
+        uint32_t o[4];
+        g_merge16(sm, (k + 1) & 1, x, bits, before + inc - pc, o);
+        g_put(sm, k, x, m, o, out + t0);
       }
       __syncthreads();
     }
-    if (sm.err) break;
-    // merge, bottom-up; level k's values go to buffer k & 1, plus one for
-    // every level but the first (its parent reads them as "1 + value")
-    for (int k = static_cast<int>(kmax) - 1; k >= 0; --k) {
-      const uint32_t tvk = sm.tv[k];
-      const uint32_t x = 16 * tid;
-      const bool act = x < tvk;
-      const uint32_t bits = act ? g_bits16(J.in + sm.boff[k], (sm.nk[k] + 7) / 8, sm.cur[k] + x) &
-                                      (tvk - x >= 16 ? 0xFFFFu : (1u << (tvk - x)) - 1)
-                                : 0u;
-      const uint32_t pc = __popc(bits);
-      const uint32_t inc = g_incl_scan(pc);
-      if (lane == kGW - 1) sm.wsum[wave] = inc;
-      __syncthreads();
-      uint32_t r1 = inc - pc;
-      for (uint32_t w = 0; w < wave; ++w) r1 += sm.wsum[w];
-      uint32_t r0 = x - r1;                  // values of the next bitmap before this task
-      const uint32_t cb = static_cast<uint32_t>(reinterpret_cast<const uint8_t *>(sm.lvl[(k + 1) & 1]) - lds);
-      uint32_t o[4];
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const uint32_t m = (bits >> (4 * g)) & 15;
-        const uint32_t a = cb + r0;
-        const uint32_t *q = reinterpret_cast<const uint32_t *>(lds + (a & ~3u));
-        const uint32_t win = __builtin_amdgcn_alignbyte(q[1], q[0], a);
-        o[g] = __builtin_amdgcn_perm(0u, win, sm.sel[m]);
-        r0 += 4 - __popc(m);
+    for (int k = kGStat - 1; k >= 0; --k) {
+      if (share[k] == 0) continue;
+      if (wave0 < share[k]) {
+        uint32_t o[4];
+        g_merge16(sm, (k + 1) & 1, x, top[k] & 0xFFFF, top[k] >> 16, o);
+        g_put(sm, k, x, share[k], o, out + t0);
       }
-      if (act) {
-        if (k > 0) {
-          uint4 *dst = reinterpret_cast<uint4 *>(sm.lvl[k & 1]) + tid;
-          *dst = make_uint4(o[0] + 0x01010101u, o[1] + 0x01010101u, o[2] + 0x01010101u, o[3] + 0x01010101u);
-        } else {
-          uint8_t *d = out + t0 + x;
-          const uint32_t cnt = tvk - x < 16 ? tvk - x : 16;
-          if (cnt == 16 && !(reinterpret_cast<uintptr_t>(d) & 15)) {
-            *reinterpret_cast<uint4 *>(d) = make_uint4(o[0], o[1], o[2], o[3]);
-          } else {
-            for (uint32_t e = 0; e < cnt; ++e) d[e] = static_cast<uint8_t>(o[e >> 2] >> (8 * (e & 3)));
-          }
-        }
-      }
-      __syncthreads();
+      if (k) __syncthreads();
     }
     for (uint32_t k = tid; k < kmax; k += kGNT) sm.cur[k] += sm.tv[k];
     __syncthreads();
