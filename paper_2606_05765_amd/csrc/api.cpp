@@ -96,6 +96,7 @@ struct HostPlan {
   uint64_t scratch_words = 0;
   uint64_t chunk_cap = 0;      // entropy-coded chunk list capacity (bound over the jobs)
   uint32_t coders = 0;         // bit 0: some job has rANS nodes; bit 1: tANS nodes
+  std::vector<uint8_t> lists;  // the lists as they lie in the workspace, from off_jobs to off_recs
   // workspace layout (byte offsets)
   uint64_t off_ctr = 0, off_jobs = 0, off_blocks = 0, off_items = 0, off_ritems = 0,
            off_tiled = 0, off_status0 = 0, off_recs = 0, off_tab = 0, off_chunks = 0, off_scratch = 0,
@@ -127,10 +128,19 @@ pivco_status read_headers(const pivco_job *h_jobs, uint32_t count, void *d_ws, u
   const uint64_t jb = align_up(sizeof(pivco_job) * count, 256);
   if (d_ws && ws_bytes >= jb + kHeaderBytes * count) {
     uint8_t *ws = static_cast<uint8_t *>(d_ws);
-    if (hipMemcpyAsync(ws, h_jobs, sizeof(pivco_job) * count, hipMemcpyHostToDevice, s) != hipSuccess)
+    if (count == 1) {                    // one header: a copy on s, without the kernel that gathers several
+      const uint64_t nbytes = std::min<uint64_t>(kHeaderBytes, h_jobs[0].in_len);
+      if (nbytes && (hipMemcpyAsync(hdr.data(), h_jobs[0].d_in, nbytes, hipMemcpyDeviceToHost, s) != hipSuccess ||
+                     hipStreamSynchronize(s) != hipSuccess))
+        return PIVCO_E_DEVICE;
+      return PIVCO_OK;
+    }
+    if (count <= kGatherJobs) {
+      if (launch_gather_headers_of(s, h_jobs, count, ws + jb) != hipSuccess) return PIVCO_E_DEVICE;
+    } else if (hipMemcpyAsync(ws, h_jobs, sizeof(pivco_job) * count, hipMemcpyHostToDevice, s) != hipSuccess ||
+               launch_gather_headers(s, reinterpret_cast<const pivco_job *>(ws), count, ws + jb) != hipSuccess) {
       return PIVCO_E_DEVICE;
-    if (launch_gather_headers(s, reinterpret_cast<const pivco_job *>(ws), count, ws + jb) != hipSuccess)
-      return PIVCO_E_DEVICE;
+    }
     if (hipMemcpyAsync(hdr.data(), ws + jb, kHeaderBytes * count, hipMemcpyDeviceToHost, s) != hipSuccess)
       return PIVCO_E_DEVICE;
     if (hipStreamSynchronize(s) != hipSuccess) return PIVCO_E_DEVICE;
@@ -213,19 +223,18 @@ pivco_status build_plan(const pivco_job *h_jobs, uint32_t count, const std::vect
   return PIVCO_OK;
 }
 
-pivco_status upload_plan(const HostPlan &p, void *d_ws, hipStream_t s) {
-  uint8_t *ws = static_cast<uint8_t *>(d_ws);
-  auto cp = [&](uint64_t off, const void *src, uint64_t n) {
-    return n == 0 || hipMemcpyAsync(ws + off, src, n, hipMemcpyHostToDevice, s) == hipSuccess;
+void pack_lists(HostPlan &p) {
+  std::vector<uint8_t> &buf = p.lists;
+  buf.assign(p.off_recs - p.off_jobs, 0);
+  auto put = [&](uint64_t off, const void *src, uint64_t n) {
+    if (n) std::memcpy(&buf[off - p.off_jobs], src, n);
   };
-  if (!cp(p.off_jobs, p.jobs.data(), sizeof(JobDev) * p.count) ||
-      !cp(p.off_blocks, p.w.blocks.data(), 8 * p.w.blocks.size()) ||
-      !cp(p.off_items, p.w.items.data(), 8 * p.w.items.size()) ||
-      !cp(p.off_ritems, p.w.ritems.data(), 8 * p.w.ritems.size()) ||
-      !cp(p.off_tiled, p.w.tiled.data(), sizeof(TiledBlock) * p.w.tiled.size()) ||
-      !cp(p.off_status0, p.status0.data(), 4ull * p.count))
-    return PIVCO_E_DEVICE;
-  return PIVCO_OK;
+  put(p.off_jobs, p.jobs.data(), sizeof(JobDev) * p.count);
+  put(p.off_blocks, p.w.blocks.data(), 8 * p.w.blocks.size());
+  put(p.off_items, p.w.items.data(), 8 * p.w.items.size());
+  put(p.off_ritems, p.w.ritems.data(), 8 * p.w.ritems.size());
+  put(p.off_tiled, p.w.tiled.data(), sizeof(TiledBlock) * p.w.tiled.size());
+  put(p.off_status0, p.status0.data(), 4ull * p.count);
 }
 
 struct Dev {
@@ -271,12 +280,33 @@ pivco_tune default_tune(uint32_t n_items, uint64_t chunk_cap) {
   return t;
 }
 
-// Enqueue one batched decode (kernels only; capturable).
+pivco_status upload_lists(const HostPlan &p, void *d_ws, hipStream_t s) {
+  return p.lists.empty() || hipMemcpyAsync(static_cast<uint8_t *>(d_ws) + p.off_jobs, p.lists.data(), p.lists.size(),
+                                           hipMemcpyHostToDevice, s) == hipSuccess
+             ? PIVCO_OK : PIVCO_E_DEVICE;
+}
+
+// Resets the counters and statuses of a decode whose lists are in the
+// workspace; with_lists: they are brought there too, up to kInitListBytes as
+// the kernel's arguments, else by one copy.
+pivco_status enqueue_init(const HostPlan &p, void *d_ws, int32_t *d_status, bool with_lists, hipStream_t s) {
+  const Dev d = dev_ptrs(p, d_ws);
+  if (with_lists && p.lists.size() <= kInitListBytes)
+    return launch_init_lists(s, d.ctr, d_status, p.count, static_cast<uint32_t>(p.off_status0 - p.off_jobs),
+                             static_cast<uint8_t *>(d_ws) + p.off_jobs, p.lists.data(),
+                             static_cast<uint32_t>(p.lists.size())) == hipSuccess
+               ? PIVCO_OK : PIVCO_E_DEVICE;
+  if (with_lists)
+    if (const pivco_status st = upload_lists(p, d_ws, s)) return st;
+  return launch_init(s, d.ctr, d_status, d.status0, p.count) == hipSuccess ? PIVCO_OK : PIVCO_E_DEVICE;
+}
+
+// Enqueue one batched decode (without lists kernels only, capturable).
 pivco_status enqueue_batch(const HostPlan &p, void *d_ws, int32_t *d_status, const pivco_tune &t,
-                           hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+                           hipStream_t s, hipEvent_t ev0, hipEvent_t ev1, bool with_lists = false) {
   Dev d = dev_ptrs(p, d_ws);
   const WorkLists &w = p.w;
-  if (launch_init(s, d.ctr, d_status, d.status0, p.count) != hipSuccess) return PIVCO_E_DEVICE;
+  if (const pivco_status st = enqueue_init(p, d_ws, d_status, with_lists, s)) return st;
   if (launch_plan(s, d.jobs, d.blocks, static_cast<uint32_t>(w.blocks.size()), d.recs, d.ctr,
                   d.chunks, p.chunk_cap) != hipSuccess)
     return PIVCO_E_DEVICE;
@@ -297,8 +327,10 @@ pivco_status enqueue_batch(const HostPlan &p, void *d_ws, int32_t *d_status, con
   return PIVCO_OK;
 }
 
+// Plans a decode from the streams' headers; upload: its lists go into the
+// workspace, else enqueue_init brings them.
 pivco_status prepare(const pivco_job *h_jobs, uint32_t count, int32_t *d_status, void *d_ws,
-                     uint64_t ws_bytes, hipStream_t s, HostPlan &p) {
+                     uint64_t ws_bytes, hipStream_t s, HostPlan &p, bool upload = true) {
   pivco_status st = check_jobs(h_jobs, count);
   if (st) return st;
   if (count && (!d_status || !d_ws)) return PIVCO_E_ARG;
@@ -308,7 +340,8 @@ pivco_status prepare(const pivco_job *h_jobs, uint32_t count, int32_t *d_status,
   st = build_plan(h_jobs, count, hdr, d_status, p);
   if (st) return st;
   if (p.total > ws_bytes) return PIVCO_E_CAPACITY;
-  return upload_plan(p, d_ws, s);
+  pack_lists(p);
+  return upload ? upload_lists(p, d_ws, s) : PIVCO_OK;
 }
 
 }  // namespace
@@ -418,11 +451,11 @@ uint64_t pivco_decode_workspace(const pivco_job *h_jobs, uint32_t count, hipStre
 pivco_status pivco_decode_batch(const pivco_job *h_jobs, uint32_t count, int32_t *d_status,
                                 void *d_ws, uint64_t ws_bytes, hipStream_t s) {
   HostPlan p;
-  pivco_status st = prepare(h_jobs, count, d_status, d_ws, ws_bytes, s, p);
+  pivco_status st = prepare(h_jobs, count, d_status, d_ws, ws_bytes, s, p, false);
   if (st) return st;
   if (count == 0) return PIVCO_OK;
   const pivco_tune t = default_tune(static_cast<uint32_t>(p.w.items.size()), p.chunk_cap);
-  return enqueue_batch(p, d_ws, d_status, t, s, nullptr, nullptr);
+  return enqueue_batch(p, d_ws, d_status, t, s, nullptr, nullptr, true);
 }
 
 pivco_status pivco_decode(const void *d_in, uint64_t in_len, void *d_out, uint64_t out_cap,

@@ -2580,6 +2580,20 @@ __global__ void k_init(Counters *ctr, int32_t *status, const int32_t *status0, u
   if (i < count) status[i] = status0[i];
 }
 
+// The same with the plan's lists in the arguments (one workgroup): a call of
+// one small stream then starts without a copy from the host (six of them and
+// the header's gathering were most of the 115 us of a 4 KiB call; 117 -> 68).
+struct InitLists {
+  uint32_t w[kInitListBytes / 4];
+};
+__global__ __launch_bounds__(256) void k_init_lists(Counters *ctr, int32_t *status, uint32_t count, uint32_t status0_at,
+                                                    uint32_t *dst, uint32_t nw, InitLists lists) {
+  const uint32_t i = threadIdx.x;
+  if (i == 0) { ctr->merge_next = 0; ctr->rans_next = 0; ctr->rans_chunks = 0; ctr->fse_next = 0; }
+  for (uint32_t k = i; k < nw; k += 256) dst[k] = lists.w[k];
+  for (uint32_t k = i; k < count; k += 256) status[k] = static_cast<int32_t>(lists.w[status0_at + k]);
+}
+
 // Copies the 48-byte header of every job's stream into hdr (planning).
 __global__ void k_gather_headers(const pivco_job *jobs, uint32_t count, uint8_t *hdr) {
   const uint32_t j = blockIdx.x;
@@ -2590,6 +2604,16 @@ __global__ void k_gather_headers(const pivco_job *jobs, uint32_t count, uint8_t 
     hdr[static_cast<uint64_t>(j) * kHeaderBytes + i] =
         i < jb.in_len ? static_cast<const uint8_t *>(jb.d_in)[i] : 0;
   }
+}
+
+// The same for up to kGatherJobs jobs in the kernel's arguments.
+struct GatherJobs {
+  const uint8_t *in[kGatherJobs];
+  uint32_t len[kGatherJobs];   // readable bytes, at most a header's
+};
+__global__ void k_gather_headers_of(GatherJobs a, uint8_t *hdr) {
+  const uint32_t j = blockIdx.x, i = threadIdx.x;
+  if (i < kHeaderBytes) hdr[j * kHeaderBytes + i] = i < a.len[j] ? a.in[j][i] : 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -2833,8 +2857,11 @@ const char *merge_variant_name(uint32_t v) {
 }
 
 int merge_variant_occupancy(uint32_t v) {
+  if (v == 0) {                          // the default configuration's, asked for on every call
+    static const int occ = occupancy_t<Cfg0>();
+    return occ;
+  }
   switch (v) {
-    case 0: return occupancy_t<Cfg0>();
     case 1: return occupancy_t<Cfg1>();
     case 2: return occupancy_t<Cfg2>();
     case 3: return occupancy_t<Cfg3>();
@@ -2921,6 +2948,25 @@ hipError_t launch_init(hipStream_t s, Counters *ctr, int32_t *status, const int3
                        uint32_t count) {
   const uint32_t n = count > 0 ? count : 1;
   hipLaunchKernelGGL(k_init, dim3((n + 255) / 256), dim3(256), 0, s, ctr, status, status0, count);
+  return hipGetLastError();
+}
+
+hipError_t launch_init_lists(hipStream_t s, Counters *ctr, int32_t *status, uint32_t count, uint32_t status0_at,
+                             uint8_t *dst, const uint8_t *h_src, uint32_t n) {
+  InitLists a;
+  __builtin_memcpy(a.w, h_src, n);
+  hipLaunchKernelGGL(k_init_lists, dim3(1), dim3(256), 0, s, ctr, status, count, status0_at / 4,
+                     reinterpret_cast<uint32_t *>(dst), n / 4, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_gather_headers_of(hipStream_t s, const pivco_job *h_jobs, uint32_t count, uint8_t *hdr) {
+  GatherJobs a;
+  for (uint32_t j = 0; j < count; ++j) {
+    a.in[j] = static_cast<const uint8_t *>(h_jobs[j].d_in);
+    a.len[j] = h_jobs[j].in_len < kHeaderBytes ? static_cast<uint32_t>(h_jobs[j].in_len) : kHeaderBytes;
+  }
+  hipLaunchKernelGGL(k_gather_headers_of, dim3(count), dim3(64), 0, s, a, hdr);
   return hipGetLastError();
 }
 

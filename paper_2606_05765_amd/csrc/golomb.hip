@@ -45,9 +45,26 @@ struct GJob {
   uint64_t out_cap;
   uint64_t n_total;
   uint32_t n_blocks, block_size;
-  int32_t *status;
-  uint64_t pad;
+  uint32_t first;         // its first block among the batch's (jobs in error: none)
+  int32_t status;         // its status before any block is decoded
 };
+
+// Jobs that travel as arguments of the kernel that stores them: a call of few
+// streams copies nothing from the host.
+constexpr uint32_t kGArgJobs = 48;
+struct GArgs {
+  GJob j[kGArgJobs];
+};
+__global__ void k_ginit(GJob *jobs, uint32_t count, int32_t *status, GArgs a) {
+  const uint32_t i = threadIdx.x;
+  if (i >= count) return;
+  jobs[i] = a.j[i];
+  status[i] = a.j[i].status;
+}
+__global__ void k_gstatus(const GJob *jobs, uint32_t count, int32_t *status) {
+  const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+  if (i < count) status[i] = jobs[i].status;
+}
 
 __device__ __forceinline__ void gset_err(int32_t *status, int32_t e) {
   atomicCAS(reinterpret_cast<int *>(status), 0, e);
@@ -476,14 +493,21 @@ __device__ __forceinline__ void g_put(GSmem &sm, int k, uint32_t x, uint32_t n, 
 // a CU.  64 Mi values of mean code length 2 in 64 Ki blocks: 145 us,
 // where 1024 threads with two barriers and two loads from memory per level
 // took 289 us.
-__global__ __launch_bounds__(kGNT, 8) void k_gdecode(const GJob *jobs, const uint2 *blocks, uint32_t nblocks) {
+__global__ __launch_bounds__(kGNT, 8) void k_gdecode(const GJob *jobs, uint32_t njobs, uint32_t nblocks,
+                                                     int32_t *status) {
   __shared__ GSmem sm;
   const uint32_t tid = threadIdx.x, lane = __lane_id();
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (blockIdx.x >= nblocks) return;
-  const uint2 jb = blocks[blockIdx.x];
-  const GJob &J = jobs[jb.x];
-  const uint32_t b = jb.y;
+  uint32_t job = 0;          // the last job whose blocks start at or before this one
+  for (uint32_t n = njobs; n > 1;) {
+    const uint32_t half = n / 2;
+    if (jobs[job + half].first <= blockIdx.x) { job += half; n -= half; }
+    else n = half;
+  }
+  const GJob &J = jobs[job];
+  const uint32_t b = blockIdx.x - J.first;
+  status += job;
   if (tid < 16) {            // v_perm selectors: byte e takes the next value of
     uint32_t s = 0, z = 0;   // the next bitmap (0 bit) or the constant 0 (1 bit)
     for (int e = 0; e < 4; ++e) {
@@ -527,7 +551,7 @@ __global__ __launch_bounds__(kGNT, 8) void k_gdecode(const GJob *jobs, const uin
   if (tid == 0) sm.cur[256] = 0;
   if (!bad && hlen + body != comp) bad = true;
   if (__syncthreads_or(bad)) {
-    if (tid == 0) gset_err(J.status, PIVCO_E_CORRUPT);
+    if (tid == 0) gset_err(status, PIVCO_E_CORRUPT);
     return;
   }
   uint8_t *out = J.out + static_cast<uint64_t>(b) * J.block_size;
@@ -711,7 +735,7 @@ __global__ __launch_bounds__(kGNT, 8) void k_gdecode(const GJob *jobs, const uin
     for (uint32_t k = tid; k < K; k += kGNT)
       if (sm.cur[k] != sm.nk[k]) atomicCAS(&sm.err, 0u, static_cast<uint32_t>(PIVCO_E_CORRUPT));
   __syncthreads();
-  if (tid == 0 && sm.err) gset_err(J.status, static_cast<int32_t>(sm.err));
+  if (tid == 0 && sm.err) gset_err(status, static_cast<int32_t>(sm.err));
 }
 
 inline uint64_t galign(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
@@ -813,8 +837,7 @@ pivco_status pivco_golomb_decode(const pivco_job *h_jobs, uint32_t count, int32_
                                  uint64_t ws_bytes, hipStream_t s) {
   if (count && (!h_jobs || !d_status || !d_ws)) return PIVCO_E_ARG;
   std::vector<GJob> jobs(count);
-  std::vector<uint2> blocks;
-  std::vector<int32_t> st0(count, PIVCO_OK);
+  uint64_t blocks = 0;
   for (uint32_t j = 0; j < count; ++j) {
     const pivco_job &jb = h_jobs[j];
     GJob &g = jobs[j];
@@ -823,11 +846,11 @@ pivco_status pivco_golomb_decode(const pivco_job *h_jobs, uint32_t count, int32_
     g.in_len = jb.in_len;
     g.out = static_cast<uint8_t *>(jb.d_out);
     g.out_cap = jb.out_cap;
-    g.status = d_status + j;
+    g.first = static_cast<uint32_t>(blocks);
     if (jb.in_len && (!jb.d_in || (reinterpret_cast<uintptr_t>(jb.d_in) & 15))) return PIVCO_E_ARG;
     uint8_t h[kGHdr] = {0};
     if (jb.in_len < kGHdr || hipMemcpy(h, jb.d_in, kGHdr, hipMemcpyDeviceToHost) != hipSuccess) {
-      st0[j] = PIVCO_E_CORRUPT;
+      g.status = PIVCO_E_CORRUPT;
       continue;
     }
     uint32_t m = 0, bs = 0, nb = 0;
@@ -838,31 +861,35 @@ pivco_status pivco_golomb_decode(const pivco_job *h_jobs, uint32_t count, int32_
     std::memcpy(&nb, h + 20, 4);
     if (m != kGMagic || h[4] != 1 || h[5] || h[6] || h[7] || bs == 0 || div_up(n, bs) != nb ||
         jb.in_len < kGHdr + 8ull * (nb + 1ull)) {
-      st0[j] = PIVCO_E_CORRUPT;
+      g.status = PIVCO_E_CORRUPT;
       continue;
     }
-    if (n > jb.out_cap) { st0[j] = PIVCO_E_CAPACITY; continue; }
+    if (n > jb.out_cap) { g.status = PIVCO_E_CAPACITY; continue; }
     g.n_total = n;
     g.n_blocks = nb;
     g.block_size = bs;
-    for (uint32_t b = 0; b < nb; ++b) blocks.push_back(make_uint2(j, b));
+    blocks += nb;
   }
-  const uint64_t need = galign(count * sizeof(GJob) + 16, 256) + galign(8 * blocks.size() + 16, 256);
+  // room for the batch's blocks, 8 bytes each, is part of the workspace that
+  // callers were told to bring
+  const uint64_t need = galign(count * sizeof(GJob) + 16, 256) + galign(8 * blocks + 16, 256);
   if (ws_bytes < need) return PIVCO_E_CAPACITY;
   if (count == 0) return PIVCO_OK;
-  uint8_t *ws = static_cast<uint8_t *>(d_ws);
-  GJob *dj = reinterpret_cast<GJob *>(ws);
-  uint2 *db = reinterpret_cast<uint2 *>(ws + galign(count * sizeof(GJob) + 16, 256));
-  if (hipMemcpyAsync(dj, jobs.data(), count * sizeof(GJob), hipMemcpyHostToDevice, s) != hipSuccess ||
-      (blocks.size() && hipMemcpyAsync(db, blocks.data(), 8 * blocks.size(), hipMemcpyHostToDevice, s) != hipSuccess) ||
-      hipMemcpyAsync(d_status, st0.data(), 4ull * count, hipMemcpyHostToDevice, s) != hipSuccess)
-    return PIVCO_E_DEVICE;
-  if (!blocks.empty()) {
-    hipLaunchKernelGGL(k_gdecode, dim3(static_cast<uint32_t>(blocks.size())), dim3(kGNT), 0, s, dj, db,
-                       static_cast<uint32_t>(blocks.size()));
-    if (hipGetLastError() != hipSuccess) return PIVCO_E_DEVICE;
+  if (blocks > 0x7FFFFFFFull) return PIVCO_E_UNSUPPORTED;
+  GJob *dj = static_cast<GJob *>(d_ws);
+  if (count <= kGArgJobs) {
+    GArgs a;
+    std::copy(jobs.begin(), jobs.end(), a.j);
+    hipLaunchKernelGGL(k_ginit, dim3(1), dim3(64), 0, s, dj, count, d_status, a);
+  } else {
+    if (hipMemcpyAsync(dj, jobs.data(), count * sizeof(GJob), hipMemcpyHostToDevice, s) != hipSuccess)
+      return PIVCO_E_DEVICE;
+    hipLaunchKernelGGL(k_gstatus, dim3((count + 255) / 256), dim3(256), 0, s, dj, count, d_status);
   }
-  // the host buffers above must outlive the copies
+  if (blocks)
+    hipLaunchKernelGGL(k_gdecode, dim3(static_cast<uint32_t>(blocks)), dim3(kGNT), 0, s, dj, count,
+                       static_cast<uint32_t>(blocks), d_status);
+  if (hipGetLastError() != hipSuccess) return PIVCO_E_DEVICE;
   if (hipStreamSynchronize(s) != hipSuccess) return PIVCO_E_DEVICE;
   return PIVCO_OK;
 }

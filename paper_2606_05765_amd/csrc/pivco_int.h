@@ -262,6 +262,15 @@ hipError_t launch_topdown(uint32_t grid, hipStream_t s, const JobDev *jobs, cons
 int topdown_occupancy();
 hipError_t launch_init(hipStream_t s, Counters *ctr, int32_t *status, const int32_t *status0,
                        uint32_t count);
+// The same, with n bytes (a multiple of 4, at most kInitListBytes) of host
+// data written to `dst`, the first statuses among them at byte status0_at:
+// they travel as kernel arguments (which hold 4 KiB), so that a small decode
+// uploads nothing.
+constexpr uint32_t kInitListBytes = 3072;
+hipError_t launch_init_lists(hipStream_t s, Counters *ctr, int32_t *status, uint32_t count, uint32_t status0_at,
+                             uint8_t *dst, const uint8_t *h_src, uint32_t n);
+constexpr uint32_t kGatherJobs = 256;
+hipError_t launch_gather_headers_of(hipStream_t s, const pivco_job *h_jobs, uint32_t count, uint8_t *hdr);
 hipError_t launch_gather_headers(hipStream_t s, const pivco_job *jobs, uint32_t count, uint8_t *hdr);
 
 }  // namespace pivco

@@ -287,7 +287,7 @@ def pivco_decode_batch(streams, outs=None, ws=None, plain=False, entry="pivco_de
     jobs = _jobs(streams, outs)
     if ws is None:
         ws = Workspace(pivco_decode_workspace(streams, outs))
-    status = torch.zeros(max(len(streams), 1), dtype=torch.int32, device="cuda")
+    status = torch.empty(max(len(streams), 1), dtype=torch.int32, device="cuda")   # the call writes them all
     name = "pivco_decode_plain" if plain else entry
     _check(getattr(lib(), name)(jobs, len(streams), C.c_void_p(status.data_ptr()), ws.ptr, ws.nbytes,
                                 _stream()), name)
@@ -482,7 +482,7 @@ def pivco_golomb_decode(streams, outs=None):
     jobs = _jobs(streams, outs)
     wsb = int(lib().pivco_golomb_decode_workspace(jobs, len(streams), _stream()))
     ws = Workspace(wsb)
-    status = torch.zeros(max(len(streams), 1), dtype=torch.int32, device="cuda")
+    status = torch.empty(max(len(streams), 1), dtype=torch.int32, device="cuda")
     _check(lib().pivco_golomb_decode(jobs, len(streams), C.c_void_p(status.data_ptr()), ws.ptr,
                                      ws.nbytes, _stream()), "pivco_golomb_decode")
     return outs, status[:len(streams)].cpu().numpy()
