@@ -1032,6 +1032,11 @@ struct MergeSmem {
       uint32_t r0[256];    // resident: 1 bits of the body before the node
       uint32_t aend[256];  // resident: 1 bits of the body before the share's end
     };
+    struct {               // while a tile is loaded
+      uint64_t tq[256];    // node with staged chunks (in node order): source byte of its first
+                           // chunk less 16 times its slot | 1 when it lies in the scratch
+      uint64_t cmask[C::BODY / (16 * kWave) + 2];   // bit i of word w: a node's first chunk is 64 w + i
+    };
     struct {
       uint32_t tone[256];  // streaming: 1 bits in the tile share
       uint32_t ones[256];  // streaming: 1 bits seen so far
@@ -1123,14 +1128,33 @@ __device__ __forceinline__ uint32_t lds_win(const uint8_t *lds, uint32_t a) {
 }
 
 // Enters a node with work into its level's task windows: its record goes to
-// its slot, its first task sets a bit of the window start mask, and the
-// windows whose first task falls inside it point at its level slot.
+// its slot, and its first task sets a bit of the window start mask.
 template <class C>
-__device__ __forceinline__ void list_node(MergeSmem<C> &sm, uint32_t d, uint32_t ai, uint32_t gslot,
-                                          uint32_t tp, uint32_t nt, const NodeRec &r) {
+__device__ __forceinline__ void list_node(MergeSmem<C> &sm, uint32_t d, uint32_t gslot, uint32_t tp,
+                                          const NodeRec &r) {
   sm.rec[gslot] = r;
   atomicOr(reinterpret_cast<unsigned long long *>(&sm.smask[d][tp >> 6]), 1ull << (tp & 63));
-  for (uint32_t w = (tp + 63) >> 6; kWave * w < tp + nt; ++w) sm.wstart[d][w] = static_cast<uint8_t>(ai);
+}
+
+// Level slot of the node that holds each window's first task, run by one wave
+// (a window per lane) once the level's start masks are complete: the nodes
+// are in slot order, so it is the number of starts up to that task, less one.
+// (Written by the node instead, window by window, the root's 32 stores kept
+// every other node waiting: the lists took 3.9K cycles a tile, 3.6K now.)
+template <class C>
+__device__ __forceinline__ void window_starts(MergeSmem<C> &sm, uint32_t d) {
+  const uint32_t lane = lane_id();
+  static_assert(C::WIN <= 2 * kWave, "two windows a lane at most");
+  uint32_t carry = 0;
+#pragma unroll
+  for (uint32_t w0 = 0; w0 < static_cast<uint32_t>(C::WIN); w0 += kWave) {
+    const uint32_t w = w0 + lane;
+    const uint64_t m = w < static_cast<uint32_t>(C::WIN) ? sm.smask[d][w] : 0u;
+    const uint32_t n = static_cast<uint32_t>(__popcll(m)), inc = wave_incl_scan(n);
+    const uint32_t at = carry + inc - n + static_cast<uint32_t>(m & 1);   // starts up to the window's first task
+    if (w < static_cast<uint32_t>(C::WIN)) sm.wstart[d][w] = static_cast<uint8_t>(at ? at - 1 : 0u);
+    carry += static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(inc), kWave - 1));
+  }
 }
 
 // Exclusive prefix over the 64 lanes of a wave, and the wave total.
@@ -1214,7 +1238,7 @@ __device__ void count_level_streaming(MergeSmem<C> &sm, uint32_t d) {
         r.arank = fl ? flat_tag<C>(sm, t, v) : 0u;
         r.ot = sm.obase[v] | (tp << 16);
         r.kids = kids;
-        list_node<C>(sm, d, ai, act_base + ai, tp, tasks, r);
+        list_node<C>(sm, d, act_base + ai, tp, r);
       }
       sm.cur[v] += tvv;
     }
@@ -1223,6 +1247,7 @@ __device__ void count_level_streaming(MergeSmem<C> &sm, uint32_t d) {
     act_top += static_cast<uint32_t>(tot >> 48);
     wave_sync_lds();
   }
+  window_starts<C>(sm, d);
   if (lane == 0) {
     sm.ntask[d] = task_top + (FLAT ? flat_pad(ftask) : 0u);
     sm.nftask[d] = ftask;
@@ -1347,8 +1372,7 @@ __device__ void tile_lists(MergeSmem<C> &sm) {
       r.arank = fdv ? flat_tag<C>(sm, t, v) : sm.arank[v];
       r.ot = static_cast<uint32_t>(rel) | (tp << 16);
       r.kids = kids;
-      list_node<C>(sm, d, static_cast<uint32_t>(rel >> 48), static_cast<uint32_t>(pfx[v] >> 48), tp,
-                   (tvv + C::K - 1) / C::K, r);
+      list_node<C>(sm, d, static_cast<uint32_t>(pfx[v] >> 48), tp, r);
     }
     sm.cur[v] += tvv;
     sm.arank[v] = sm.aend[v];
@@ -1365,6 +1389,8 @@ __device__ void tile_lists(MergeSmem<C> &sm) {
     }
     sm.actbase[tid] = static_cast<uint32_t>(pfx[h.lvl[tid]] >> 48);
   }
+  lds_barrier();
+  for (uint32_t d = wave; d < h.maxlen; d += C::NW) window_starts<C>(sm, d);
   lds_barrier();
 }
 
@@ -1827,28 +1853,35 @@ __device__ void build_directory(MergeSmem<C> &sm, uint32_t body_dw, uint32_t I, 
   const uint32_t wave = wave_id();
   const uint32_t lane = lane_id();
   const uint32_t nsb = (body_dw + 7) / 8 + 1;
-  const uint32_t per = (nsb + C::NT - 1) / C::NT;
-  const uint32_t s0 = tid * per;
-  uint32_t loc = 0;
-  for (uint32_t k = s0; k < s0 + per && k < nsb; ++k) {
-    const uint4 a = *reinterpret_cast<const uint4 *>(&sm.body[8 * k]);
-    const uint4 c = *reinterpret_cast<const uint4 *>(&sm.body[8 * k + 4]);
-    const uint32_t w0 = __popc(a.x) + __popc(a.y), w1 = __popc(a.z) + __popc(a.w);
-    const uint32_t w2 = __popc(c.x) + __popc(c.y), w3 = __popc(c.z) + __popc(c.w);
-    *reinterpret_cast<uint32_t *>(&sm.rel[4 * k]) = (w0 << 8) | ((w0 + w1) << 16) | ((w0 + w1 + w2) << 24);
-    const uint32_t cnt = w0 + w1 + w2 + w3;
-    sm.sup[k] = cnt;
-    loc += cnt;
+  // a wave has PER consecutive rows of 64 superblocks, one a lane
+  constexpr uint32_t PER = (C::BODY / 32 + 1 + C::NT - 1) / C::NT;
+  const uint32_t s0 = wave * (PER * kWave) + lane;
+  uint32_t cnt[PER], ex[PER], loc = 0;
+#pragma unroll
+  for (uint32_t j = 0; j < PER; ++j) {
+    const uint32_t k = s0 + kWave * j;
+    cnt[j] = 0;
+    if (k < nsb) {
+      const uint4 a = *reinterpret_cast<const uint4 *>(&sm.body[8 * k]);
+      const uint4 c = *reinterpret_cast<const uint4 *>(&sm.body[8 * k + 4]);
+      const uint32_t w0 = __popc(a.x) + __popc(a.y), w1 = __popc(a.z) + __popc(a.w);
+      const uint32_t w2 = __popc(c.x) + __popc(c.y), w3 = __popc(c.z) + __popc(c.w);
+      *reinterpret_cast<uint32_t *>(&sm.rel[4 * k]) = (w0 << 8) | ((w0 + w1) << 16) | ((w0 + w1 + w2) << 24);
+      cnt[j] = w0 + w1 + w2 + w3;
+    }
   }
-  const uint32_t inc = wave_incl_scan(loc);
-  if (lane == kWave - 1) sm.scan_tot[wave] = inc;
+#pragma unroll
+  for (uint32_t j = 0; j < PER; ++j) {
+    const uint32_t inc = wave_incl_scan(cnt[j]);
+    ex[j] = loc + inc - cnt[j];
+    loc += static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(inc), kWave - 1));
+  }
+  if (lane == 0) sm.scan_tot[wave] = loc;
   lds_barrier();
-  uint32_t run = inc - loc + sum_first(sm.scan_tot, wave);
-  for (uint32_t k = s0; k < s0 + per && k < nsb; ++k) {
-    const uint32_t c = sm.sup[k];
-    sm.sup[k] = run;
-    run += c;
-  }
+  const uint32_t run = sum_first(sm.scan_tot, wave);
+#pragma unroll
+  for (uint32_t j = 0; j < PER; ++j)
+    if (s0 + kWave * j < nsb) sm.sup[s0 + kWave * j] = run + ex[j];
   lds_barrier();
   for (uint32_t i = tid; i < I; i += C::NT) {
     const uint32_t r = rank_at(sm.body, sm.sup, sm.rel, sm.abit[i]);
@@ -2016,6 +2049,9 @@ __device__ void load_tile(const JobDev &J, const ParsedBlock *rec, const uint2 *
   for (uint32_t base = kWave * wave; base < kRec16; base += kWave * C::NW)
     if (base + lane < kRec16)
       __builtin_amdgcn_global_load_lds(rb + 16ull * (base + lane), &pbw[4 * base], 16, 0, 0);
+  constexpr uint32_t CW = C::BODY / (16 * kWave) + 2;
+  static_assert(CW <= kWave, "a lane per word of the chunk start mask");
+  if (static_cast<uint32_t>(tid) < CW) sm.cmask[tid] = 0;
   for (uint32_t v = tid; v < kTabCols; v += C::NT) {
     const uint32_t a = tab[static_cast<uint64_t>(k) * kTabCols + v].x;
     const uint32_t b = tab[static_cast<uint64_t>(k + 1) * kTabCols + v].x;
@@ -2042,17 +2078,19 @@ __device__ void load_tile(const JobDev &J, const ParsedBlock *rec, const uint2 *
     const uint64_t b16 = (((gb + static_cast<uint64_t>(dv) * sm.tv[tid] + 7) >> 3) + 15) & ~15ull;
     nch = static_cast<uint32_t>((b16 - a16) >> 4);
   }
-  const uint32_t inc = tid < 256 ? wave_incl_scan(nch) : 0u;
+  const uint32_t pk = nch | (nch ? 0x10000u : 0u);          // chunks, nodes with chunks
+  const uint32_t inc = tid < 256 ? wave_incl_scan(pk) : 0u;
   if (tid < 256 && lane == kWave - 1) sm.scan_tot[wave] = inc;
   lds_barrier();
-  const uint32_t before = tid < 256 ? sum_first(sm.scan_tot, static_cast<uint32_t>(wave)) : 0u;
-  if (static_cast<uint32_t>(tid) < I) {
-    sm.stg[tid] = inc - nch + before;   // first staged chunk of the node
-    sm.ones[tid] = nch;                 // its chunks
-  }
+  const uint32_t before = tid < 256 ? sum_first(sm.scan_tot, static_cast<uint32_t>(wave)) + inc - pk : 0u;
+  const uint32_t stg = before & 0xFFFF;                       // first staged chunk of the node
   if (wave == 0) {
     const uint32_t tot = sum_first(sm.scan_tot, 4);
-    if (tid == 0) sm.stage_top = tot;
+    if (tid == 0) sm.stage_top = tot & 0xFFFF;
+  }
+  if (nch && 16ull * (stg + nch) + 64 <= static_cast<uint64_t>(C::BODY)) {
+    sm.tq[before >> 16] = (a16 - 16ull * stg) | t.kind[tid];
+    atomicOr(reinterpret_cast<unsigned long long *>(&sm.cmask[stg >> 6]), 1ull << (stg & 63));
   }
   lds_barrier();
   const uint32_t total = sm.stage_top;
@@ -2061,35 +2099,36 @@ __device__ void load_tile(const JobDev &J, const ParsedBlock *rec, const uint2 *
     lds_barrier();
     return;
   }
-  // copy: the staged chunks in order, C::NT per step.  Staged chunk s (of
-  // node v, stg[v] <= s < stg[v] + ones[v]) goes to LDS slot s, so a wave's
-  // 64 lanes fill 64 consecutive slots with one direct-to-LDS load, each lane
-  // gathering from its own node's range; chunks not wholly inside their
-  // buffer take guarded byte loads afterwards.  Every source address is
-  // computed (LDS reads) before the first load is issued: a direct-to-LDS
-  // load writes LDS, so an LDS or global read issued after it waits for
-  // every such load in flight.
+  // copy: the staged chunks in order, C::NT per step.  Staged chunk s goes to
+  // LDS slot s, so a wave's 64 lanes fill 64 consecutive slots with one
+  // direct-to-LDS load, each lane gathering from its own node's range; chunks
+  // not wholly inside their buffer take guarded byte loads afterwards.  A
+  // chunk's node is the number of node starts up to it: those before the
+  // wave's 64 chunks (one scan of the start mask's words) and those of them up
+  // to the lane's.  (A search over the nodes' first chunks, and their address
+  // from five tables: 2.8K cycles a tile, 0.9K now.)  Every source address is
+  // computed (LDS reads) before the first load is issued: a direct-to-LDS load
+  // writes LDS, so an LDS or global read issued after it waits for every such
+  // load in flight.
   constexpr uint32_t KS = (C::BODY / 16 + C::NT - 1) / C::NT;
   for (uint32_t i = 4 * total + tid; i < 4 * total + 16; i += C::NT) sm.body[i] = 0u;   // not a load target
   uint64_t qa[KS];          // source byte offset of the lane's chunk at each step
   uint32_t inb = 0, scr = 0;  // bit k: step k's chunk lies inside its buffer / comes from scratch
+  const uint64_t upto = (2ull << lane) - 1;
+  const uint32_t starts = lane < CW ? static_cast<uint32_t>(__popcll(sm.cmask[lane])) : 0u;
+  const uint32_t starts_ex = wave_incl_scan(starts) - starts;
 #pragma unroll
   for (uint32_t k = 0; k < KS; ++k) {
-    const uint32_t sc = k * C::NT + static_cast<uint32_t>(tid);
+    const uint32_t w = k * C::NW + static_cast<uint32_t>(wave), sc = kWave * w + lane;
     qa[k] = 0;
-    if (sc < total) {
-      uint32_t lo = 0, hi = I;                  // the last node whose chunks start at or before sc
-      while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (sm.stg[mid] <= sc) lo = mid; else hi = mid;
-      }
-      const uint32_t v = lo;
-      const bool kind = t.kind[v] != 0;
-      const uint64_t g = (kind ? 32ull * (h.ans_word0 + t.boff[v]) : 8ull * (h.blk + t.boff[v])) +
-                         static_cast<uint64_t>(t.fd[v] ? t.fd[v] : 1u) * sm.cur[v];
-      const uint64_t q = ((g >> 3) & ~15ull) + 16ull * (sc - sm.stg[v]);
+    if (kWave * w < total) {                   // the same for the whole wave
+      const uint32_t node = __builtin_amdgcn_readlane(starts_ex, w) +
+                            static_cast<uint32_t>(__popcll(sm.cmask[w] & upto)) - 1;
+      const uint64_t e = sm.tq[node & 255];
+      const uint64_t q = (e & ~1ull) + 16ull * sc;
+      const bool kind = e & 1;
       qa[k] = q;
-      if (q + 16 <= (kind ? 4ull * scratch_words : jlen)) inb |= 1u << k;
+      if (sc < total && q + 16 <= (kind ? 4ull * scratch_words : jlen)) inb |= 1u << k;
       if (kind) scr |= 1u << k;
     }
   }
@@ -2122,11 +2161,10 @@ __device__ void load_tile(const JobDev &J, const ParsedBlock *rec, const uint2 *
   }
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  // LDS bit address of each share's first bit (abit shares its words with
-  // tone, not with stg or ones); read after the rank directory's first
-  // barrier
+  // LDS bit address of each share's first bit; read after the rank
+  // directory's first barrier
   if (static_cast<uint32_t>(tid) < I)
-    sm.abit[tid] = sm.tv[tid] ? 128u * sm.stg[tid] + static_cast<uint32_t>(gb - 8 * a16) : 0u;
+    sm.abit[tid] = sm.tv[tid] ? 128u * stg + static_cast<uint32_t>(gb - 8 * a16) : 0u;
 }
 
 // Persistent merge: a workgroup takes items from the queue (largest first) --
