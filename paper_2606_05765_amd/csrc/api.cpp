@@ -96,6 +96,7 @@ struct HostPlan {
   uint64_t scratch_words = 0;
   uint64_t chunk_cap = 0;      // entropy-coded chunk list capacity (bound over the jobs)
   uint32_t coders = 0;         // bit 0: some job has rANS nodes; bit 1: tANS nodes
+  bool skewed = false;         // at least half of the symbols are in skewed jobs
   std::vector<uint8_t> lists;  // the lists as they lie in the workspace, from off_jobs to off_recs
   // workspace layout (byte offsets)
   uint64_t off_ctr = 0, off_jobs = 0, off_blocks = 0, off_items = 0, off_ritems = 0,
@@ -177,7 +178,7 @@ pivco_status build_plan(const pivco_job *h_jobs, uint32_t count, const std::vect
   uint64_t sw = 0;
   std::vector<StreamHdr> hs(count);
   std::vector<pivco_status> sts(count);
-  uint64_t batch_symbols = 0;
+  uint64_t batch_symbols = 0, skewed_symbols = 0;
   for (uint32_t j = 0; j < count; ++j) {
     const pivco_job &jb = h_jobs[j];
     StreamHdr &sh = hs[j];
@@ -212,9 +213,11 @@ pivco_status build_plan(const pivco_job *h_jobs, uint32_t count, const std::vect
     d.ans_words = sh.ans_words;
     sw = align_up(sw + sh.ans_words, 4);
     p.chunk_cap += rans_chunk_bound(sh.ans_words, sh.n_blocks, sh.chunk_log2);
-    p.w.add_job(j, sh.n_total, sh.n_blocks, sh.block_size, sh.ans_words != 0,
-                split_threshold(jb.in_len, sh.ans_words, sh.n_blocks, batch_symbols, device_cus()));
+    const uint64_t split_min = split_threshold(jb.in_len, sh.ans_words, sh.n_blocks, batch_symbols, device_cus());
+    p.w.add_job(j, sh.n_total, sh.n_blocks, sh.block_size, sh.ans_words != 0, split_min);
+    if (skewed_job(sh.n_total, jb.in_len, sh.ans_words, sh.block_size, split_min)) skewed_symbols += sh.n_total;
   }
+  p.skewed = skewed_symbols && 2 * skewed_symbols >= batch_symbols;
   p.w.finish();
   if (p.w.items.size() > 0xFFFFFFF0ull || p.w.blocks.size() > 0xFFFFFFF0ull) return PIVCO_E_UNSUPPORTED;
   if ((p.coders & 2) && !fse_tables()) return PIVCO_E_DEVICE;   // tables on this device, before any launch
@@ -321,7 +324,7 @@ pivco_status enqueue_batch(const HostPlan &p, void *d_ws, int32_t *d_status, con
   const uint32_t ni = static_cast<uint32_t>(w.items.size());
   if (ni && launch_merge(t.merge_variant, t.grid_mode ? ni : t.merge_grid, s, d.jobs, d.items, d.recs,
                          d.tiled, d.tab, ni, d.ctr, d.scratch, p.scratch_words,
-                         t.grid_mode ? kGridItems : kQueueItems) != hipSuccess)
+                         t.grid_mode ? kGridItems : kQueueItems, p.skewed) != hipSuccess)
     return PIVCO_E_DEVICE;
   if (ev1 && hipEventRecord(ev1, s) != hipSuccess) return PIVCO_E_DEVICE;
   return PIVCO_OK;
@@ -494,7 +497,7 @@ pivco_status pivco_decode_plain(const pivco_job *h_jobs, uint32_t count, int32_t
   for (uint32_t i : idx)
     if (launch_merge(0, 1, s, d.jobs, d.items, d.recs, d.tiled, d.tab,
                      static_cast<uint32_t>(w.items.size()), d.ctr, d.scratch, p.scratch_words,
-                     static_cast<int32_t>(i)) != hipSuccess)
+                     static_cast<int32_t>(i), p.skewed) != hipSuccess)
       return PIVCO_E_DEVICE;
   return PIVCO_OK;
 }

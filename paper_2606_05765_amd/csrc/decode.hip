@@ -141,7 +141,8 @@ struct BlockHdr {
   uint8_t nfl[18];         // per level: flat nodes (the level's first nodes)
   uint64_t lvl_total[17];  // bits staged per level (sum of n_v D); set by the merge kernel for streamed blocks
   uint32_t nflat;          // flat nodes of the block (0: binary nodes only)
-  uint32_t pad2;           // the node tables start at a multiple of 16 bytes
+  uint32_t below;          // symbols below the root (of its internal children); the node tables
+                           // start at a multiple of 16 bytes
 };
 static_assert(offsetof(BlockHdr, job) == offsetof(BlockExt, job) && sizeof(BlockExt) == 48, "BlockExt prefix");
 
@@ -520,6 +521,8 @@ __device__ void parse_block_wave(const JobDev &J, uint32_t b, BlockHdr &h, NodeT
     err = __shfl(err, src, kWave);
   }
   if (lane == 0) {
+    const uint32_t c0 = t.child[0][0], c1 = t.child[0][1];
+    h.below = ((c0 & 0x8000) ? 0u : t.nv[c0]) + ((c1 & 0x8000) ? 0u : t.nv[c1]);
     h.raw_end = raw_end > 0xFFFFFFFFull ? 0xFFFFFFFFu : static_cast<uint32_t>(raw_end);
     h.n_ans = n_ans;
     h.err = err;
@@ -988,13 +991,14 @@ __global__ __launch_bounds__(kFseNT) void k_fse(const JobDev *jobs, const Parsed
 // ---------------------------------------------------------------------------
 // Kernel: bottom-up merge decode
 // ---------------------------------------------------------------------------
-template <int NT_, int T_, int BODY_, int K_, int LOCK_>
+template <int NT_, int T_, int BODY_, int K_, int LOCK_, bool ONCE_ = false>
 struct MergeCfg {
   static constexpr int NT = NT_;
   static constexpr int T = T_;                        // output symbols per tile
   static constexpr int BODY = BODY_;                  // resident block bytes
   static constexpr int K = K_;                        // outputs per merge task (8, 16 or 32)
   static constexpr int LOCK = LOCK_;                  // windows a wave merges at once (1, 2 or 4)
+  static constexpr bool ONCE = ONCE_;                 // levels below a skewed root once per block (below_root_fits)
   static_assert(LOCK == 1 || LOCK == 2 || LOCK == 4, "windows per wave step");
   static constexpr int NW = NT / kWave;
   static constexpr int LVL = T + (K - 1) * 128 + 64;  // bytes per level buffer (shares rounded to K)
@@ -1675,6 +1679,72 @@ __device__ __forceinline__ void merge_tile(MergeSmem<C> &sm, int maxd, uint8_t *
   merge_level<C, RESIDENT, true, FLAT>(sm, 0, out);
 }
 
+// A whole block of more than one tile whose root keeps all but at most C::T of
+// its symbols in a leaf (very skewed sources): the levels below the root hold
+// the whole block at once, so they are merged once instead of once per tile
+// and only the root runs over the block, one span of it per wave and no
+// barrier, task lists or shares.  The levels' cost is their latency, 1.2K cycles
+// each however narrow: 128 KiB blocks with one symbol at 0.9 took 112K cycles
+// a block in 4 tiles, 50K of them in the 10 levels below the root; 41K now.
+template <class C>
+__device__ __forceinline__ bool below_root_fits(const BlockHdr &h) {
+  return h.n > static_cast<uint32_t>(C::T) && h.below <= static_cast<uint32_t>(C::T) && h.maxlen >= 2;
+}
+
+// The root of such a block over all its outputs, its children's sequences
+// complete in level buffer 1: windows of 64 tasks, wave by wave.
+template <class C>
+__device__ void merge_root_block(MergeSmem<C> &sm, uint32_t n, uint8_t *out) {
+  const uint32_t lane = item_tid() & (kWave - 1);
+  const NodeTab &t = sm.pb.t;
+  constexpr int G = C::K / 4;
+  const uint8_t *lds = reinterpret_cast<const uint8_t *>(&sm);
+  // the children: a leaf's constant row (rank times 0), or the sequence in
+  // the level buffer (the second node's after the first, rounded up)
+  uint32_t base[2], mul[2], off = 0;
+#pragma unroll
+  for (int bb = 0; bb < 2; ++bb) {
+    const uint32_t c = t.child[0][bb];
+    mul[bb] = (c & 0x8000) ? 0u : 1u;
+    base[bb] = static_cast<uint32_t>((c & 0x8000) ? reinterpret_cast<const uint8_t *>(&sm.leafrow[c & 255]) - lds
+                                                  : reinterpret_cast<const uint8_t *>(sm.lvl[1]) - lds + off);
+    if (!(c & 0x8000)) off += (t.nv[c] + C::K - 1) & ~(C::K - 1u);
+  }
+  const uint32_t x0 = sm.abit[0], a0 = sm.r0[0];
+  const uint32_t ntask = (n + C::K - 1) / C::K, nwin = (ntask + kWave - 1) / kWave;
+  for (uint32_t w = wave_id(); w < nwin; w += C::NW) {
+    const uint32_t j = C::K * (kWave * w + lane), jc = j < n ? j : 0u;
+    const uint32_t x = x0 + jc, bits = bits32_lds(sm.body, x);
+    uint32_t r1 = rank_at(sm.body, sm.sup, sm.rel, x) - a0, r0 = jc - r1;
+    uint32_t aL[G], aR[G], sel[G], o[G];
+    uint2 wl[G], wr[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const uint32_t m = (bits >> (4 * g)) & 15, pc = __popc(m);
+      aL[g] = base[0] + __umul24(mul[0], r0);
+      aR[g] = base[1] + __umul24(mul[1], r1);
+      sel[g] = m;
+      r1 += pc;
+      r0 += 4 - pc;
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const uint32_t *ql = reinterpret_cast<const uint32_t *>(lds + (aL[g] & ~3u));
+      const uint32_t *qr = reinterpret_cast<const uint32_t *>(lds + (aR[g] & ~3u));
+      wl[g] = make_uint2(ql[0], ql[1]);
+      wr[g] = make_uint2(qr[0], qr[1]);
+      sel[g] = sm.sel[sel[g]];
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const uint32_t l4 = __builtin_amdgcn_alignbyte(wl[g].y, wl[g].x, aL[g]);
+      const uint32_t r4 = __builtin_amdgcn_alignbyte(wr[g].y, wr[g].x, aR[g]);
+      o[g] = __builtin_amdgcn_perm(r4, l4, sel[g]);
+    }
+    if (j < n) store_task<C, true>(sm, 0, 0u, j, o, n, out);
+  }
+}
+
 // The block's extent and owner from the first 48 bytes of its record.
 __device__ __forceinline__ BlockExt load_ext(const ParsedBlock *rec) {
   const uint4 *p = reinterpret_cast<const uint4 *>(rec);
@@ -1964,15 +2034,16 @@ __device__ void decode_block(const JobDev &J, const BlockExt &ext, uint32_t k,
     if (resident) build_directory<C>(sm, static_cast<uint32_t>(span >> 2) + h.ans_words, I, n == 0);
     else lds_barrier();
   }
-  const uint32_t T = sm.tile;
   const uint32_t maxd = h.maxlen;        // internal levels are 0 .. maxd-1
   const bool flat = h.nflat != 0;
   bool bad = false;
 
   publish_next<C>(sm, la);            // visible after the next barrier
+  const bool once = C::ONCE && resident && !tiled && below_root_fits<C>(h);
   // a split block's tile is one pass whose shares are known: the task lists'
   // first barrier orders the rank directory's last writes before their
   // readers, and the root's share already is troot
+  const uint32_t T = once ? n : sm.tile;
   const bool one_tile = tiled && C::T >= static_cast<int>(kTileOut);
   for (uint32_t t0 = 0; t0 < n; t0 += T) {
     const uint32_t troot = n - t0 < T ? n - t0 : T;
@@ -1989,6 +2060,13 @@ __device__ void decode_block(const JobDev &J, const BlockExt &ext, uint32_t k,
           else if (wave == 1 && t0 == 0) warm_next<C>(sm);
         } else {
           count_last<C>(sm);
+          if (once && tid == 0) {
+            // the nodes below the root whole, no task for the root; its 1 bits
+            // must be its right child's symbols, else its ranks would leave
+            // their sequence
+            sm.tv[0] = 0;
+            if (sm.aend[0] - sm.r0[0] != t.nr[0]) atomicCAS(&h.err, 0, static_cast<int32_t>(PIVCO_E_CORRUPT));
+          }
         }
         lds_barrier();
       }
@@ -2014,10 +2092,16 @@ __device__ void decode_block(const JobDev &J, const BlockExt &ext, uint32_t k,
       if (flat) merge_tile<C, false, true>(sm, static_cast<int>(maxd), out + t0, !tiled);
       else merge_tile<C, false, false>(sm, static_cast<int>(maxd), out + t0, !tiled);
     }
+
     if (!resident) {
       for (uint32_t i = tid; i < I; i += C::NT) sm.tv[i] = 0;
       lds_barrier();
     }
+  }
+  if (once && !bad) {
+    if (wave == C::NW - 1) warm_next<C>(sm);
+    merge_root_block<C>(sm, n, out);
+    if (tid == 0) sm.cur[0] = n;       // its rank is at its end already
   }
   if (!bad && !tiled) {
     for (uint32_t i = tid; i < I; i += C::NT) {
@@ -2168,7 +2252,10 @@ __device__ void load_tile(const JobDev &J, const ParsedBlock *rec, const uint2 *
 }
 
 // Persistent merge: a workgroup takes items from the queue (largest first) --
-// whole blocks, or tiles of split blocks -- looking one item ahead.  `single`
+// whole blocks, or tiles of split blocks -- looking one item ahead.
+// C::ONCE: blocks that below_root_fits are merged that way; a kernel of its own,
+// for batches of them, since the path costs other blocks 4% (574 against 595
+// us a 256 MiB Zipf v2 batch with no such block in it).  `single`
 // selects the item source: kQueueItems (the persistent queue), kGridItems
 // (workgroup b decodes item b and exits: one non-persistent launch with a
 // workgroup per item), or an item index (one item, one workgroup).
@@ -2851,6 +2938,7 @@ __global__ __launch_bounds__(kTdNT) void k_topdown(const JobDev *jobs, const uin
 // Merge-kernel variants: workgroup size, tile of a whole block, resident
 // block bytes, outputs per task, windows per wave step.
 using Cfg0 = MergeCfg<1024, 32768, 57344, 16, 2>;
+using Cfg0Once = MergeCfg<1024, 32768, 57344, 16, 2, true>;   // variant 0 for skewed batches
 using Cfg1 = MergeCfg<1024, 32768, 56320, 8, 2>;
 using Cfg2 = MergeCfg<1024, 32768, 55296, 32, 1>;
 using Cfg3 = MergeCfg<1024, 16384, 57344, 16, 2>;
@@ -2912,10 +3000,12 @@ hipError_t launch_merge(uint32_t variant, uint32_t grid, hipStream_t s, const Jo
                         const uint2 *items, const void *recs,
                         const TiledBlock *tiled, const uint2 *tab, uint32_t n_items,
                         Counters *ctr, const uint32_t *scratch, uint64_t scratch_words,
-                        int32_t single) {
+                        int32_t single, bool skewed) {
   const ParsedBlock *r = static_cast<const ParsedBlock *>(recs);
   switch (variant) {
-    case 0: return launch_merge_t<Cfg0>(dim3(grid), s, jobs, items, r, tiled, tab, n_items, ctr, scratch, scratch_words, single);
+    case 0:
+      if (skewed) return launch_merge_t<Cfg0Once>(dim3(grid), s, jobs, items, r, tiled, tab, n_items, ctr, scratch, scratch_words, single);
+      return launch_merge_t<Cfg0>(dim3(grid), s, jobs, items, r, tiled, tab, n_items, ctr, scratch, scratch_words, single);
     case 1: return launch_merge_t<Cfg1>(dim3(grid), s, jobs, items, r, tiled, tab, n_items, ctr, scratch, scratch_words, single);
     case 2: return launch_merge_t<Cfg2>(dim3(grid), s, jobs, items, r, tiled, tab, n_items, ctr, scratch, scratch_words, single);
     case 3: return launch_merge_t<Cfg3>(dim3(grid), s, jobs, items, r, tiled, tab, n_items, ctr, scratch, scratch_words, single);

@@ -379,7 +379,7 @@ pivco_status pivco_server_run(pivco_server *sv, const pivco_request *reqs, uint3
         return PIVCO_E_DEVICE;
       if (ni && launch_merge(variant, std::max<uint32_t>(1, std::min(mgrid_full, ni)), s.stream, dj,
                              reinterpret_cast<const uint2 *>(s.ws + o_items), recs,
-                             d_tiled, d_tab, ni, ctr, scr, sw, -1) != hipSuccess)
+                             d_tiled, d_tab, ni, ctr, scr, sw, -1, false) != hipSuccess)
         return PIVCO_E_DEVICE;
       if (hipMemcpyAsync(s.pinned + sv->off_pstatus, s.ws + sv->off_status, 4 * batch.size(),
                          hipMemcpyDeviceToHost, s.stream) != hipSuccess)
