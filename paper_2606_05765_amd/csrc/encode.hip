@@ -375,97 +375,158 @@ __device__ __forceinline__ uint64_t rbm_area(const BlockLay &L) { return (static
 // id, packages in creation order; the multiset of lengths handed out again
 // ascending to the symbols by (count desc, id asc)), in parallel form:
 //   * the present symbols are ranked by (count, id) by counting over all 256
-//     keys (a broadcast LDS read each);
+//     counts (broadcast LDS reads);
 //   * row L holds the m singles in that order; row r - 1 merges the singles
 //     with the packages (sums of consecutive pairs) of row r: single i lands
 //     at i + #(packages lighter than it), package j at j + #(singles no
-//     heavier), both by binary search, and positions past 2m - 2 are dropped.
+//     heavier), and positions past 2m - 2 are dropped.
 //     Each row keeps the positions of its singles;
 //   * buying the first k = 2m - 2 items of row 1 buys the singles placed
 //     below k and 2 (k - singles) items of the next row, and so on; single i
 //     is as deep as the rows that bought more than i singles, so the depths
 //     fall with i and the symbol that is the j-th by (count desc, id asc) gets
 //     the depth of single m - 1 - j.
-// A row costs two barriers and one round of searches (9 dependent LDS reads):
-// its latency, not work, is the kernel's time.  One block of 64 KiB: 24 us
-// with the layout, where one wave per block took 100 + 6; 4096 blocks 87 us,
-// was 312 + 22.  W is the weights' type: a
-// package's weight is at most the code length limit times the block's size,
-// and a key is a count and 8 bits of id, so 32 bits hold both below 2^24 symbols.
+// The rows are a chain, so their latency, not work, is the kernel's time.  A
+// count over a sorted row of 256 is 16 comparisons with the last item of each
+// 16 and 16 more within one: two round trips to LDS where a binary search took
+// 9 (2450 -> 1270 cycles a row, the ranking 8300 -> 4500).  With few blocks a
+// second half of the workgroup takes the packages and half the ranking; with
+// more than two blocks a CU, work counts too and 256 threads do it all.  One
+// block of 64 KiB: 17 us with the layout (24 with 256 threads and binary
+// searches; one wave per block took 100 + 6); 4096 blocks 99 us with 256
+// threads, 112 with 512, was 312 + 22.  W is the weights' type: a package's
+// weight is at most the code length limit times the block's size, which for
+// blocks below 2^24 symbols is below 2^28.
+constexpr uint32_t kFewBlocks = 512;
 constexpr uint32_t kTreeRows = kMaxLenGpu + 1;
 struct TreeSmem {
-  uint64_t key[256];          // (count << 8 | symbol); all ones for an absent symbol
-  uint64_t w[256];            // counts in (count, id) order
-  uint64_t row[2][512];       // item weights of two rows
-  uint64_t pk[256];           // packages of the row below
-  uint16_t spos[kTreeRows][256];   // row r: position of single i (0xFFFF: not in the row)
+  alignas(16) uint64_t w[256];     // counts in (count, id) order, the largest value past the last
+  alignas(16) uint64_t row[2][512];   // item weights of two rows
+  alignas(16) uint64_t pk[256];    // packages of the row below, the largest value past the last
+  alignas(16) uint64_t wl[16], pl[16];   // the last of each 16 of w and of pk
+  alignas(16) uint32_t cnt[256];   // counts by symbol
+  uint16_t rank[256];              // symbols of the upper half's share ranked before this one
+  alignas(16) uint16_t spos[kTreeRows][256];   // row r: position of single i (0xFFFF: not in the row)
 };
 
+// a < b as 0 or 1 for values below 2^31: the sign of the difference, as a
+// comparison's mask may only be read two wait states after it is made.
 template <class W>
-__device__ uint32_t tree_lengths(TreeSmem &sm, uint32_t c, uint32_t m, uint32_t L, bool *bad) {
-  const uint32_t t = threadIdx.x, lane = __lane_id();
-  W *key = reinterpret_cast<W *>(sm.key), *w = reinterpret_cast<W *>(sm.w), *pk = reinterpret_cast<W *>(sm.pk);
+__device__ __forceinline__ uint32_t less(W a, W b) {
+  if (sizeof(W) == 4) return static_cast<uint32_t>(a - b) >> 31;
+  return a < b ? 1u : 0u;
+}
+
+// The number of items of a sorted row of 256 (absent items: the largest
+// value) that are less than x; pv: the last item of each run of 16.
+template <class W>
+__device__ __forceinline__ uint32_t row_count(const W *row, const W *pv, W x) {
+  uint32_t g = 0, k = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < 16; ++i) g += less<W>(pv[i], x);
+  g = 16 * (g < 15 ? g : 15u);
+#pragma unroll
+  for (uint32_t i = 0; i < 16; ++i) k += less<W>(row[g + i], x);
+  return g + k;
+}
+
+// A thread per symbol, single and package, or with NT = 512 two, u = thread &
+// 255: the upper half takes half the ranking and the packages.  The length of
+// symbol u for the threads below 256.
+template <uint32_t NT, class W>
+__device__ uint32_t tree_lengths(TreeSmem &sm, uint32_t m, uint32_t L, bool *bad) {
+  const uint32_t u = threadIdx.x & 255, lane = __lane_id();
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool upper = NT == 256 || wave >= 4, lower = NT == 256 || wave < 4;
+  W *w = reinterpret_cast<W *>(sm.w), *pk = reinterpret_cast<W *>(sm.pk);
+  W *wl = reinterpret_cast<W *>(sm.wl), *pl = reinterpret_cast<W *>(sm.pl);
   W *row[2] = {reinterpret_cast<W *>(sm.row[0]), reinterpret_cast<W *>(sm.row[1])};
-  const W mine = (static_cast<W>(c) << 8) | t;
-  key[t] = c ? mine : ~static_cast<W>(0);
-  __syncthreads();
+  const W none = ~static_cast<W>(0) >> 1;
+  // rank by (count, id): a smaller id goes first on the same count.  The
+  // absent symbols, all lighter, are taken off again.
+  const uint32_t c = sm.cnt[u];
   uint32_t rank = 0;
+#pragma unroll 1
+  for (uint32_t q = lower ? 0 : 2, e = upper ? 4 : 2; q < e; ++q) {
+    const uint32_t *v = sm.cnt + 64 * q;
+    if (q == (wave & 3)) {
 #pragma unroll 16
-  for (uint32_t i = 0; i < 256; ++i) rank += key[i] < mine ? 1u : 0u;
-  if (c) {
-    w[rank] = c;
-    row[L & 1][rank] = c;
+      for (uint32_t i = 0; i < 64; ++i) rank += less<uint32_t>(v[i], c + less<uint32_t>(i, lane));
+    } else {
+      const uint32_t x = c + (q < (wave & 3) ? 1u : 0u);
+#pragma unroll 16
+      for (uint32_t i = 0; i < 64; ++i) rank += less<uint32_t>(v[i], x);
+    }
   }
-  sm.spos[L][t] = t < m ? static_cast<uint16_t>(t) : 0xFFFFu;
+  if (!lower) sm.rank[u] = static_cast<uint16_t>(rank);
+  __syncthreads();
+  if (lower) {
+    rank += (NT == 256 ? 0u : sm.rank[u]) - (256 - m);
+    if (c) {
+      w[rank] = c;
+      row[L & 1][rank] = c;
+      if ((rank & 15) == 15) wl[rank >> 4] = c;
+    }
+    if (u >= m) {
+      w[u] = none;
+      if ((u & 15) == 15) wl[u >> 4] = none;
+    }
+    sm.spos[L][u] = u < m ? static_cast<uint16_t>(u) : 0xFFFFu;
+  }
   const uint32_t cap = 2 * m - 2;
   uint32_t rl = m, rl_l = m;               // items of row r; lane r keeps its row's
   __syncthreads();
-  const W x = w[t < m ? t : 0u];           // single t
+  const W x = w[u];                        // single u
   // this symbol's run of equal counts: [lt, le)
   uint32_t lt = 0, le = 0;
-#pragma unroll
-  for (uint32_t st = 256; st; st >>= 1) {
-    const uint32_t a = lt + st, b = le + st;
-    const W wa = w[a <= m ? a - 1 : 0u], wb = w[b <= m ? b - 1 : 0u];
-    lt = a <= m && wa < c ? a : lt;
-    le = b <= m && wb <= c ? b : le;
+#pragma unroll 1
+  for (uint32_t i = 0; i < 2; ++i) {
+    lt = le;
+    le = row_count<W>(w, wl, c + i);
   }
   for (uint32_t r = L; r > 1; --r) {
     const W *cur = row[r & 1];
     W *nxt = row[(r - 1) & 1];
     const uint32_t np = rl / 2;
-    W y = 0;
-    if (t < np) {
-      y = cur[2 * t] + cur[2 * t + 1];
-      pk[t] = y;
+    const uint32_t total = m + np < cap ? m + np : cap;
+    W y = none;
+    if (upper) {
+      if (u < np) y = cur[2 * u] + cur[2 * u + 1];
+      pk[u] = y;
+      if ((u & 15) == 15) pl[u >> 4] = y;
     }
     __syncthreads();
-    const uint32_t total = m + np < cap ? m + np : cap;
-    uint32_t lo = 0, hi = 0;               // packages lighter than single t; singles no heavier than package t
-#pragma unroll
-    for (uint32_t st = 256; st; st >>= 1) {
-      const uint32_t a = lo + st, b = hi + st;
-      const W pa = pk[a <= np ? a - 1 : 0u], wb = w[b <= m ? b - 1 : 0u];
-      lo = a <= np && pa < x ? a : lo;
-      hi = b <= m && wb <= y ? b : hi;
+    if (upper) {
+      const uint32_t at = u + row_count<W>(w, wl, y + 1);    // singles no heavier
+      if (u < np && at < total) nxt[at] = y;
     }
-    const uint32_t ps = t + lo, pp = t + hi;
-    if (t < m && ps < total) nxt[ps] = x;
-    if (t < np && pp < total) nxt[pp] = y;
-    sm.spos[r - 1][t] = t < m && ps < total ? static_cast<uint16_t>(ps) : 0xFFFFu;
+    if (lower) {
+      const uint32_t at = u + row_count<W>(pk, pl, x);   // packages lighter
+      const bool in = u < m && at < total;
+      if (in) nxt[at] = x;
+      sm.spos[r - 1][u] = in ? static_cast<uint16_t>(at) : 0xFFFFu;
+    }
     rl = total;
     if (lane == r - 1) rl_l = rl;
     __syncthreads();
   }
-  // bought items, row by row (every wave by itself, 4 singles a lane)
+  if (!lower) {
+    *bad = false;
+    return 0;
+  }
+  // bought items, row by row (every wave by itself, 4 singles a lane; the
+  // next row's positions on their way)
   const uint32_t pd = (m - le) + (rank - lt), single = m - 1 - pd;
   uint32_t len = 0, k = cap;
   bool ok = false, over = false;
+  uint2 pos = reinterpret_cast<const uint2 *>(sm.spos[1])[lane];
+#pragma unroll 1
   for (uint32_t r = 1; r <= L && k; ++r) {
+    const uint2 p = pos;
+    pos = reinterpret_cast<const uint2 *>(sm.spos[r < L ? r + 1 : L])[lane];
     if (k > static_cast<uint32_t>(__builtin_amdgcn_readlane(rl_l, r))) { over = true; break; }
-    uint32_t sg = 0;
-#pragma unroll
-    for (uint32_t e = 0; e < 4; ++e) sg += static_cast<uint32_t>(__popcll(__ballot(sm.spos[r][64 * e + lane] < k)));
+    const uint32_t sg = static_cast<uint32_t>(__popcll(__ballot((p.x & 0xFFFF) < k)) + __popcll(__ballot((p.x >> 16) < k)) +
+                                              __popcll(__ballot((p.y & 0xFFFF) < k)) + __popcll(__ballot((p.y >> 16) < k)));
     len += sg > single ? 1u : 0u;
     ok |= sg >= m;
     k = 2 * (k - sg);
@@ -474,7 +535,8 @@ __device__ uint32_t tree_lengths(TreeSmem &sm, uint32_t c, uint32_t m, uint32_t 
   return c && !*bad ? len : 0u;
 }
 
-// Code of one block per workgroup, a thread per symbol, leaf or node: its
+// Code of one block per workgroup, a thread per symbol, leaf or node (the upper
+// half of 512 ends after the lengths): its
 // lengths (package-merge, or the supplied tree), then its layout.  A block
 // with one symbol becomes a constant block; a present symbol without a code
 // in the supplied tree is an argument error, and so are more symbols than
@@ -547,7 +609,8 @@ __device__ void block_done(uint32_t ans_mode, uint32_t nb, BlockLay &L, uint8_t 
   }
 }
 
-__global__ __launch_bounds__(256) void k_code(
+template <uint32_t NT>
+__global__ __launch_bounds__(NT) void k_code(
     const uint32_t *hist, uint32_t nb, uint64_t n, uint32_t bs, uint32_t max_len, pivco_tree tree,
     uint32_t use_tree, uint32_t ans_mode, uint32_t chunk_log2, uint32_t shape, const uint8_t *fse_dmax,
     EncBlock *eb, BlockLay *lay, RansNode *rnodes, uint8_t *hdr, uint32_t *err, Totals *tot, Result res) {
@@ -561,12 +624,15 @@ __global__ __launch_bounds__(256) void k_code(
   const uint64_t start = static_cast<uint64_t>(b) * bs;
   const uint32_t nblk = static_cast<uint32_t>(n - start < bs ? n - start : bs);
   const uint32_t cw = nblk <= 65535 ? 2u : 4u;
-  const uint32_t c = hist[256ull * b + t];   // the symbol's count
+  const uint32_t c = wave < 4 ? hist[256ull * b + t] : 0u;   // the symbol's count
   // its length l, and the block's mode (0 coded, 1 | symbol << 8 constant)
   uint32_t mode = 0, l = 0;
   {
     const uint64_t bal = __ballot(c != 0);
-    if (lane == 0) sm.present[wave] = bal;
+    if (wave < 4) {
+      if (lane == 0) sm.present[wave] = bal;
+      sm.tree.cnt[t] = c;
+    }
     __syncthreads();
     uint32_t m = 0, sym = 0;
 #pragma unroll
@@ -577,18 +643,19 @@ __global__ __launch_bounds__(256) void k_code(
     }
     bool bad = false;
     if (use_tree) {
-      l = tree.code_len[t];
+      l = tree.code_len[t & 255];
       bad = __syncthreads_or(c && l == 0);
       mode = bad ? 1u : 0u;
     } else if (m <= 1 || m > (1u << max_len)) {   // constant block, or no code of this length exists
       mode = 1u | (sym << 8);
       bad = m != 1;
     } else {
-      l = nblk < (1u << 24) ? tree_lengths<uint32_t>(sm.tree, c, m, max_len, &bad)
-                            : tree_lengths<uint64_t>(sm.tree, c, m, max_len, &bad);
+      l = nblk < (1u << 24) ? tree_lengths<NT, uint32_t>(sm.tree, m, max_len, &bad)
+                            : tree_lengths<NT, uint64_t>(sm.tree, m, max_len, &bad);
       mode = bad ? 1u : 0u;
       __syncthreads();                       // the tables of the layout take the same memory
     }
+    if (wave >= 4) return;                   // a barrier waits for the waves that are left
     if (bad && t == 0) atomicCAS(err, 0u, kErrArg);
   }
   if (t == 0) {
@@ -1801,7 +1868,8 @@ pivco_status encode_enqueue(const void *d_in, uint64_t n, void *d_out, uint64_t 
   // 2. code lengths (package-merge per block, or the supplied tree), layout
   pivco_tree tree{};
   if (o->tree) tree = *o->tree;
-  hipLaunchKernelGGL(k_code, dim3(nb), dim3(256), 0, s, dh, nb, n, static_cast<uint32_t>(bs), o->max_len, tree,
+  const bool few = nb <= kFewBlocks;
+  hipLaunchKernelGGL(few ? k_code<512> : k_code<256>, dim3(nb), dim3(few ? 512 : 256), 0, s, dh, nb, n, static_cast<uint32_t>(bs), o->max_len, tree,
                      o->tree ? 1u : 0u, o->ans_mode, o->rans_chunk_log2, o->tree_shape,
                      ft ? ft->dmax : nullptr, deb, dlay, drn, ws + L.hdr, derr, dtot, res);
   HIPCHK(hipGetLastError());
