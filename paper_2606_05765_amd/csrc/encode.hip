@@ -1758,7 +1758,9 @@ struct WsLayout {
 WsLayout ws_layout(uint64_t n, const pivco_encode_opts *o) {
   WsLayout L{};
   const uint64_t nb = div_up(n, o->block_size);
-  const uint64_t spb = div_up(std::min<uint64_t>(n, o->block_size), slice_of(n, o->block_size));
+  // rows for the small slice also where the large one is taken, so that the
+  // workspace of a longer input holds every shorter one
+  const uint64_t spb = div_up(std::min<uint64_t>(n, o->block_size), kSliceSmall);
   const uint64_t C = 1ull << o->rans_chunk_log2;
   const uint64_t bits = n * o->max_len;
   const uint64_t chunks = o->ans_mode ? bits / C + nb * 255 + 1 : 0;
