@@ -991,11 +991,10 @@ __device__ void chunk_jobs(const BlockLay &L, const RansNode *rnodes, uint32_t b
   }
 }
 
-constexpr uint32_t kEndsHere = 0x7F00;   // SplitSmem::K of a leaf: past every place
+constexpr uint32_t kEndsHere = 0x7F00;   // SplitSmem::K of a leaf: past every place (in bytes)
 
 template <int NT, uint32_t S>
 struct SplitSmem {
-  uint16_t buf[S + 64 * 4];            // a level's codes, in its nodes' order (groups of 4 chunks read past its end)
   union {
     uint32_t bits[13 * S / 32 + 2 * 16 + 4];   // every level's bits, then the flat nodes' fields
     struct {                           // before the levels only
@@ -1003,7 +1002,10 @@ struct SplitSmem {
       uint32_t T[257], O[257];         // symbols / 1 bits of the nodes before each node
     };
   };
-  int16_t K[2 * 272];                  // node in slot i: [2i] where its 0 symbols go, [2i + 1] its 1 symbols (see k_split)
+  // a level's codes, in its nodes' order (groups of 4 chunks read past its
+  // end; not first, as a place less the chunks done may be below 0)
+  uint16_t buf[S + 64 * 4];
+  int16_t K[2 * 272];                  // node in slot i: [2i] where its 0 symbols go, [2i + 1] its 1 symbols, in bytes (see k_split)
   uint32_t F[272];                     // flat node, by slot: where its fields go | D << 24
   uint32_t wx[257];                    // output words of the nodes before each node
   uint32_t src[256], len[256];         // node's first bit in `bits`; bits | rANS << 31
@@ -1042,9 +1044,12 @@ __device__ __forceinline__ uint32_t bits32(const uint32_t *w, uint32_t x) {
 // places are known and k_head has zeroed the bodies.  A word that this slice
 // does not fill is ORed into zeroed memory, the others are stored.
 //   The first slice's workgroup also lists the block's chunk jobs.
-// Bound by vector instructions, about 17 per 64 symbols and level, and by the
-// latency of the small levels (two barriers each).  256 MiB Zipf(1.1) in 64
-// KiB blocks: 1.38 ms where one wave per node (the root's 4096 symbols on one
+// Bound by vector instructions (four fifths of the issue slots), about 15 per 64
+// symbols and level, and by the latency of the small levels (two barriers
+// each).  Symbols that end are stored to one unused place instead of being masked
+// off, a place is one shift and add from the rank, and waves take whole groups
+// of 4 chunks: 17 instructions, 1.39 -> 1.31 ms.  256 MiB Zipf(1.1) in 64
+// KiB blocks: 1.31 ms where one wave per node (the root's 4096 symbols on one
 // wave of four) took 4.15 ms; one 64 KiB block: 18 us, was 86.  LDS holds one
 // level buffer (a level is in registers before it moves) and no more tables
 // than the levels need, for 6 workgroups of 256 threads on a CU: with two
@@ -1059,7 +1064,7 @@ __global__ __launch_bounds__(NT) void k_split(const uint8_t *in, const EncBlock 
   constexpr int kSplitNT = NT, kSplitNW = NT / kWaveE;
   constexpr uint32_t kPer = kSlice / NT;     // symbols of a thread, and 64-symbol chunks of a wave, at most
   constexpr uint32_t kSplitCh = kPer;
-  static_assert(kSlice <= 16384 && kPer % 4 == 0 && kPer <= 16, "places and leaf marks in 16 signed bits");
+  static_assert(kSlice <= 8192 && kPer % 4 == 0 && kPer <= 16, "places and leaf marks in 16 signed bits");
   __shared__ __attribute__((aligned(16))) SplitSmem<NT, kSlice> sm;
   const uint32_t tid = threadIdx.x, lane = __lane_id();
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1199,8 +1204,8 @@ __global__ __launch_bounds__(NT) void k_split(const uint8_t *in, const EncBlock 
     const uint32_t l0 = sm.lvl[d], l1 = sm.lvl[d + 1];
     const uint32_t seg = tv - sm.T[l0], rs = ones - sm.O[l0], t1 = sm.T[l1];
     const uint32_t c0 = cc & 0xFFFF, c1 = cc >> 16;
-    const uint32_t k0 = (c0 & 0x8000) ? kEndsHere : (sm.T[c0 & 255] - t1 - seg + rs) & 0xFFFF;
-    const uint32_t k1 = (c1 & 0x8000) ? kEndsHere : (sm.T[c1 & 255] - t1 - rs) & 0xFFFF;
+    const uint32_t k0 = (c0 & 0x8000) ? kEndsHere : 2 * (sm.T[c0 & 255] - t1 - seg + rs) & 0xFFFF;
+    const uint32_t k1 = (c1 & 0x8000) ? kEndsHere : 2 * (sm.T[c1 & 255] - t1 - rs) & 0xFFFF;
     reinterpret_cast<uint32_t *>(sm.K)[slot] = k0 | (k1 << 16);
     const uint32_t sb = FLAT && fd ? 64 * all64 + fx : 64 * lw_d + seg;
     if (FLAT) sm.F[slot] = ((sb - fd * seg) & 0xFFFFFF) | (fd << 24);   // bit sb + D (p - seg)
@@ -1210,12 +1215,14 @@ __global__ __launch_bounds__(NT) void k_split(const uint8_t *in, const EncBlock 
   // the flat fields are ORed in, from the second half of the root level on
   if (FLAT)
     for (uint32_t i = tid; i < (fbits + 31) / 32; i += kSplitNT) sm.bits[2 * all64 + i] = 0;
+  uint32_t next = __builtin_amdgcn_readlane(ln_l, 0);
   for (uint32_t lev = 0; lev < levels; ++lev) {
-    const uint32_t ln = __builtin_amdgcn_readlane(ln_l, lev);
+    const uint32_t ln = next;
     if (ln == 0) break;
     const uint32_t lf = FLAT ? __builtin_amdgcn_readlane(lf_l, lev) : 0u;
-    const uint32_t next = __builtin_amdgcn_readlane(ln_l, lev + 1);
-    const uint32_t nch = (ln + 63) / 64, per = (nch + kSplitNW - 1) / kSplitNW;
+    next = __builtin_amdgcn_readlane(ln_l, lev + 1);
+    const uint32_t nch = (ln + 63) / 64, least = (nch + kSplitNW - 1) / kSplitNW;
+    const uint32_t per = NT > 512 ? least : (least + 3) & ~3u;   // whole groups where several workgroups share a CU
     const uint32_t ch0 = wave * per, ch1 = ch0 + per < nch ? ch0 + per : nch;
     uint16_t *buf = sm.buf;              // every symbol is in registers before any moves
     uint2 *lbits = reinterpret_cast<uint2 *>(sm.bits) + __builtin_amdgcn_readlane(lw_l, lev);
@@ -1256,55 +1263,59 @@ __global__ __launch_bounds__(NT) void k_split(const uint8_t *in, const EncBlock 
     if (next == 0 && lf == 0) break;         // every symbol ends here
     if (lane == 0) sm.wsum[lev & 1][wave] = run;
     lds_sync();
-    uint32_t R = 0;
-    if (kSplitNW <= 4) {
+    if (ch0 < ch1) {
+      uint32_t R = 0;
+      if (kSplitNW <= 4) {
 #pragma unroll
-      for (uint32_t w = 0; w < kSplitNW; ++w) R += w < wave ? sm.wsum[lev & 1][w] : 0u;
-    } else {
-      R = __builtin_amdgcn_readlane(wave_incl_scan(lane < wave ? sm.wsum[lev & 1][lane & (kSplitNW - 1)] : 0u), 63);
-    }
-    R = __builtin_amdgcn_readfirstlane(R);
-    const int32_t kbase = static_cast<int32_t>(__builtin_amdgcn_readlane(kb_l, lev));
-    const int16_t *Kl = sm.K + 2 * kbase;    // by the code's first lev + 1 bits
-#pragma unroll
-    for (uint32_t g = 0; g < kSplitCh; g += 4) {
-      if (ch0 + g >= ch1) break;
-      if (64 * (ch0 + g + 4) <= lim && (!FLAT || 64 * (ch0 + g) >= lf)) {
-        int32_t k[4];
-#pragma unroll
-        for (uint32_t i = 0; i < 4; ++i) k[i] = Kl[pl[g + i] >> (15 - lev)];
-#pragma unroll
-        for (uint32_t i = 0; i < 4; ++i) {
-          const bool bit = pl[g + i] & mask;
-          const uint64_t mm = __ballot(bit);
-          const uint32_t r = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mm >> 32),
-                                                       __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mm), R));
-          R += static_cast<uint32_t>(__popcll(mm));
-          const uint32_t x = bit ? r : p0 + 64 * (g + i) - r;
-          const uint32_t at = x + k[i];
-          if (at < kSlice) buf[at] = static_cast<uint16_t>(pl[g + i]);
-        }
+        for (uint32_t w = 0; w < kSplitNW; ++w) R += w < wave ? sm.wsum[lev & 1][w] : 0u;
       } else {
+        R = __builtin_amdgcn_readlane(wave_incl_scan(lane < wave ? sm.wsum[lev & 1][lane & (kSplitNW - 1)] : 0u), 63);
+      }
+      // from here on R and a symbol's place are 32 less per chunk done: the
+      // constant goes into the store's offset, also for p - R
+      char *to = reinterpret_cast<char *>(buf);
+      const int32_t kbase = static_cast<int32_t>(__builtin_amdgcn_readlane(kb_l, lev));
+      const int16_t *Kl = sm.K + 2 * kbase;    // by the code's first lev + 1 bits
 #pragma unroll
-        for (uint32_t i = 0; i < 4; ++i) {
-          if (ch0 + g + i >= ch1) break;
-          const uint32_t p = p0 + 64 * (g + i), c = pl[g + i];
-          const uint32_t v = p < lim ? (c >> (16 - lev)) + kbase : 0u;
-          const int32_t k = sm.K[2 * v + ((c >> (15 - lev)) & 1)];
-          const bool bit = (c & mask) && p < lim && (!FLAT || p >= lf);
-          const uint64_t mm = __ballot(bit);
-          const uint32_t r = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mm >> 32),
-                                                       __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mm), R));
-          R += static_cast<uint32_t>(__popcll(mm));
-          if (p >= lim) continue;
-          if (FLAT && p < lf) {              // D-bit field: the code's last D bits
-            const uint32_t F = sm.F[v], D = F >> 24, x = (F + D * p) & 0xFFFFFF;
-            const uint32_t f = ((c << lev) & 0xFFFF) >> (16 - D);
-            atomicOr(&sm.bits[x >> 5], f << (x & 31));
-            if ((x & 31) + D > 32) atomicOr(&sm.bits[(x >> 5) + 1], f >> (32 - (x & 31)));
-          } else {
-            const uint32_t at = (bit ? r : p - r) + k;
-            if (at < kSlice) buf[at] = static_cast<uint16_t>(c);
+      for (uint32_t g = 0; g < kSplitCh; g += 4) {
+        if (ch0 + g >= ch1) break;
+        if (64 * (ch0 + g + 4) <= lim && (!FLAT || 64 * (ch0 + g) >= lf)) {
+          int32_t k[4];
+#pragma unroll
+          for (uint32_t i = 0; i < 4; ++i) k[i] = Kl[pl[g + i] >> (15 - lev)];
+#pragma unroll
+          for (uint32_t i = 0; i < 4; ++i) {
+            const bool bit = pl[g + i] & mask;
+            const uint64_t mm = __ballot(bit);
+            const uint32_t r = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mm >> 32),
+                                                         __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mm), R));
+            R += static_cast<uint32_t>(__popcll(mm)) - 32u;
+            const int32_t at = static_cast<int32_t>((bit ? r : p0 - r) << 1) + k[i];
+            const int32_t off = 64 * static_cast<int32_t>(g + i), unused = 2 * (kSlice + 64) - off;
+            *reinterpret_cast<uint16_t *>(to + (at < unused ? at : unused) + off) = static_cast<uint16_t>(pl[g + i]);
+          }
+        } else {
+#pragma unroll
+          for (uint32_t i = 0; i < 4; ++i) {
+            if (ch0 + g + i >= ch1) break;
+            const uint32_t p = p0 + 64 * (g + i), c = pl[g + i];
+            const uint32_t v = p < lim ? (c >> (16 - lev)) + kbase : 0u;
+            const int32_t k = sm.K[2 * v + ((c >> (15 - lev)) & 1)];
+            const bool bit = (c & mask) && p < lim && (!FLAT || p >= lf);
+            const uint64_t mm = __ballot(bit);
+            const uint32_t r = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mm >> 32),
+                                                         __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mm), R));
+            R += static_cast<uint32_t>(__popcll(mm)) - 32u;
+            if (p >= lim) continue;
+            if (FLAT && p < lf) {              // D-bit field: the code's last D bits
+              const uint32_t F = sm.F[v], D = F >> 24, x = (F + D * p) & 0xFFFFFF;
+              const uint32_t f = ((c << lev) & 0xFFFF) >> (16 - D);
+              atomicOr(&sm.bits[x >> 5], f << (x & 31));
+              if ((x & 31) + D > 32) atomicOr(&sm.bits[(x >> 5) + 1], f >> (32 - (x & 31)));
+            } else {
+              const uint32_t at = ((bit ? r : p0 - r) << 1) + k + 64 * (g + i);
+              if (at < 2 * kSlice) *reinterpret_cast<uint16_t *>(to + at) = static_cast<uint16_t>(c);
+            }
           }
         }
       }
