@@ -548,98 +548,122 @@ constexpr int kRansNT = 256;
 constexpr int kRansWin = 2048;        // u16 words per half-wave window in LDS
 constexpr uint32_t kRansSteps = 32;   // steps per window check (one output word per lane)
 
-// Lists the entropy-coded chunks of the block parsed in h/t (one lane):
+// Lists the entropy-coded chunks of the block parsed in h/t (one wave):
 // reserves the block's slots in the batch's list (their number follows
 // from the node sizes), then walks the bodies that follow the raw bodies
-// once, checking every size and filling the slots (on a corrupt body the
-// rest become empty chunks).  A rANS body is u16 probability, u16 zero, u32
+// once, checking every size and filling the slots (on a corrupt body all
+// become empty chunks).  A rANS body is u16 probability, u16 zero, u32
 // length, then per chunk of 2^chunk_log2 bits a u32 word count, the 32 u32
 // lane states and the words, padded to 4 bytes.  In a stream with flags bit
 // 0 a body is the tANS marker u8 (table 1..50, 0x80: complemented), u8
 // zero, u16 zero, u32 length, then per chunk the 32 u16 cursor states, the
-// 32 u16 stream lengths, the streams and zero padding to 4 bytes.  Returns
-// a status.
+// 32 u16 stream lengths, the streams and zero padding to 4 bytes.  A body's
+// place follows from the lengths before it, so the wave walks the bodies'
+// headers (one load each) and then checks up to 64 bodies' chunks at once, a
+// lane each: a node costs one round trip to memory where one lane for all took
+// three (16 mixed tANS streams of up to 64 MiB: the plan kernel 54 -> 32 us).  Returns a status.
 __device__ int32_t walk_rans(const JobDev &J, BlockHdr &h, const NodeTab &t, Counters *ctr,
                              RansChunk *chunks, uint64_t cap) {
+  const uint32_t lane = lane_id();
   const uint8_t *bp = J.in + h.blk;
   const uint64_t comp = h.comp, C = 1ull << J.chunk_log2;
   const bool fse = J.flags & 1;
+  const uint32_t I = h.I, job = h.job;
   // a node of n_v bits has ceil(n_v / C) chunks: the block's slots are
   // reserved before the walk, which then reads each chunk header once
   uint64_t want = 0;
-  for (uint32_t i = 0; i < h.I; ++i)
+  for (uint32_t i = lane; i < I; i += kWave)
     if (t.kind[i]) want += (static_cast<uint64_t>(t.nv[i]) + C - 1) / C;
-  const uint32_t nch = want > 0xFFFFFFFFull ? 0xFFFFFFFFu : static_cast<uint32_t>(want);
-  const uint32_t base = atomicAdd(&ctr->rans_chunks, nch);
+  for (int sh = kWave / 2; sh; sh >>= 1) want += __shfl_xor(want, sh, kWave);
+  const uint32_t nch = __builtin_amdgcn_readfirstlane(want > 0xFFFFFFFFull ? 0xFFFFFFFFu : static_cast<uint32_t>(want));
+  uint32_t base = 0;
+  if (lane == 0) base = atomicAdd(&ctr->rans_chunks, nch);
+  base = __builtin_amdgcn_readfirstlane(base);
   if (static_cast<uint64_t>(base) + nch > cap) {
     // slots reserved past the list's capacity stay unused (k_rans reads
     // at most cap); the ones below it become empty chunks
-    for (uint64_t f = base; f < cap; ++f) chunks[f] = RansChunk{0, 0, 0, 0, 1, h.job};
+    for (uint64_t f = static_cast<uint64_t>(base) + lane; f < cap; f += kWave) chunks[f] = RansChunk{0, 0, 0, 0, 1, job};
     return PIVCO_E_UNSUPPORTED;
   }
-  h.chunk0 = base;
-  h.nchunk = nch;
-  uint32_t k = 0;                        // slots written
-  // on a corrupt body the slots not yet written become empty chunks
-  auto fail = [&]() {
-    for (uint32_t f = k; f < nch; ++f) chunks[base + f] = RansChunk{0, 0, 0, 0, 1, h.job};
-    return static_cast<int32_t>(PIVCO_E_CORRUPT);
-  };
-  uint64_t o = h.raw_end;
-  for (uint32_t i = 0; i < h.I; ++i) {
-    if (!t.kind[i]) continue;
-    while (o & 3) {
-      if (o >= comp || bp[o]) return fail();
-      ++o;
-    }
-    if (o + 8 > comp || t.nv[i] == 0) return fail();
-    const uint32_t w0 = bp[o] | (bp[o + 1] << 8);
-    const uint32_t pad = bp[o + 2] | (bp[o + 3] << 8);
-    const uint32_t blen = *reinterpret_cast<const uint32_t *>(bp + o + 4);
-    const uint32_t tt = w0 & 0x7F;
-    if (pad || o + 8 + blen > comp) return fail();
-    if (fse ? ((w0 >> 8) || tt < 1 || tt > kFseTables) : (w0 < 1 || w0 > 4095)) return fail();
-    const uint32_t p1q = fse ? kFseTag | w0 : w0;
-    const uint64_t body = o + 8;
+  if (lane == 0) {
+    h.chunk0 = base;
+    h.nchunk = nch;
+  }
+  // the chunks of node i, whose body starts at o and whose slots at k0
+  auto list = [&](uint32_t i, uint64_t o, uint32_t k0, uint32_t w0, uint32_t blen) -> bool {
+    const uint64_t body = o + 8, nv = t.nv[i];
     uint64_t co = 0;
-    const uint64_t nv = t.nv[i];
     for (uint64_t s = 0; s < nv; s += C) {
       uint32_t nw;
       uint64_t size;
       if (fse) {
-        if (co + kFseChunkHdr > blen) return fail();
+        if (co + kFseChunkHdr > blen) return false;
         const uint32_t *lens = reinterpret_cast<const uint32_t *>(bp + body + co + 2 * kFseLanes);
         nw = 0;
+#pragma unroll
         for (uint32_t q = 0; q < kFseLanes / 2; ++q) {
           const uint32_t v = lens[q];
           nw += (v & 0xFFFF) + (v >> 16);
         }
         const uint64_t used = kFseChunkHdr + static_cast<uint64_t>(nw);
         size = (used + 3) & ~3ull;
-        if (co + size > blen) return fail();
+        if (co + size > blen) return false;
         for (uint64_t u = used; u < size; ++u)
-          if (bp[body + co + u]) return fail();
+          if (bp[body + co + u]) return false;
       } else {
-        if (co + kChunkHdr > blen) return fail();
+        if (co + kChunkHdr > blen) return false;
         nw = *reinterpret_cast<const uint32_t *>(bp + body + co);
         size = (kChunkHdr + 2ull * nw + 3) & ~3ull;
-        if (nw > C || co + size > blen) return fail();
+        if (nw > C || co + size > blen) return false;
       }
       RansChunk c;
       c.src = h.blk + body + co;
       c.dst = h.ans_word0 + t.boff[i] + s / 32;
       c.nbits = static_cast<uint32_t>(nv - s < C ? nv - s : C);
       c.nw = nw;
-      c.p1q = p1q;
-      c.job = h.job;
-      chunks[base + k] = c;
-      ++k;
+      c.p1q = fse ? kFseTag | w0 : w0;
+      c.job = job;
+      chunks[base + k0++] = c;
       co += size;
     }
-    if (co != blen) return fail();
-    o = body + blen;
+    return co == blen;
+  };
+  uint64_t o = h.raw_end;
+  bool ok = true;
+  uint32_t k = 0;                        // slots of the nodes before
+  for (uint32_t i = 0; ok && i < I;) {
+    uint32_t got = 0, my_i = 0, my_k = 0, my_w0 = 0, my_blen = 0;   // lane j: the body found j-th
+    uint64_t my_o = 0;
+    for (; i < I && got < kWave; ++i) {
+      if (!t.kind[i]) continue;
+      while (ok && (o & 3)) {
+        ok = o < comp && bp[o] == 0;
+        ++o;
+      }
+      const uint32_t nv = t.nv[i];
+      if (!ok || o + 8 > comp || nv == 0) { ok = false; break; }
+      const uint32_t *hd = reinterpret_cast<const uint32_t *>(bp + o);
+      const uint32_t w = hd[0], blen = hd[1], w0 = w & 0xFFFF, tt = w & 0x7F;
+      if ((w >> 16) || o + 8 + blen > comp) { ok = false; break; }
+      if (fse ? ((w0 >> 8) || tt < 1 || tt > kFseTables) : (w0 < 1 || w0 > 4095)) { ok = false; break; }
+      if (lane == got) {
+        my_i = i;
+        my_o = o;
+        my_k = k;
+        my_w0 = w0;
+        my_blen = blen;
+      }
+      ++got;
+      k += static_cast<uint32_t>((static_cast<uint64_t>(nv) + C - 1) / C);
+      o += 8ull + blen;
+    }
+    ok = __all(ok && (lane >= got || list(my_i, my_o, my_k, my_w0, my_blen)));
   }
-  if (o != comp) return fail();
+  if (!ok || o != comp) {
+    __threadfence();                     // after the slots that were filled
+    for (uint32_t f = lane; f < nch; f += kWave) chunks[base + f] = RansChunk{0, 0, 0, 0, 1, job};
+    return PIVCO_E_CORRUPT;
+  }
   return PIVCO_OK;
 }
 
@@ -2686,10 +2710,11 @@ __global__ __launch_bounds__(kWave * kPlanWaves) void k_plan(const JobDev *jobs,
   if (lane == 0) {
     h.chunk0 = 0;
     h.nchunk = 0;
-    if (!h.err && h.mode == 0 && h.n_ans) {
-      const int32_t e = walk_rans(J, h, t, ctr, chunks, chunk_cap);
-      if (e) h.err = e;
-    }
+  }
+  wave_sync_lds();
+  if (!h.err && h.mode == 0 && h.n_ans) {
+    const int32_t e = walk_rans(J, h, t, ctr, chunks, chunk_cap);
+    if (lane == 0 && e) h.err = e;
   }
   wave_sync_lds();
   const uint4 *src = reinterpret_cast<const uint4 *>(&pb[wave]);
