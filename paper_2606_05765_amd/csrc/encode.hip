@@ -5,7 +5,8 @@
 // through it, emits one bit per symbol (its bitmap) and partitions the
 // symbols between its children (the enc_partition primitives of Table 11).
 // The driver:
-//   1. k_hist        symbol histogram of every block and of every slice of it (end-to-end encode time is dominated by this
+//   1. k_hist        symbol histogram of every block and of every slice of it
+//                    (end-to-end encode time is dominated by this
 //                    count, Sec. 4); k_slice_prefix turns the slice counts
 //                    into per-slice prefixes;
 //   2. k_code        per block: optimal length-limited lengths (package-merge,

@@ -14,3 +14,10 @@ NS = [1, 63, 4096, 4097, 8191, 8192, 65_536, 1 << 20, (8 << 20) - 4097, (8 << 20
 def test_grows_with_n(bs, ans):
     w = [P.pivco_encode_workspace(n, bs, ans_mode=ans) for n in NS]
     assert all(a <= b for a, b in zip(w, w[1:]))
+
+
+@pytest.mark.parametrize("bs", [1, 64, 8191, 8192, 8193, 65_536, 16 << 20])
+def test_golomb_grows_with_n(bs):
+    f = P.lib().pivco_golomb_encode_workspace
+    w = [f(n, bs) for n in NS]
+    assert all(a <= b for a, b in zip(w, w[1:]))
