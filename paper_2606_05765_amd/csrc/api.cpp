@@ -314,7 +314,7 @@ pivco_status enqueue_batch(const HostPlan &p, void *d_ws, int32_t *d_status, con
                   d.chunks, p.chunk_cap) != hipSuccess)
     return PIVCO_E_DEVICE;
   if (!w.ritems.empty() &&
-      launch_rans(t.rans_grid, s, d.jobs, d.recs, d.ritems, d.ctr, d.chunks, p.chunk_cap, d.scratch,
+      launch_rans(t.rans_grid, device_cus(), s, d.jobs, d.recs, d.ritems, d.ctr, d.chunks, p.chunk_cap, d.scratch,
                   -1, p.coders) != hipSuccess)
     return PIVCO_E_DEVICE;
   if (launch_tiles(s, d.jobs, d.tiled, static_cast<uint32_t>(w.tiled.size()), d.recs,
@@ -482,7 +482,7 @@ pivco_status pivco_decode_plain(const pivco_job *h_jobs, uint32_t count, int32_t
   // one launch per block (rANS), then the boundaries of split blocks, then
   // one merge launch per item, in stream order
   for (size_t r = 0; r < w.ritems.size(); ++r)
-    if (launch_rans(1, s, d.jobs, d.recs, d.ritems, d.ctr, d.chunks, p.chunk_cap, d.scratch,
+    if (launch_rans(1, 1, s, d.jobs, d.recs, d.ritems, d.ctr, d.chunks, p.chunk_cap, d.scratch,
                     static_cast<int32_t>(r), p.coders) != hipSuccess)
       return PIVCO_E_DEVICE;
   if (launch_tiles(s, d.jobs, d.tiled, static_cast<uint32_t>(w.tiled.size()), d.recs,
@@ -516,7 +516,7 @@ pivco_status pivco_decode_topdown(const pivco_job *h_jobs, uint32_t count, int32
                   d.chunks, p.chunk_cap) != hipSuccess)
     return PIVCO_E_DEVICE;
   if (!w.ritems.empty() &&
-      launch_rans(t.rans_grid, s, d.jobs, d.recs, d.ritems, d.ctr, d.chunks, p.chunk_cap, d.scratch,
+      launch_rans(t.rans_grid, device_cus(), s, d.jobs, d.recs, d.ritems, d.ctr, d.chunks, p.chunk_cap, d.scratch,
                   kQueueItems, p.coders) != hipSuccess)
     return PIVCO_E_DEVICE;
   if (launch_tiles(s, d.jobs, d.tiled, static_cast<uint32_t>(w.tiled.size()), d.recs,

@@ -810,13 +810,20 @@ __device__ void rans_pair(const JobDev *jobs, const RansChunk *chunks, uint32_t 
   if (hl == 0 && eh) set_err(jobs[c.job].status, PIVCO_E_CORRUPT);
 }
 
+// Whether one workgroup a CU holds every pair of the list's chunks: then the
+// others leave at once, so that no two busy waves share a SIMD while another
+// idles (a pair is a chain of dependent steps, and a second one beside it on
+// a SIMD slows both: k_fse of 16 mixed streams 44 -> 34 us with one workgroup a
+// CU, but 88 -> 102 for the 4096 chunks of 256 MiB skewed data, so those keep two).
+__device__ __forceinline__ bool few_pairs(uint32_t chunks, uint32_t waves) { return (chunks + 1) / 2 <= waves; }
+
 // Decodes the batch's listed chunks, a pair per wave from a shared counter;
 // or, for single >= 0, only the chunks of block ritems[single] with one
 // workgroup (the per-block launch mode).
 __global__ __launch_bounds__(kRansNT) void k_rans(const JobDev *jobs, const ParsedBlock *recs,
                                                    const uint2 *ritems, Counters *ctr,
                                                    const RansChunk *chunks, uint64_t cap,
-                                                   uint32_t *scratch, int32_t single) {
+                                                   uint32_t *scratch, int32_t single, uint32_t cus) {
   __shared__ uint16_t win[kRansNT / kWave][2][kRansWin];
   const uint32_t wave = wave_id();
   constexpr uint32_t NW = kRansNT / kWave;
@@ -827,6 +834,7 @@ __global__ __launch_bounds__(kRansNT) void k_rans(const JobDev *jobs, const Pars
   } else {
     const uint32_t n = ctr->rans_chunks;
     end = n < cap ? n : static_cast<uint32_t>(cap);
+    if (blockIdx.x >= cus && few_pairs(end, NW * cus)) return;
   }
   for (uint32_t it = 0;; ++it) {
     uint32_t pair;
@@ -983,7 +991,8 @@ __device__ void fse_pair(const JobDev *jobs, const RansChunk *chunks, uint32_t i
 __global__ __launch_bounds__(kFseNT) void k_fse(const JobDev *jobs, const ParsedBlock *recs,
                                                  const uint2 *ritems, Counters *ctr,
                                                  const RansChunk *chunks, uint64_t cap,
-                                                 const uint32_t *dec, uint32_t *scratch, int32_t single) {
+                                                 const uint32_t *dec, uint32_t *scratch, int32_t single,
+                                                 uint32_t cus) {
   __shared__ uint32_t tab[kFseNT / kWave][2][kFseSize];
   __shared__ uint32_t stage[kFseNT / kWave][2][256];
   const uint32_t wave = wave_id();
@@ -995,6 +1004,7 @@ __global__ __launch_bounds__(kFseNT) void k_fse(const JobDev *jobs, const Parsed
   } else {
     const uint32_t n = ctr->rans_chunks;
     end = n < cap ? n : static_cast<uint32_t>(cap);
+    if (blockIdx.x >= cus && few_pairs(end, NW * cus)) return;
   }
   uint32_t loaded = 0;
   for (uint32_t it = 0;; ++it) {
@@ -3116,13 +3126,13 @@ hipError_t launch_tiles(hipStream_t s, const JobDev *jobs, const TiledBlock *til
   return hipGetLastError();
 }
 
-hipError_t launch_rans(uint32_t grid, hipStream_t s, const JobDev *jobs, const void *recs,
+hipError_t launch_rans(uint32_t grid, uint32_t cus, hipStream_t s, const JobDev *jobs, const void *recs,
                        const uint2 *ritems, Counters *ctr, const RansChunk *chunks,
                        uint64_t chunk_cap, uint32_t *scratch, int32_t single, uint32_t coders) {
   if (coders & 1) {
     hipLaunchKernelGGL(k_rans, dim3(grid), dim3(kRansNT), 0, s, jobs,
                        static_cast<const ParsedBlock *>(recs), ritems, ctr, chunks, chunk_cap, scratch,
-                       single);
+                       single, cus);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -3131,7 +3141,7 @@ hipError_t launch_rans(uint32_t grid, hipStream_t s, const JobDev *jobs, const v
     if (!ft) return hipErrorNotInitialized;
     hipLaunchKernelGGL(k_fse, dim3(grid), dim3(kFseNT), 0, s, jobs,
                        static_cast<const ParsedBlock *>(recs), ritems, ctr, chunks, chunk_cap, ft->dec,
-                       scratch, single);
+                       scratch, single, cus);
     return hipGetLastError();
   }
   return hipSuccess;

@@ -262,7 +262,8 @@ inline bool skewed_job(uint64_t n_total, uint64_t in_len, uint64_t ans_words, ui
 }
 // coders: bit 0, some job has rANS nodes; bit 1, some job has tANS nodes
 // (then fse_tables() has been called for the device).
-hipError_t launch_rans(uint32_t grid, hipStream_t s, const JobDev *jobs, const void *recs,
+// cus: the device's compute units (see few_pairs).
+hipError_t launch_rans(uint32_t grid, uint32_t cus, hipStream_t s, const JobDev *jobs, const void *recs,
                        const uint2 *ritems, Counters *ctr, const RansChunk *chunks,
                        uint64_t chunk_cap, uint32_t *scratch, int32_t single, uint32_t coders);
 int rans_occupancy();

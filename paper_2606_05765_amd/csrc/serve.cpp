@@ -372,7 +372,7 @@ pivco_status pivco_server_run(pivco_server *sv, const pivco_request *reqs, uint3
       if (launch_plan(s.stream, dj, d_blocks, nb, recs, ctr, d_chunks, chunks) != hipSuccess)
         return PIVCO_E_DEVICE;
       if (nr && launch_rans(std::max<uint32_t>(1, std::min<uint32_t>(rgrid_full, static_cast<uint32_t>((chunks + 7) / 8))),
-                            s.stream, dj, recs, reinterpret_cast<const uint2 *>(s.ws + o_ritems), ctr,
+                            rgrid_full / 2, s.stream, dj, recs, reinterpret_cast<const uint2 *>(s.ws + o_ritems), ctr,
                             d_chunks, chunks, scr, -1, coders) != hipSuccess)
         return PIVCO_E_DEVICE;
       if (launch_tiles(s.stream, dj, d_tiled, nt, recs, scr, sw, d_tab) != hipSuccess)
