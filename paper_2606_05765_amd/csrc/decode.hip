@@ -1165,20 +1165,32 @@ __device__ __forceinline__ uint32_t lds_win(const uint8_t *lds, uint32_t a) {
   return __builtin_amdgcn_alignbyte(p[1], p[0], a);
 }
 
+// Whether a tile of `share` symbols is small: its nodes enter the window starts
+// themselves (list_node), at most 16 windows of 64 tasks for its root.  Above
+// that the root's stores, one window after the other, keep every other node
+// waiting, and one wave per level finds the starts (window_starts), whose barrier
+// and scans are what a small tile would wait for.  128 MiB Zipf(1.1) in blocks of 4
+// Ki symbols, starts by the waves and by the nodes: 1601 and 1579 us, of 8 Ki 827
+// and 819; 256 MiB in blocks of 16 Ki 988 and 982, of 32 Ki 648 and 648, of 64 Ki 609
+// and 614.
+constexpr uint32_t kSmallTile = 16384;
+
 // Enters a node with work into its level's task windows: its record goes to
-// its slot, and its first task sets a bit of the window start mask.
+// its slot, and its first task sets a bit of the window start mask; in a small
+// tile (starts) the windows whose first task falls inside it point at its level
+// slot ai.
 template <class C>
 __device__ __forceinline__ void list_node(MergeSmem<C> &sm, uint32_t d, uint32_t gslot, uint32_t tp,
-                                          const NodeRec &r) {
+                                          const NodeRec &r, bool starts, uint32_t ai, uint32_t nt) {
   sm.rec[gslot] = r;
+  if (starts)
+    for (uint32_t w = (tp + 63) >> 6; kWave * w < tp + nt; ++w) sm.wstart[d][w] = static_cast<uint8_t>(ai);
   atomicOr(reinterpret_cast<unsigned long long *>(&sm.smask[d][tp >> 6]), 1ull << (tp & 63));
 }
 
 // Level slot of the node that holds each window's first task, run by one wave
 // (a window per lane) once the level's start masks are complete: the nodes
 // are in slot order, so it is the number of starts up to that task, less one.
-// (Written by the node instead, window by window, the root's 32 stores kept
-// every other node waiting: the lists took 3.9K cycles a tile, 3.6K now.)
 template <class C>
 __device__ __forceinline__ void window_starts(MergeSmem<C> &sm, uint32_t d) {
   const uint32_t lane = lane_id();
@@ -1276,7 +1288,7 @@ __device__ void count_level_streaming(MergeSmem<C> &sm, uint32_t d) {
         r.arank = fl ? flat_tag<C>(sm, t, v) : 0u;
         r.ot = sm.obase[v] | (tp << 16);
         r.kids = kids;
-        list_node<C>(sm, d, act_base + ai, tp, r);
+        list_node<C>(sm, d, act_base + ai, tp, r, false, ai, tasks);
       }
       sm.cur[v] += tvv;
     }
@@ -1351,15 +1363,16 @@ __device__ void count_last(MergeSmem<C> &sm) {
   }
 }
 
-// Resident tile bookkeeping (all threads), from the shares in sm.tv: one
-// exclusive scan over the nodes in breadth-first order, where every level is
-// a contiguous range, of (share rounded up to 16 bytes | 16-output tasks <<
-// 32 | has-work << 48).  Differences of the scan within a level give each
+// Resident bookkeeping (all threads) of a tile of `share` symbols, from the
+// nodes' shares in sm.tv: one exclusive scan over the nodes in breadth-first
+// order, where every level is a contiguous range, of (share rounded up to 16
+// bytes | 16-output tasks << 32 | has-work << 48).  Differences of the scan within a level give each
 // node's output offset in its level buffer, its slot in the level's list of
 // nodes with work and the tasks before it; the merge records follow, and
 // the cursors advance.
 template <class C, bool FLAT>
-__device__ void tile_lists(MergeSmem<C> &sm) {
+__device__ void tile_lists(MergeSmem<C> &sm, uint32_t share) {
+  const bool small = share <= kSmallTile;
   const int tid = item_tid();
   const int wave = wave_id();
   const uint32_t lane = lane_id();
@@ -1410,7 +1423,8 @@ __device__ void tile_lists(MergeSmem<C> &sm) {
       r.arank = fdv ? flat_tag<C>(sm, t, v) : sm.arank[v];
       r.ot = static_cast<uint32_t>(rel) | (tp << 16);
       r.kids = kids;
-      list_node<C>(sm, d, static_cast<uint32_t>(pfx[v] >> 48), tp, r);
+      list_node<C>(sm, d, static_cast<uint32_t>(pfx[v] >> 48), tp, r, small, static_cast<uint32_t>(rel >> 48),
+                   (tvv + C::K - 1) / C::K);
     }
     sm.cur[v] += tvv;
     sm.arank[v] = sm.aend[v];
@@ -1428,6 +1442,7 @@ __device__ void tile_lists(MergeSmem<C> &sm) {
     sm.actbase[tid] = static_cast<uint32_t>(pfx[h.lvl[tid]] >> 48);
   }
   lds_barrier();
+  if (small) return;
   for (uint32_t d = wave; d < h.maxlen; d += C::NW) window_starts<C>(sm, d);
   lds_barrier();
 }
@@ -1950,7 +1965,11 @@ __device__ void fill_constant(uint8_t *out, uint32_t n, uint32_t c) {
 // superblock the 1 bits before it, per 64-bit word the 1 bits of its
 // superblock before it; then every node's rank at its first bit (sm.abit).
 // Ends with a barrier only when `last` is set: otherwise the caller's next
-// barrier orders the ranks before their readers.
+// barrier orders the ranks before their readers.  A thread has consecutive
+// superblocks (two at most in the kernels of 1024 threads) and one scan runs over
+// the threads' sums: with a row of 64 superblocks a wave, read coalesced, two scans
+// a wave cost small blocks more than the reads gained large ones (256 MiB Zipf in
+// blocks of 8 KiB 829 -> 817 us, in blocks of 64 KiB 609 -> 609).
 template <class C>
 __device__ void build_directory(MergeSmem<C> &sm, uint32_t body_dw, uint32_t I, bool last) {
   const uint32_t tid = item_tid();
@@ -2104,8 +2123,8 @@ __device__ void decode_block(const JobDev &J, const BlockExt &ext, uint32_t k,
         }
         lds_barrier();
       }
-      if (flat) tile_lists<C, true>(sm);
-      else tile_lists<C, false>(sm);
+      if (flat) tile_lists<C, true>(sm, troot);
+      else tile_lists<C, false>(sm, troot);
     } else {
       for (uint32_t d = 0; d < maxd; ++d) {
         stage_level_streaming<C>(J, sm, d, scratch, scratch_words);
