@@ -1967,44 +1967,37 @@ __device__ void fill_constant(uint8_t *out, uint32_t n, uint32_t c) {
 // Ends with a barrier only when `last` is set: otherwise the caller's next
 // barrier orders the ranks before their readers.  A thread has consecutive
 // superblocks (two at most in the kernels of 1024 threads) and one scan runs over
-// the threads' sums: with a row of 64 superblocks a wave, read coalesced, two scans
-// a wave cost small blocks more than the reads gained large ones (256 MiB Zipf in
-// blocks of 8 KiB 829 -> 817 us, in blocks of 64 KiB 609 -> 609).
+// the threads' sums: a row of 64 superblocks a wave, read coalesced, takes a scan
+// per row, which small blocks wait for (128 MiB Zipf(1.1) in blocks of 8 Ki symbols
+// 819 us, 808 so; 256 MiB in blocks of 64 Ki 612 and 611).
 template <class C>
 __device__ void build_directory(MergeSmem<C> &sm, uint32_t body_dw, uint32_t I, bool last) {
   const uint32_t tid = item_tid();
   const uint32_t wave = wave_id();
   const uint32_t lane = lane_id();
   const uint32_t nsb = (body_dw + 7) / 8 + 1;
-  // a wave has PER consecutive rows of 64 superblocks, one a lane
-  constexpr uint32_t PER = (C::BODY / 32 + 1 + C::NT - 1) / C::NT;
-  const uint32_t s0 = wave * (PER * kWave) + lane;
-  uint32_t cnt[PER], ex[PER], loc = 0;
-#pragma unroll
-  for (uint32_t j = 0; j < PER; ++j) {
-    const uint32_t k = s0 + kWave * j;
-    cnt[j] = 0;
-    if (k < nsb) {
-      const uint4 a = *reinterpret_cast<const uint4 *>(&sm.body[8 * k]);
-      const uint4 c = *reinterpret_cast<const uint4 *>(&sm.body[8 * k + 4]);
-      const uint32_t w0 = __popc(a.x) + __popc(a.y), w1 = __popc(a.z) + __popc(a.w);
-      const uint32_t w2 = __popc(c.x) + __popc(c.y), w3 = __popc(c.z) + __popc(c.w);
-      *reinterpret_cast<uint32_t *>(&sm.rel[4 * k]) = (w0 << 8) | ((w0 + w1) << 16) | ((w0 + w1 + w2) << 24);
-      cnt[j] = w0 + w1 + w2 + w3;
-    }
+  const uint32_t per = (nsb + C::NT - 1) / C::NT;
+  const uint32_t s0 = tid * per;
+  uint32_t loc = 0;
+  for (uint32_t k = s0; k < s0 + per && k < nsb; ++k) {
+    const uint4 a = *reinterpret_cast<const uint4 *>(&sm.body[8 * k]);
+    const uint4 c = *reinterpret_cast<const uint4 *>(&sm.body[8 * k + 4]);
+    const uint32_t w0 = __popc(a.x) + __popc(a.y), w1 = __popc(a.z) + __popc(a.w);
+    const uint32_t w2 = __popc(c.x) + __popc(c.y), w3 = __popc(c.z) + __popc(c.w);
+    *reinterpret_cast<uint32_t *>(&sm.rel[4 * k]) = (w0 << 8) | ((w0 + w1) << 16) | ((w0 + w1 + w2) << 24);
+    const uint32_t cnt = w0 + w1 + w2 + w3;
+    sm.sup[k] = cnt;
+    loc += cnt;
   }
-#pragma unroll
-  for (uint32_t j = 0; j < PER; ++j) {
-    const uint32_t inc = wave_incl_scan(cnt[j]);
-    ex[j] = loc + inc - cnt[j];
-    loc += static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(inc), kWave - 1));
-  }
-  if (lane == 0) sm.scan_tot[wave] = loc;
+  const uint32_t inc = wave_incl_scan(loc);
+  if (lane == kWave - 1) sm.scan_tot[wave] = inc;
   lds_barrier();
-  const uint32_t run = sum_first(sm.scan_tot, wave);
-#pragma unroll
-  for (uint32_t j = 0; j < PER; ++j)
-    if (s0 + kWave * j < nsb) sm.sup[s0 + kWave * j] = run + ex[j];
+  uint32_t run = inc - loc + sum_first(sm.scan_tot, wave);
+  for (uint32_t k = s0; k < s0 + per && k < nsb; ++k) {
+    const uint32_t c = sm.sup[k];
+    sm.sup[k] = run;
+    run += c;
+  }
   lds_barrier();
   for (uint32_t i = tid; i < I; i += C::NT) {
     const uint32_t r = rank_at(sm.body, sm.sup, sm.rel, sm.abit[i]);
