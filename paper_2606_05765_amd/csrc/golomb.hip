@@ -14,7 +14,7 @@
 // bitmap sizes and places) -> k_gscan (block offsets) -> k_ghead (stream
 // header, zeroed blocks) -> k_gsplit (per slice, every value's one 1 bit).
 // Nothing is planned on the host; the call waits once, for the length.
-// Decode: k_gdecode, one workgroup per block, tiles of kGT values: a
+// Decode: k_gdecode, one workgroup per block, tiles of 16 values a thread: a
 // top-down count gives each bitmap's share of the tile (the 0 bits of one
 // bitmap's share are the next one's), then the bottom-up merge: a lane makes
 // 16 values from 16 bits, their rank, 4-byte windows of the next bitmap's
@@ -34,8 +34,6 @@ namespace {
 constexpr uint32_t kGMagic = 0x31475650u;   // "PVG1"
 constexpr uint32_t kGHdr = 32;
 constexpr int kGW = 64;
-constexpr int kGNT = 512;                   // decode workgroup
-constexpr uint32_t kGT = 16 * kGNT;         // values per decode tile
 
 // One Golomb job as the decode kernel sees it.
 struct GJob {
@@ -401,32 +399,39 @@ __global__ __launch_bounds__(kGEN, 5) void k_gsplit(const uint8_t *in, uint64_t 
 // ---------------------------------------------------------------------------
 // decode kernel
 // ---------------------------------------------------------------------------
-constexpr int kGNW = kGNT / kGW;
-constexpr int kGStat = 4;                   // top levels, all waves, bits in registers
-constexpr int kGDeep = 6;                   // levels below them that one wave takes in registers
+// Workgroups of 1024 threads, tiles of 16384 values, where two a CU hold all
+// blocks and some block is longer than a tile of 512 threads: a tile's time is
+// its levels' latency, and few blocks leave nothing to hide it behind.  Mean code
+// length 2, 512 and 1024 threads: one block of 1 Mi values 1146 and 735 us a call,
+// 512 blocks of 64 Ki 152 and 126; 1024 blocks, which 512 threads still hold at
+// once, 167 and 186.  Uniform values (mean 128): 512 blocks of 64 Ki 3.47 and 2.44
+// ms, 768 3.84 and 4.00.
+constexpr uint32_t kGFew = 512, kGNarrow = 16 * 512;
 constexpr uint32_t kGWave = 16 * kGW;       // values one wave merges at once
 
+template <int NT>
 struct GSmem {
   uint32_t nk[257];          // values reaching bitmap k (n_0 = n, n_K = 0)
   uint32_t cur[257];         // of which decoded by earlier tiles
   uint32_t tv[257];          // of which in this tile
   uint64_t boff[256];        // bitmap k's first byte in the stream
-  uint64_t part[kGNW];
-  uint32_t wsum[2][kGNW];
+  uint64_t part[NT / kGW];
+  uint32_t wsum[2][NT / kGW];
   uint32_t sel[16];
   uint32_t err, depth;
-  uint32_t lvl[2][kGT / 4 + 32] __attribute__((aligned(16)));
+  uint32_t lvl[2][4 * NT + 32] __attribute__((aligned(16)));
 };
 
 // Sum over the workgroup of a wave's inclusive scan `inc` (its last lane's),
 // and of the waves before this one; one barrier, two slots used in turn.
-__device__ __forceinline__ uint32_t g_waves(GSmem &sm, uint32_t slot, uint32_t inc, uint32_t *before) {
+template <int NT>
+__device__ __forceinline__ uint32_t g_waves(GSmem<NT> &sm, uint32_t slot, uint32_t inc, uint32_t *before) {
   const uint32_t wave = threadIdx.x >> 6;
   if (__lane_id() == kGW - 1) sm.wsum[slot][wave] = inc;
   __syncthreads();
   uint32_t b = 0, t = 0;
 #pragma unroll
-  for (uint32_t w = 0; w < kGNW; ++w) {
+  for (uint32_t w = 0; w < NT / kGW; ++w) {
     const uint32_t x = sm.wsum[slot][w];
     b += w < wave ? x : 0u;
     t += x;
@@ -442,7 +447,8 @@ __device__ __forceinline__ uint32_t g_first(uint32_t bits, uint32_t x, uint32_t 
 
 // 16 outputs of a level from 16 bits and the 1 bits before them: 4-byte
 // windows of the next level's values at cb + rank, one v_perm_b32 per 4.
-__device__ __forceinline__ void g_merge16(const GSmem &sm, uint32_t parity, uint32_t x, uint32_t bits, uint32_t r1,
+template <int NT>
+__device__ __forceinline__ void g_merge16(const GSmem<NT> &sm, uint32_t parity, uint32_t x, uint32_t bits, uint32_t r1,
                                           uint32_t o[4]) {
   const uint8_t *lds = reinterpret_cast<const uint8_t *>(&sm);
   uint32_t a[4], s[4], w0[4], w1[4];
@@ -465,7 +471,8 @@ __device__ __forceinline__ void g_merge16(const GSmem &sm, uint32_t parity, uint
 
 // Values of a level to its buffer, plus one (the level above reads them as
 // "1 + value"); the root's to the output.
-__device__ __forceinline__ void g_put(GSmem &sm, int k, uint32_t x, uint32_t n, const uint32_t o[4], uint8_t *out) {
+template <int NT>
+__device__ __forceinline__ void g_put(GSmem<NT> &sm, int k, uint32_t x, uint32_t n, const uint32_t o[4], uint8_t *out) {
   if (x >= n) return;
   if (k > 0) {
     *reinterpret_cast<uint4 *>(reinterpret_cast<uint8_t *>(sm.lvl[k & 1]) + x) =
@@ -478,24 +485,23 @@ __device__ __forceinline__ void g_put(GSmem &sm, int k, uint32_t x, uint32_t n, 
   }
 }
 
-// One workgroup per block, tiles of kGT values, 16 a thread.  Top-down, the 0
-// bits of a level's share are the next level's share; bottom-up, the merge.
-// A tile's bits start at the levels' cursors, which are known before it, so
-// the top levels' bits (all threads) and those of the deeper ones (wave 0,
-// which takes every level of at most kGWave values without a barrier) are
-// loaded at once and stay in registers for both directions.  A level of at
-// most 64 values and all below it need no way up: a lane per value follows it
-// down, its place among the values still alive a mbcnt of their ballot, each
-// level's bits a 64-bit scalar.  Levels past those in registers load theirs
-// as they come.
+// One workgroup per block, tiles of 16 values a thread.  Top-down, the 0 bits of
+// a level's share are the next level's share; bottom-up, the merge.  The root's
+// bits stay in a register for both directions, wave 0 takes every level of at
+// most kGWave values without a barrier.  A level of at most 64 values and all
+// below it need no way up: a lane per value follows it down, its place among
+// the values still alive a mbcnt of their ballot, each level's bits a 64-bit
+// scalar, loaded at the tile's start.  The other levels load their bits in each
+// direction.  (Ten levels' bits loaded up front and held in registers spilled 50 of
+// the 64 that 8 waves a SIMD leave: 1024 blocks of 64 Ki values of mean code length
+// 2 took 143 us, 104 without; the call 203 and 165, of 16384 blocks of 4 Ki 363 and 259.)
 // Bound by the vector instructions of the levels (about 60 per 1024 values)
-// and the chain of the deep ones: 512 threads a block keep several blocks on
-// a CU.  64 Mi values of mean code length 2 in 64 Ki blocks: 145 us,
-// where 1024 threads with two barriers and two loads from memory per level
-// took 289 us.
-__global__ __launch_bounds__(kGNT, 8) void k_gdecode(const GJob *jobs, uint32_t njobs, uint32_t nblocks,
-                                                     int32_t *status) {
-  __shared__ GSmem sm;
+// and the chain of the deep ones.
+template <int NT>
+__global__ __launch_bounds__(NT, 8) void k_gdecode(const GJob *jobs, uint32_t njobs, uint32_t nblocks,
+                                                   int32_t *status) {
+  constexpr uint32_t kGT = 16 * NT;          // values per tile
+  __shared__ GSmem<NT> sm;
   const uint32_t tid = threadIdx.x, lane = __lane_id();
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (blockIdx.x >= nblocks) return;
@@ -542,7 +548,7 @@ __global__ __launch_bounds__(kGNT, 8) void k_gdecode(const GJob *jobs, uint32_t 
   if (tid < 256) sm.nk[tid] = nk;
   if (tid == 0) { sm.nk[256] = 0; sm.err = 0; }
   uint64_t body;
-  const uint64_t bo = g_block_scan<kGNT>((static_cast<uint64_t>(nk) + 7) / 8, sm.part, &body);
+  const uint64_t bo = g_block_scan<NT>((static_cast<uint64_t>(nk) + 7) / 8, sm.part, &body);
   if (tid < 256) {
     sm.boff[tid] = off + hlen + bo;
     sm.cur[tid] = 0;
@@ -569,9 +575,7 @@ __global__ __launch_bounds__(kGNT, 8) void k_gdecode(const GJob *jobs, uint32_t 
   const uint32_t x = 16 * tid, xl = 16 * lane;
   for (uint32_t t0 = 0; t0 < n; t0 += kGT) {
     const uint32_t S = n - t0 < kGT ? n - t0 : kGT;
-    uint32_t top[kGStat], deep[kGDeep];
-#pragma unroll
-    for (int k = 0; k < kGStat; ++k) top[k] = fetch(k, x);
+    uint32_t root = fetch(0, x);
     uint32_t w_lo = 0, w_hi = 0, rem = 0;    // level lane: its first 64 bits, values left of it
     auto words64 = [&](uint32_t k) {
       w_lo = w_hi = rem = 0;
@@ -584,12 +588,8 @@ __global__ __launch_bounds__(kGNT, 8) void k_gdecode(const GJob *jobs, uint32_t 
       w_lo = __builtin_amdgcn_alignbit(a1, a0, static_cast<uint32_t>(bit & 31));
       w_hi = __builtin_amdgcn_alignbit(a2, a1, static_cast<uint32_t>(bit & 31));
     };
-    if (wave == 0) {
-#pragma unroll
-      for (int i = 0; i < kGDeep; ++i) deep[i] = fetch(kGStat + i, xl);
-      words64(lane);
-    }
-    // count: a level's bits and the 1 bits before them, packed
+    if (wave == 0) words64(lane);
+    // count
     uint32_t tv = S, kmax = 0;               // kmax: levels with a share in this tile
     bool over = false;
     auto next = [&](uint32_t k, uint32_t ones) {   // level k's share tv is counted
@@ -600,22 +600,18 @@ __global__ __launch_bounds__(kGNT, 8) void k_gdecode(const GJob *jobs, uint32_t 
       tv = over ? 0u : zeros;
     };
     const uint32_t wave0 = kGWave * wave;    // the wave's first value
-    uint32_t share[kGStat] = {};
-#pragma unroll
-    for (int k = 0; k < kGStat; ++k) {
-      if (tv == 0) break;
-      share[k] = tv;
+    {
       uint32_t bits = 0, pc = 0, inc = 0, before;
-      if (wave0 < tv) {
-        bits = g_first(top[k], x, tv);
+      if (wave0 < S) {
+        bits = g_first(root, x, S);
         pc = __popc(bits);
         inc = g_incl_scan(pc);
       }
-      const uint32_t ones = g_waves(sm, k & 1, inc, &before);
-      top[k] = bits | ((before + inc - pc) << 16);
-      next(k, ones);
+      const uint32_t ones = g_waves(sm, 0, inc, &before);
+      root = bits | ((before + inc - pc) << 16);   // with the 1 bits before them
+      next(0, ones);
     }
-    // deeper levels still wider than a wave
+    // the levels wider than a wave
     uint32_t kw = kmax;
     while (tv > kGWave) {
       const uint32_t k = kmax;
@@ -626,19 +622,8 @@ __global__ __launch_bounds__(kGNT, 8) void k_gdecode(const GJob *jobs, uint32_t 
     }
     // one wave takes the rest, down and up again
     if (wave == 0 && tv) {
-      const uint32_t k0 = kmax;
-      const bool regs = k0 == kGStat;
+      const int k0 = static_cast<int>(kmax);
       auto total = [](uint32_t inc) { return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(inc), kGW - 1)); };
-      if (regs) {
-#pragma unroll
-        for (int i = 0; i < kGDeep; ++i) {
-          if (tv <= kGW) break;
-          const uint32_t bits = g_first(deep[i], xl, tv), pc = __popc(bits), inc = g_incl_scan(pc);
-          deep[i] = bits | ((inc - pc) << 16);
-          next(kGStat + i, total(inc));
-        }
-      }
-      const int kreg = static_cast<int>(kmax);   // levels from kGStat (regs) to here are in registers
       while (tv > kGW) {
         const uint32_t bits = g_first(fetch(kmax, xl), xl, tv);
         next(kmax, total(g_incl_scan(__popc(bits))));
@@ -673,22 +658,12 @@ __global__ __launch_bounds__(kGNT, 8) void k_gdecode(const GJob *jobs, uint32_t 
         reinterpret_cast<uint8_t *>(sm.lvl[kd & 1])[lane] = static_cast<uint8_t>(val + 1);
       }
       g_wave_sync();
-      for (int k = kd - 1; k >= kreg; --k) {
+      for (int k = kd - 1; k >= k0; --k) {
         const uint32_t m = sm.tv[k], bits = g_first(fetch(k, xl), xl, m), pc = __popc(bits);
         uint32_t o[4];
         g_merge16(sm, (k + 1) & 1, xl, bits, g_incl_scan(pc) - pc, o);
         g_put(sm, k, xl, m, o, out + t0);
         g_wave_sync();
-      }
-      if (regs) {
-#pragma unroll
-        for (int i = kGDeep - 1; i >= 0; --i) {
-          if (kGStat + i >= kreg) continue;
-          uint32_t o[4];
-          g_merge16(sm, (kGStat + i + 1) & 1, xl, deep[i] & 0xFFFF, deep[i] >> 16, o);
-          g_put(sm, kGStat + i, xl, sm.tv[kGStat + i], o, out + t0);
-          g_wave_sync();
-        }
       }
       if (lane == 0) {
         sm.depth = kmax;
@@ -701,7 +676,7 @@ __global__ __launch_bounds__(kGNT, 8) void k_gdecode(const GJob *jobs, uint32_t 
     __syncthreads();
     kmax = sm.depth;
     if (sm.err) break;
-    for (int k = static_cast<int>(kw) - 1; k >= kGStat; --k) {
+    for (int k = static_cast<int>(kw) - 1; k >= 1; --k) {
       const uint32_t m = sm.tv[k];
       uint32_t bits = 0, pc = 0, inc = 0, before;
       if (wave0 < m) {
@@ -717,22 +692,17 @@ __global__ __launch_bounds__(kGNT, 8) void k_gdecode(const GJob *jobs, uint32_t 
       }
       __syncthreads();
     }
-#pragma unroll
-    for (int k = kGStat - 1; k >= 0; --k) {
-      if (share[k] == 0) continue;
-      if (wave0 < share[k]) {
-        uint32_t o[4];
-        g_merge16(sm, (k + 1) & 1, x, top[k] & 0xFFFF, top[k] >> 16, o);
-        g_put(sm, k, x, share[k], o, out + t0);
-      }
-      if (k) __syncthreads();
+    if (wave0 < S) {
+      uint32_t o[4];
+      g_merge16(sm, 1, x, root & 0xFFFF, root >> 16, o);
+      g_put(sm, 0, x, S, o, out + t0);
     }
-    for (uint32_t k = tid; k < kmax; k += kGNT) sm.cur[k] += sm.tv[k];
+    for (uint32_t k = tid; k < kmax; k += NT) sm.cur[k] += sm.tv[k];
     __syncthreads();
   }
   // the whole block consumed every bitmap, and the last one had no 0 bit
   if (!sm.err)
-    for (uint32_t k = tid; k < K; k += kGNT)
+    for (uint32_t k = tid; k < K; k += NT)
       if (sm.cur[k] != sm.nk[k]) atomicCAS(&sm.err, 0u, static_cast<uint32_t>(PIVCO_E_CORRUPT));
   __syncthreads();
   if (tid == 0 && sm.err) gset_err(status, static_cast<int32_t>(sm.err));
@@ -837,7 +807,7 @@ pivco_status pivco_golomb_decode(const pivco_job *h_jobs, uint32_t count, int32_
                                  uint64_t ws_bytes, hipStream_t s) {
   if (count && (!h_jobs || !d_status || !d_ws)) return PIVCO_E_ARG;
   std::vector<GJob> jobs(count);
-  uint64_t blocks = 0;
+  uint64_t blocks = 0, longest = 0;
   for (uint32_t j = 0; j < count; ++j) {
     const pivco_job &jb = h_jobs[j];
     GJob &g = jobs[j];
@@ -869,6 +839,7 @@ pivco_status pivco_golomb_decode(const pivco_job *h_jobs, uint32_t count, int32_
     g.n_blocks = nb;
     g.block_size = bs;
     blocks += nb;
+    longest = std::max(longest, std::min<uint64_t>(n, bs));
   }
   // room for the batch's blocks, 8 bytes each, is part of the workspace that
   // callers were told to bring
@@ -886,9 +857,11 @@ pivco_status pivco_golomb_decode(const pivco_job *h_jobs, uint32_t count, int32_
       return PIVCO_E_DEVICE;
     hipLaunchKernelGGL(k_gstatus, dim3((count + 255) / 256), dim3(256), 0, s, dj, count, d_status);
   }
-  if (blocks)
-    hipLaunchKernelGGL(k_gdecode, dim3(static_cast<uint32_t>(blocks)), dim3(kGNT), 0, s, dj, count,
-                       static_cast<uint32_t>(blocks), d_status);
+  if (blocks) {
+    const bool wide = blocks <= kGFew && longest > kGNarrow;
+    hipLaunchKernelGGL(wide ? k_gdecode<1024> : k_gdecode<512>, dim3(static_cast<uint32_t>(blocks)),
+                       dim3(wide ? 1024 : 512), 0, s, dj, count, static_cast<uint32_t>(blocks), d_status);
+  }
   if (hipGetLastError() != hipSuccess) return PIVCO_E_DEVICE;
   if (hipStreamSynchronize(s) != hipSuccess) return PIVCO_E_DEVICE;
   return PIVCO_OK;
