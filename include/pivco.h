@@ -264,10 +264,15 @@ void pivco_autotune_cache_clear(void);
  * + 1), pad u16, the bitmap sizes n_1 .. n_{K-1} (u32), and the bitmaps
  * (ceil(n_k / 8) bytes each, LSB first, zero padding bits). */
 uint64_t pivco_golomb_encode_bound(uint64_t n, uint32_t block_size);
+/* Device workspace for the fastest encode: about 3 KB a block and 1 KB per 8192
+ * values of it (4.1 KB for blocks of up to 8192 values, 11 KB for 64 Ki, 131 KB
+ * for 1 Mi).  About 8.2 KB a block are enough whatever the blocks' size; with
+ * less room than this function's, longer parts of a block go to one workgroup. */
 uint64_t pivco_golomb_encode_workspace(uint64_t n, uint32_t block_size);
 /* Encodes n values at d_in (synchronous; the stream length in *h_out_len).
  * E_ARG on bad arguments (d_out must be 16-byte aligned), E_CAPACITY when
- * out_cap or ws_bytes is too small. */
+ * out_cap or ws_bytes is too small (the smaller of the workspace above and 8.2
+ * KB a block). */
 pivco_status pivco_golomb_encode(const void *d_in, uint64_t n, uint32_t block_size, void *d_out,
                                  uint64_t out_cap, uint64_t *h_out_len, void *d_ws, uint64_t ws_bytes,
                                  hipStream_t s);

@@ -153,9 +153,11 @@ __device__ __forceinline__ uint64_t g_block_scan(uint64_t v, uint64_t *part, uin
   return before + x - v;
 }
 
-// Row of slice blockIdx.x: entry k = its values >= k.
+// Row blockIdx.x, of `per` slices (see GWs; ONE: of one): entry k = their values
+// >= k.
+template <bool ONE>
 __global__ __launch_bounds__(kGEN) void k_ghist(const uint8_t *in, uint64_t n, uint32_t bs, uint32_t spb,
-                                                uint32_t *rows) {
+                                                uint32_t per, uint32_t *rows) {
   __shared__ uint32_t h[kGCopies][257];
   __shared__ uint64_t part[kGEW];
   const uint32_t tid = threadIdx.x;
@@ -163,16 +165,19 @@ __global__ __launch_bounds__(kGEN) void k_ghist(const uint8_t *in, uint64_t n, u
   __syncthreads();
   const uint64_t b = blockIdx.x / spb, sl = blockIdx.x % spb;
   const uint64_t b0 = b * bs, b1 = b0 + bs < n ? b0 + bs : n;
-  const uint64_t s0 = b0 + sl * kGES, s1 = s0 + kGES < b1 ? s0 + kGES : b1;
-  const uint32_t len = s0 < s1 ? static_cast<uint32_t>(s1 - s0) : 0u;
   uint32_t *hc = h[tid % kGCopies];
+  for (uint32_t u = 0; u < (ONE ? 1 : per); ++u) {
+    const uint64_t s0 = b0 + (ONE ? sl : sl * per + u) * kGES, s1 = s0 + kGES < b1 ? s0 + kGES : b1;
+    if (s0 >= s1) break;
+    const uint32_t len = static_cast<uint32_t>(s1 - s0);
 #pragma unroll
-  for (uint32_t t = 0; t < kGES / (4 * kGEN); ++t) {
-    const uint32_t i = 4 * (kGEN * t + tid);
-    const uint32_t w = g_load4(in + s0, i, len), have = g_have(i, len);
+    for (uint32_t t = 0; t < kGES / (4 * kGEN); ++t) {
+      const uint32_t i = 4 * (kGEN * t + tid);
+      const uint32_t w = g_load4(in + s0, i, len), have = g_have(i, len);
 #pragma unroll
-    for (uint32_t e = 0; e < 4; ++e)
-      if (e < have) atomicAdd(&hc[(w >> (8 * e)) & 255], 1u);
+      for (uint32_t e = 0; e < 4; ++e)
+        if (e < have) atomicAdd(&hc[(w >> (8 * e)) & 255], 1u);
+    }
   }
   __syncthreads();
   const uint32_t k = 255 - tid;              // a prefix sum over tid is a suffix sum over k
@@ -271,9 +276,12 @@ struct GEncSmem {
 // staged in LDS at the alignment of their stream words, one atomicOr per
 // value, and go out as words: the first and last word of a bitmap's share
 // may belong to a neighbour too and are ORed, the others are stored.  A slice
-// of long codes that does not fit the stage sets its bits in the stream.
+// of long codes that does not fit the stage sets its bits in the stream.  A
+// workgroup with several slices (ONE false) takes them in turn; the loop in every
+// workgroup took 172 us for 162.
+template <bool ONE>
 __global__ __launch_bounds__(kGEN, 5) void k_gsplit(const uint8_t *in, uint64_t n, uint32_t bs, uint32_t spb,
-                                                 const uint32_t *rows, const uint32_t *nk,
+                                                 uint32_t per, const uint32_t *rows, const uint32_t *nk,
                                                  const uint64_t *boff, const GBlk *blk, const uint64_t *off,
                                                  uint32_t nb, uint32_t *out, uint64_t out_cap) {
   __shared__ GEncSmem sm;
@@ -281,7 +289,6 @@ __global__ __launch_bounds__(kGEN, 5) void k_gsplit(const uint8_t *in, uint64_t 
   const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = __lane_id();
   const uint64_t b = blockIdx.x / spb, sl = blockIdx.x % spb;
   const uint64_t b0 = b * bs, b1 = b0 + bs < n ? b0 + bs : n;
-  const uint64_t s0 = b0 + sl * kGES, s1 = s0 + kGES < b1 ? s0 + kGES : b1;
   if (sl == 0) {                              // block header: whole words
     uint32_t *h = out + off[b] / 4;
     const uint32_t K = blk[b].K;
@@ -293,104 +300,109 @@ __global__ __launch_bounds__(kGEN, 5) void k_gsplit(const uint8_t *in, uint64_t 
       h[2 + tid] = nk[b * 256 + tid];
     }
   }
-  if (s0 >= s1) return;
   uint32_t *cur = sm.cur[wave];
+  uint32_t done = 0;                          // thread k: bits of level k in this workgroup's earlier slices
+  for (uint32_t u = 0; u < (ONE ? 1 : per); ++u) {
+    const uint64_t s0 = b0 + (ONE ? sl : sl * per + u) * kGES, s1 = s0 + kGES < b1 ? s0 + kGES : b1;
+    if (s0 >= s1) return;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) cur[kGW * e + lane] = 0;
-  g_wave_sync();
-  uint32_t vw[kGSteps];                       // 4 values a word
-  uint32_t pos[kGSteps][2];                   // two 16-bit positions a word
-  const uint32_t len = static_cast<uint32_t>(s1 - s0), i0 = wave * (256 * kGSteps) + 4 * lane;
-#pragma unroll
-  for (int t = 0; t < kGSteps; ++t) vw[t] = g_load4(in + s0, i0 + 256 * t, len);
-#pragma unroll
-  for (int t = 0; t < kGSteps; ++t) {
-    const uint32_t have = g_have(i0 + 256 * t, len);
-    int v[4];
-    uint32_t at[4], r[4] = {0, 0, 0, 0};
-#pragma unroll
-    for (uint32_t e = 0; e < 4; ++e) {
-      const uint32_t x = (vw[t] >> (8 * e)) & 255;
-      at[e] = cur[x];
-      v[e] = e < have ? static_cast<int>(x) : -1;
-    }
+    for (int e = 0; e < 4; ++e) cur[kGW * e + lane] = 0;
     g_wave_sync();
-    for (int k = 0; k < 256; ++k) {
-      uint64_t S[4];
+    uint32_t vw[kGSteps];                       // 4 values a word
+    uint32_t pos[kGSteps][2];                   // two 16-bit positions a word
+    const uint32_t len = static_cast<uint32_t>(s1 - s0), i0 = wave * (256 * kGSteps) + 4 * lane;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) S[e] = __ballot(v[e] >= k);
-      const uint32_t all = static_cast<uint32_t>(__popcll(S[0]) + __popcll(S[1]) + __popcll(S[2]) + __popcll(S[3]));
-      if (all == 0) break;
-      uint32_t c = 0;
+    for (int t = 0; t < kGSteps; ++t) vw[t] = g_load4(in + s0, i0 + 256 * t, len);
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        c = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(S[e] >> 32),
-                                      __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(S[e]), c));
+    for (int t = 0; t < kGSteps; ++t) {
+      const uint32_t have = g_have(i0 + 256 * t, len);
+      int v[4];
+      uint32_t at[4], r[4] = {0, 0, 0, 0};
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        r[e] = v[e] == k ? c : r[e];
-        c += v[e] >= k ? 1u : 0u;
+      for (uint32_t e = 0; e < 4; ++e) {
+        const uint32_t x = (vw[t] >> (8 * e)) & 255;
+        at[e] = cur[x];
+        v[e] = e < have ? static_cast<int>(x) : -1;
       }
-      if (lane == 0) atomicAdd(&cur[k], all);   // no value back: the loop does not wait for it
+      g_wave_sync();
+      for (int k = 0; k < 256; ++k) {
+        uint64_t S[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) S[e] = __ballot(v[e] >= k);
+        const uint32_t all = static_cast<uint32_t>(__popcll(S[0]) + __popcll(S[1]) + __popcll(S[2]) + __popcll(S[3]));
+        if (all == 0) break;
+        uint32_t c = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          c = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(S[e] >> 32),
+                                        __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(S[e]), c));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          r[e] = v[e] == k ? c : r[e];
+          c += v[e] >= k ? 1u : 0u;
+        }
+        if (lane == 0) atomicAdd(&cur[k], all);   // no value back: the loop does not wait for it
+      }
+      g_wave_sync();
+      pos[t][0] = (at[0] + r[0]) | (at[1] + r[1]) << 16;
+      pos[t][1] = (at[2] + r[2]) | (at[3] + r[3]) << 16;
+      // the words as they are, opaque: otherwise the unpacked values and
+      // positions of all steps are kept for the placing below, and spilled
+      asm volatile("" : "+v"(vw[t]), "+v"(pos[t][0]), "+v"(pos[t][1]));
     }
-    g_wave_sync();
-    pos[t][0] = (at[0] + r[0]) | (at[1] + r[1]) << 16;
-    pos[t][1] = (at[2] + r[2]) | (at[3] + r[3]) << 16;
-    // the words as they are, opaque: otherwise the unpacked values and
-    // positions of all steps are kept for the placing below, and spilled
-    asm volatile("" : "+v"(vw[t]), "+v"(pos[t][0]), "+v"(pos[t][1]));
-  }
-  __syncthreads();
-  uint32_t words = 0, sh = 0, cw[kGEW], cnt = 0;
-  uint64_t gb = 0;
-  {
-    const uint32_t k = tid;
+    __syncthreads();
+    uint32_t words = 0, sh = 0, cw[kGEW], cnt = 0;
+    uint64_t gb = 0;
+    {
+      const uint32_t k = tid;
 #pragma unroll
-    for (int w = 0; w < kGEW; ++w) { cw[w] = sm.cur[w][k]; cnt += cw[w]; }
-    if (cnt) {
-      gb = 8 * (off[b] + boff[b * 256 + k]) + rows[static_cast<uint64_t>(blockIdx.x) * 256 + k];
-      sh = static_cast<uint32_t>(gb & 31);
-      words = (sh + cnt + 31) / 32;
+      for (int w = 0; w < kGEW; ++w) { cw[w] = sm.cur[w][k]; cnt += cw[w]; }
+      if (cnt) {
+        gb = 8 * (off[b] + boff[b * 256 + k]) + rows[static_cast<uint64_t>(blockIdx.x) * 256 + k] + (ONE ? 0u : done);
+        sh = static_cast<uint32_t>(gb & 31);
+        words = (sh + cnt + 31) / 32;
+      }
     }
-  }
-  const uint32_t Ks = static_cast<uint32_t>(__syncthreads_count(cnt != 0));
-  uint64_t tot;
-  const uint32_t lw = static_cast<uint32_t>(g_block_scan<kGEN>(words, sm.part, &tot));
-  {
-    uint32_t x = 32 * lw + sh;                // below 2^23: at most 8192 * 256 staged bits and the edges
+    done += cnt;
+    const uint32_t Ks = static_cast<uint32_t>(__syncthreads_count(cnt != 0));
+    uint64_t tot;
+    const uint32_t lw = static_cast<uint32_t>(g_block_scan<kGEN>(words, sm.part, &tot));
+    {
+      uint32_t x = 32 * lw + sh;                // below 2^23: at most 8192 * 256 staged bits and the edges
 #pragma unroll
-    for (int w = 0; w < kGEW; ++w) { sm.cur[w][tid] = x; x += cw[w]; }
-    sm.gw[tid] = gb >> 5;
-    sm.lw[tid] = lw;
-    sm.nw[tid] = words;
-  }
-  const bool staged = tot <= kGStage;
-  if (staged)
-    for (uint32_t i = tid; i < tot; i += kGEN) sm.stage[i] = 0;
-  __syncthreads();
-#pragma unroll
-  for (int t = 0; t < kGSteps; ++t) {
-    const uint32_t have = g_have(i0 + 256 * t, len);
-#pragma unroll
-    for (uint32_t e = 0; e < 4; ++e) {
-      if (e >= have) continue;
-      const uint32_t k = (vw[t] >> (8 * e)) & 255;
-      const uint32_t x = cur[k] + ((pos[t][e >> 1] >> (16 * (e & 1))) & 0xFFFF);
-      if (staged) atomicOr(&sm.stage[x >> 5], 1u << (x & 31));
-      else atomicOr(&out[sm.gw[k] + ((x >> 5) - sm.lw[k])], 1u << (x & 31));
+      for (int w = 0; w < kGEW; ++w) { sm.cur[w][tid] = x; x += cw[w]; }
+      sm.gw[tid] = gb >> 5;
+      sm.lw[tid] = lw;
+      sm.nw[tid] = words;
     }
-  }
-  if (!staged) return;
-  __syncthreads();
-  for (uint32_t k = wave; k < Ks; k += kGEW) {
-    const uint32_t nw = sm.nw[k], l0 = sm.lw[k];
-    uint32_t *dst = out + sm.gw[k];
-    for (uint32_t j = lane; j < nw; j += kGW) {
-      const uint32_t w = sm.stage[l0 + j];
-      if (j == 0 || j == nw - 1) {
-        if (w) atomicOr(&dst[j], w);
-      } else {
-        dst[j] = w;
+    const bool staged = tot <= kGStage;
+    if (staged)
+      for (uint32_t i = tid; i < tot; i += kGEN) sm.stage[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < kGSteps; ++t) {
+      const uint32_t have = g_have(i0 + 256 * t, len);
+#pragma unroll
+      for (uint32_t e = 0; e < 4; ++e) {
+        if (e >= have) continue;
+        const uint32_t k = (vw[t] >> (8 * e)) & 255;
+        const uint32_t x = cur[k] + ((pos[t][e >> 1] >> (16 * (e & 1))) & 0xFFFF);
+        if (staged) atomicOr(&sm.stage[x >> 5], 1u << (x & 31));
+        else atomicOr(&out[sm.gw[k] + ((x >> 5) - sm.lw[k])], 1u << (x & 31));
+      }
+    }
+    if (!staged) continue;
+    __syncthreads();
+    for (uint32_t k = wave; k < Ks; k += kGEW) {
+      const uint32_t nw = sm.nw[k], l0 = sm.lw[k];
+      uint32_t *dst = out + sm.gw[k];
+      for (uint32_t j = lane; j < nw; j += kGW) {
+        const uint32_t w = sm.stage[l0 + j];
+        if (j == 0 || j == nw - 1) {
+          if (w) atomicOr(&dst[j], w);
+        } else {
+          dst[j] = w;
+        }
       }
     }
   }
@@ -492,8 +504,8 @@ __device__ __forceinline__ void g_put(GSmem<NT> &sm, int k, uint32_t x, uint32_t
 // below it need no way up: a lane per value follows it down, its place among
 // the values still alive a mbcnt of their ballot, each level's bits a 64-bit
 // scalar, loaded at the tile's start.  The other levels load their bits in each
-// direction.  (Ten levels' bits loaded up front and held in registers spilled 50 of
-// the 64 that 8 waves a SIMD leave: 1024 blocks of 64 Ki values of mean code length
+// direction.  (Ten levels' bits loaded up front and held in registers spilled 50
+// registers past the 64 that 8 waves a SIMD leave: 1024 blocks of 64 Ki values of mean code length
 // 2 took 143 us, 104 without; the call 203 and 165, of 16384 blocks of 4 Ki 363 and 259.)
 // Bound by the vector instructions of the levels (about 60 per 1024 values)
 // and the chain of the deep ones.
@@ -710,16 +722,17 @@ __global__ __launch_bounds__(NT, 8) void k_gdecode(const GJob *jobs, uint32_t nj
 
 inline uint64_t galign(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
 
-// Encode workspace: slice rows, then per block the bitmap sizes, their
-// places, the block's size and its offset.
+// Encode workspace: rows of `per` slices each, then per block the bitmap sizes,
+// their places, the block's size and its offset.
 struct GWs {
   uint64_t rows, nk, boff, blk, off, total;
-  uint32_t spb;           // slices per block
+  uint32_t per, spb;      // slices a row, rows per block
 };
-GWs gws_layout(uint64_t n, uint32_t bs) {
+GWs gws_layout(uint64_t n, uint32_t bs, uint32_t per) {
   GWs L{};
   const uint64_t nb = div_up(n, bs);
-  L.spb = static_cast<uint32_t>(div_up(std::min<uint64_t>(n, bs), kGES));
+  L.per = per;
+  L.spb = static_cast<uint32_t>(div_up(std::min<uint64_t>(n, bs), static_cast<uint64_t>(per) * kGES));
   uint64_t x = 0;
   L.rows = x; x = galign(x + nb * L.spb * 1024, 256);
   L.nk = x; x = galign(x + nb * 1024, 256);
@@ -728,6 +741,17 @@ GWs gws_layout(uint64_t n, uint32_t bs) {
   L.off = x; x = galign(x + 8 * (nb + 1), 256);
   L.total = x;
   return L;
+}
+
+// Bytes that have always been enough for an encode: the room of a list of the
+// block's bitmaps (24 bytes each, at most 256) and of its header beside its
+// counts.  A row per slice takes more than that for blocks past 24 Ki values, so
+// an encode with less room than pivco_golomb_encode_workspace asks for takes rows
+// of more slices.
+uint64_t gws_enough(uint64_t n, uint32_t bs) {
+  const uint64_t nb = div_up(n, bs);
+  return galign(nb * 1024 + 16, 256) + galign(nb * 256 * 24, 256) +
+         galign(kGHdr + 8 * (nb + 1) + nb * (12 + 4 * 255) + 64, 256);
 }
 
 }  // namespace
@@ -745,7 +769,7 @@ uint64_t pivco_golomb_encode_bound(uint64_t n, uint32_t block_size) {
 
 uint64_t pivco_golomb_encode_workspace(uint64_t n, uint32_t block_size) {
   if (block_size == 0) return 0;
-  return gws_layout(n, block_size).total;
+  return gws_layout(n, block_size, 1).total;
 }
 
 pivco_status pivco_golomb_encode(const void *d_in, uint64_t n, uint32_t block_size, void *d_out,
@@ -755,10 +779,11 @@ pivco_status pivco_golomb_encode(const void *d_in, uint64_t n, uint32_t block_si
     return PIVCO_E_ARG;
   const uint64_t nb64 = div_up(n, block_size);
   if (nb64 > 0xFFFFFFFFull) return PIVCO_E_ARG;
-  const GWs L = gws_layout(n, block_size);
-  if (!d_ws || ws_bytes < L.total) return PIVCO_E_CAPACITY;
+  GWs L = gws_layout(n, block_size, 1);
+  if (!d_ws || ws_bytes < std::min(L.total, gws_enough(n, block_size))) return PIVCO_E_CAPACITY;
+  while (L.spb > 1 && L.total > ws_bytes) L = gws_layout(n, block_size, 2 * L.per);
   if (nb64 * L.spb > 0x7FFFFFFFull) return PIVCO_E_ARG;
-  const uint32_t nb = static_cast<uint32_t>(nb64), spb = L.spb;
+  const uint32_t nb = static_cast<uint32_t>(nb64), spb = L.spb, per = L.per;
   const uint8_t *in = static_cast<const uint8_t *>(d_in);
   uint8_t *ws = static_cast<uint8_t *>(d_ws);
   uint32_t *rows = reinterpret_cast<uint32_t *>(ws + L.rows), *nk = reinterpret_cast<uint32_t *>(ws + L.nk);
@@ -766,7 +791,8 @@ pivco_status pivco_golomb_encode(const void *d_in, uint64_t n, uint32_t block_si
   GBlk *blk = reinterpret_cast<GBlk *>(ws + L.blk);
   uint32_t *out = static_cast<uint32_t *>(d_out);
   if (nb) {
-    hipLaunchKernelGGL(k_ghist, dim3(nb * spb), dim3(kGEN), 0, s, in, n, block_size, spb, rows);
+    hipLaunchKernelGGL(per == 1 ? k_ghist<true> : k_ghist<false>, dim3(nb * spb), dim3(kGEN), 0, s, in, n, block_size,
+                       spb, per, rows);
     hipLaunchKernelGGL(k_gprefix, dim3(nb), dim3(kGEN), 0, s, rows, spb, nk, boff, blk);
   }
   hipLaunchKernelGGL(k_gscan, dim3(1), dim3(kGScanNT), 0, s, blk, nb, off);
@@ -775,8 +801,8 @@ pivco_status pivco_golomb_encode(const void *d_in, uint64_t n, uint32_t block_si
   hipLaunchKernelGGL(k_ghead, dim3(static_cast<uint32_t>(std::min<uint64_t>(2048, div_up(most, 2048)))),
                      dim3(256), 0, s, off, nb, n, block_size, out, out_cap);
   if (nb)
-    hipLaunchKernelGGL(k_gsplit, dim3(nb * spb), dim3(kGEN), 0, s, in, n, block_size, spb, rows, nk, boff, blk,
-                       off, nb, out, out_cap);
+    hipLaunchKernelGGL(per == 1 ? k_gsplit<true> : k_gsplit<false>, dim3(nb * spb), dim3(kGEN), 0, s, in, n,
+                       block_size, spb, per, rows, nk, boff, blk, off, nb, out, out_cap);
   if (hipGetLastError() != hipSuccess) return PIVCO_E_DEVICE;
   uint64_t total = 0;
   if (hipMemcpyAsync(&total, off + nb, 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
