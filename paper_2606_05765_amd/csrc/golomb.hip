@@ -754,6 +754,9 @@ uint64_t gws_enough(uint64_t n, uint32_t bs) {
          galign(kGHdr + 8 * (nb + 1) + nb * (12 + 4 * 255) + 64, 256);
 }
 
+// Workgroups of kGEN threads that one launch may have: fewer than 2^32 threads.
+constexpr uint64_t kGMaxGrid = ((1ull << 32) - 1) / kGEN;
+
 }  // namespace
 }  // namespace pivco
 
@@ -781,8 +784,9 @@ pivco_status pivco_golomb_encode(const void *d_in, uint64_t n, uint32_t block_si
   if (nb64 > 0xFFFFFFFFull) return PIVCO_E_ARG;
   GWs L = gws_layout(n, block_size, 1);
   if (!d_ws || ws_bytes < std::min(L.total, gws_enough(n, block_size))) return PIVCO_E_CAPACITY;
-  while (L.spb > 1 && L.total > ws_bytes) L = gws_layout(n, block_size, 2 * L.per);
+  while (L.spb > 1 && (L.total > ws_bytes || nb64 * L.spb > kGMaxGrid)) L = gws_layout(n, block_size, 2 * L.per);
   if (nb64 * L.spb > 0x7FFFFFFFull) return PIVCO_E_ARG;
+  if (nb64 > kGMaxGrid) return PIVCO_E_DEVICE;       // no launch has a workgroup for every block
   const uint32_t nb = static_cast<uint32_t>(nb64), spb = L.spb, per = L.per;
   const uint8_t *in = static_cast<const uint8_t *>(d_in);
   uint8_t *ws = static_cast<uint8_t *>(d_ws);
@@ -794,6 +798,7 @@ pivco_status pivco_golomb_encode(const void *d_in, uint64_t n, uint32_t block_si
     hipLaunchKernelGGL(per == 1 ? k_ghist<true> : k_ghist<false>, dim3(nb * spb), dim3(kGEN), 0, s, in, n, block_size,
                        spb, per, rows);
     hipLaunchKernelGGL(k_gprefix, dim3(nb), dim3(kGEN), 0, s, rows, spb, nk, boff, blk);
+    if (hipGetLastError() != hipSuccess) return PIVCO_E_DEVICE;   // the rest reads what these write
   }
   hipLaunchKernelGGL(k_gscan, dim3(1), dim3(kGScanNT), 0, s, blk, nb, off);
   // the stream is at most the bound: 8 words a thread when it is that large
