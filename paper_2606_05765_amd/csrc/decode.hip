@@ -2298,21 +2298,14 @@ __device__ void load_tile(const JobDev &J, const ParsedBlock *rec, const uint2 *
 }
 
 // Persistent merge: a workgroup takes items from the queue (largest first) --
-// whole blocks, or tiles of split blocks -- looking one item ahead.
-// C::ONCE: blocks that below_root_fits are merged that way; a kernel of its own,
-// for batches of them, since the path costs other blocks 4% (574 against 595
-// us a 256 MiB Zipf v2 batch with no such block in it).  `single`
+// whole blocks, or tiles of split blocks -- looking one item ahead.  `single`
 // selects the item source: kQueueItems (the persistent queue), kGridItems
 // (workgroup b decodes item b and exits: one non-persistent launch with a
 // workgroup per item), or an item index (one item, one workgroup).
+// merge_begin takes the first item; a barrier, then merge_items.
 template <class C>
-__global__ __launch_bounds__(C::NT) void k_merge(const JobDev *jobs, const uint2 *items,
-                                                  const ParsedBlock *recs,
-                                                  const TiledBlock *tiled, const uint2 *tab,
-                                                  uint32_t n_items, Counters *ctr,
-                                                  const uint32_t *scratch, uint64_t scratch_words,
-                                                  int32_t single) {
-  __shared__ MergeSmem<C> sm;
+__device__ __forceinline__ void merge_begin(const uint2 *items, const ParsedBlock *recs, uint32_t n_items,
+                                            Counters *ctr, int32_t single, MergeSmem<C> &sm) {
   const int tid = threadIdx.x;
   for (int i = tid; i < 256; i += C::NT) sm.leafrow[i] = static_cast<uint32_t>(i) * 0x01010101u;
   init_sel<C>(sm);
@@ -2327,7 +2320,14 @@ __global__ __launch_bounds__(C::NT) void k_merge(const JobDev *jobs, const uint2
       sm.nxt = load_ext(recs + rt.x);
     }
   }
-  lds_barrier();
+}
+
+template <class C>
+__device__ __forceinline__ void merge_items(const JobDev *jobs, const uint2 *items, const ParsedBlock *recs,
+                                            const TiledBlock *tiled, const uint2 *tab, uint32_t n_items,
+                                            Counters *ctr, const uint32_t *scratch, uint64_t scratch_words,
+                                            int32_t single, MergeSmem<C> &sm) {
+  const int tid = threadIdx.x;
   for (;;) {
     const uint32_t it = sm.item;
     if (it >= n_items) break;
@@ -2357,6 +2357,80 @@ __global__ __launch_bounds__(C::NT) void k_merge(const JobDev *jobs, const uint2
     decode_block<C>(J, ext, whole ? kWholeBlock : rt.y & 255, scratch, scratch_words, sm, la);
     lds_barrier();
   }
+}
+
+template <class C>
+__global__ __launch_bounds__(C::NT) void k_merge(const JobDev *jobs, const uint2 *items,
+                                                  const ParsedBlock *recs,
+                                                  const TiledBlock *tiled, const uint2 *tab,
+                                                  uint32_t n_items, Counters *ctr,
+                                                  const uint32_t *scratch, uint64_t scratch_words,
+                                                  int32_t single) {
+  __shared__ MergeSmem<C> sm;
+  merge_begin<C>(items, recs, n_items, ctr, single, sm);
+  lds_barrier();
+  merge_items<C>(jobs, items, recs, tiled, tab, n_items, ctr, scratch, scratch_words, single, sm);
+}
+
+using Cfg0 = MergeCfg<1024, 32768, 57344, 16, 2>;
+using Cfg0Once = MergeCfg<1024, 32768, 57344, 16, 2, true>;
+
+// Whether Cfg0Once merges the levels of item it below its root once; *n gets its
+// symbols (2^24 at most).  Every field is read before any is looked at: one trip
+// to memory.
+__device__ __forceinline__ bool merged_once(uint2 it, const ParsedBlock *recs, uint32_t *n) {
+  const BlockExt e = load_ext(recs + it.x);
+  const BlockHdr &r = recs[it.x].h;
+  BlockHdr h;
+  h.n = r.n;
+  h.mode = r.mode;
+  h.maxlen = r.maxlen;
+  h.below = r.below;
+  asm volatile("" ::"v"(h.n), "v"(h.mode), "v"(h.maxlen), "v"(h.below));
+  const bool whole = it.y == kWholeBlock;
+  *n = !whole ? kTileOut : h.n < (1u << 24) ? h.n : 1u << 24;
+  return whole && h.mode == 0 && block_resident<Cfg0Once>(e) && below_root_fits<Cfg0Once>(h);
+}
+
+// For batches whose sizes allow skewed blocks (skewed_job): the sizes do not tell
+// them from others of few bits a symbol, so a workgroup looks at its one item,
+// or at 64 of the queue's, and takes Cfg0Once where the blocks that it merges once
+// hold at least half of their symbols, else Cfg0: the path costs other blocks up
+// to 6% (256 MiB of 4 equal symbols in blocks of 64 Ki, v2 trees: 201 us with
+// Cfg0, 213 with Cfg0Once).  One kernel holds both, so that nothing is launched
+// twice; the look runs beside the first item's loads.  256 MiB with one symbol at
+// 0.9 in blocks of 128 Ki 171 us as with Cfg0Once alone, at 0.97 in blocks of 64 Ki,
+// tANS, 386 for 382.  (Counted by the plan kernel, an atomic per block, 2048
+// blocks took 20 us more.)
+__global__ __launch_bounds__(Cfg0::NT) void k_merge_either(const JobDev *jobs, const uint2 *items,
+                                                           const ParsedBlock *recs, const TiledBlock *tiled,
+                                                           const uint2 *tab, uint32_t n_items, Counters *ctr,
+                                                           const uint32_t *scratch, uint64_t scratch_words,
+                                                           int32_t single) {
+  __shared__ union {
+    MergeSmem<Cfg0> each;
+    MergeSmem<Cfg0Once> once;
+  } sm;
+  __shared__ uint32_t pick;
+  static_assert(sizeof(sm.each) == sizeof(sm.once), "what merge_begin wrote is either's");
+  merge_begin<Cfg0>(items, recs, n_items, ctr, single, sm.each);
+  if (threadIdx.x / kWave == 1) {            // beside the first item's loads
+    const uint32_t lane = lane_id();
+    const uint32_t looks = single == kQueueItems ? (n_items < kWave ? n_items : static_cast<uint32_t>(kWave)) : 1u;
+    const uint32_t at = single >= 0            ? static_cast<uint32_t>(single)
+                        : single == kGridItems ? blockIdx.x
+                                               : static_cast<uint32_t>(static_cast<uint64_t>(lane) * n_items / looks);
+    uint32_t n = 0;
+    bool o = false;
+    if (lane < looks && at < n_items) o = merged_once(items[at], recs, &n);
+    const uint32_t all = wave_incl_scan(n), of = wave_incl_scan(o ? n : 0u);
+    if (lane == kWave - 1) pick = 2ull * of >= all ? 1u : 0u;
+  }
+  lds_barrier();
+  if (pick)
+    merge_items<Cfg0Once>(jobs, items, recs, tiled, tab, n_items, ctr, scratch, scratch_words, single, sm.once);
+  else
+    merge_items<Cfg0>(jobs, items, recs, tiled, tab, n_items, ctr, scratch, scratch_words, single, sm.each);
 }
 
 // Bits [b0, b1) of a 32-bit word whose first bit is bit wb.
@@ -3029,9 +3103,7 @@ __global__ __launch_bounds__(kTdNT) void k_topdown(const JobDev *jobs, const uin
 // host-side launch table
 // ---------------------------------------------------------------------------
 // Merge-kernel variants: workgroup size, tile of a whole block, resident
-// block bytes, outputs per task, windows per wave step.
-using Cfg0 = MergeCfg<1024, 32768, 57344, 16, 2>;
-using Cfg0Once = MergeCfg<1024, 32768, 57344, 16, 2, true>;   // variant 0 for skewed batches
+// block bytes, outputs per task, windows per wave step (variant 0: Cfg0).
 using Cfg1 = MergeCfg<1024, 32768, 56320, 8, 2>;
 using Cfg2 = MergeCfg<1024, 32768, 55296, 32, 1>;
 using Cfg3 = MergeCfg<1024, 16384, 57344, 16, 2>;
@@ -3097,7 +3169,11 @@ hipError_t launch_merge(uint32_t variant, uint32_t grid, hipStream_t s, const Jo
   const ParsedBlock *r = static_cast<const ParsedBlock *>(recs);
   switch (variant) {
     case 0:
-      if (skewed) return launch_merge_t<Cfg0Once>(dim3(grid), s, jobs, items, r, tiled, tab, n_items, ctr, scratch, scratch_words, single);
+      if (skewed) {
+        hipLaunchKernelGGL(k_merge_either, dim3(grid), dim3(Cfg0::NT), 0, s, jobs, items, r, tiled, tab, n_items, ctr,
+                           scratch, scratch_words, single);
+        return hipGetLastError();
+      }
       return launch_merge_t<Cfg0>(dim3(grid), s, jobs, items, r, tiled, tab, n_items, ctr, scratch, scratch_words, single);
     case 1: return launch_merge_t<Cfg1>(dim3(grid), s, jobs, items, r, tiled, tab, n_items, ctr, scratch, scratch_words, single);
     case 2: return launch_merge_t<Cfg2>(dim3(grid), s, jobs, items, r, tiled, tab, n_items, ctr, scratch, scratch_words, single);

@@ -249,12 +249,12 @@ hipError_t launch_merge(uint32_t variant, uint32_t grid, hipStream_t s, const Jo
                         const TiledBlock *tiled, const uint2 *tab, uint32_t n_items,
                         Counters *ctr, const uint32_t *scratch, uint64_t scratch_words,
                         int32_t single, bool skewed);
-// Whether a job's blocks count as skewed for launch_merge: whole blocks of
-// more than one tile that take fewer than 3 bits a symbol, stream and decoded
-// bitmaps together (with one symbol at 0.9 and rANS 2.4 bits; the merge kernel
-// itself looks at each block's root).  A batch with at least half its symbols
-// in such jobs gets the kernel that merges the levels below the root once per
-// block: 379 -> 151 us on 2048 blocks of 128 KiB.
+// Whether a job's blocks may be skewed: whole blocks of more than one tile that
+// take fewer than 3 bits a symbol, stream and decoded bitmaps together (with one
+// symbol at 0.9 and rANS 2.4 bits).  For a batch with at least half its symbols in
+// such jobs (skewed) variant 0 looks at the blocks' roots and merges the levels
+// below them once per block where these fit a tile (k_merge_either): 379 -> 151
+// us on 2048 blocks of 128 KiB.
 inline bool skewed_job(uint64_t n_total, uint64_t in_len, uint64_t ans_words, uint32_t block_size, uint64_t split_min) {
   return block_size > kTileOut && n_total > kTileOut &&
          tiles_of_block(std::min<uint64_t>(block_size, n_total), split_min) == 0 &&
