@@ -1740,25 +1740,21 @@ __device__ __forceinline__ bool below_root_fits(const BlockHdr &h) {
   return h.n > static_cast<uint32_t>(C::T) && h.below <= static_cast<uint32_t>(C::T) && h.maxlen >= 2;
 }
 
-// The root of such a block over all its outputs, its children's sequences
-// complete in level buffer 1: windows of 64 tasks, wave by wave.
+// The root of such a block over all its outputs, its one internal child's
+// sequence complete in level buffer 1 (two would hold all n > T symbols below
+// the root): windows of 64 tasks, wave by wave.
 template <class C>
 __device__ void merge_root_block(MergeSmem<C> &sm, uint32_t n, uint8_t *out) {
   const uint32_t lane = item_tid() & (kWave - 1);
   const NodeTab &t = sm.pb.t;
   constexpr int G = C::K / 4;
   const uint8_t *lds = reinterpret_cast<const uint8_t *>(&sm);
-  // the children: a leaf's constant row (rank times 0), or the sequence in
-  // the level buffer (the second node's after the first, rounded up)
-  uint32_t base[2], mul[2], off = 0;
-#pragma unroll
-  for (int bb = 0; bb < 2; ++bb) {
-    const uint32_t c = t.child[0][bb];
-    mul[bb] = (c & 0x8000) ? 0u : 1u;
-    base[bb] = static_cast<uint32_t>((c & 0x8000) ? reinterpret_cast<const uint8_t *>(&sm.leafrow[c & 255]) - lds
-                                                  : reinterpret_cast<const uint8_t *>(sm.lvl[1]) - lds + off);
-    if (!(c & 0x8000)) off += (t.nv[c] + C::K - 1) & ~(C::K - 1u);
-  }
+  // the children: a leaf's constant row (rank times 0), or the sequence
+  const uint32_t c0 = __builtin_amdgcn_readfirstlane(t.child[0][0]), c1 = __builtin_amdgcn_readfirstlane(t.child[0][1]);
+  const uint32_t seq = static_cast<uint32_t>(reinterpret_cast<const uint8_t *>(sm.lvl[1]) - lds);
+  const uint32_t rows = static_cast<uint32_t>(reinterpret_cast<const uint8_t *>(sm.leafrow) - lds);
+  const uint32_t base[2] = {(c0 & 0x8000) ? rows + 4 * (c0 & 255) : seq, (c1 & 0x8000) ? rows + 4 * (c1 & 255) : seq};
+  const uint32_t mul[2] = {(c0 & 0x8000) ? 0u : 1u, (c1 & 0x8000) ? 0u : 1u};
   const uint32_t x0 = sm.abit[0], a0 = sm.r0[0];
   const uint32_t ntask = (n + C::K - 1) / C::K, nwin = (ntask + kWave - 1) / kWave;
   for (uint32_t w = wave_id(); w < nwin; w += C::NW) {
