@@ -244,7 +244,7 @@ void pivco_batch_plan_destroy(pivco_batch_plan *p);
  * CU) when the jobs have rANS nodes; each candidate is the best of three
  * timed batched decodes.  The choice is cached per device architecture and
  * workload bucket (work items per CU, mean symbols per item, share of tile
- * items, rANS present): a later call for the same bucket returns it without
+ * items, rANS present, skewed blocks): a later call for the same bucket returns it without
  * timing.  Synchronous. */
 pivco_status pivco_autotune(const pivco_job *h_jobs, uint32_t count, int32_t *d_status,
                             void *d_ws, uint64_t ws_bytes, hipStream_t s, pivco_tune *out);

@@ -352,14 +352,16 @@ pivco_status prepare(const pivco_job *h_jobs, uint32_t count, int32_t *d_status,
 namespace {
 
 // Autotuner cache: one choice per device architecture and workload bucket
-// (items per CU, mean symbols per item, share of tile items, rANS present),
-// so that batches of the same shape reuse a configuration without timing.
+// (items per CU, mean symbols per item, share of tile items, rANS present, and
+// which kernel variant 0 is for the batch: 0 that of all batches, 1 and 2 the two
+// ways of a skewed one), so that batches of the same shape reuse a configuration
+// without timing.
 struct TuneKey {
   std::string arch;
-  uint32_t items_per_cu, mean_log2, tile_share, rans;
+  uint32_t items_per_cu, mean_log2, tile_share, rans, kernel;
   bool operator<(const TuneKey &o) const {
-    return std::tie(arch, items_per_cu, mean_log2, tile_share, rans) <
-           std::tie(o.arch, o.items_per_cu, o.mean_log2, o.tile_share, o.rans);
+    return std::tie(arch, items_per_cu, mean_log2, tile_share, rans, kernel) <
+           std::tie(o.arch, o.items_per_cu, o.mean_log2, o.tile_share, o.rans, o.kernel);
   }
 };
 
@@ -395,6 +397,7 @@ TuneKey tune_key(const HostPlan &p) {
   k.mean_log2 = log2_bucket(symbols / ni + 1);
   k.tile_share = static_cast<uint32_t>(4 * tiles / ni);   // quarters
   k.rans = p.w.ritems.empty() ? 0u : 1u;
+  k.kernel = 0;
   return k;
 }
 
@@ -598,7 +601,19 @@ pivco_status pivco_autotune(const pivco_job *h_jobs, uint32_t count, int32_t *d_
   if (st) return st;
   pivco_tune best = default_tune(static_cast<uint32_t>(p.w.items.size()), p.chunk_cap);
   if (p.w.items.empty()) { *out = best; return PIVCO_OK; }
-  const TuneKey key = tune_key(p);
+  TuneKey key = tune_key(p);
+  if (p.skewed) {                        // the blocks' roots say which way the merge takes
+    const Dev d = dev_ptrs(p, d_ws);
+    uint32_t once = 0;
+    if ((st = enqueue_init(p, d_ws, d_status, false, s))) return st;
+    if (launch_plan(s, d.jobs, d.blocks, static_cast<uint32_t>(p.w.blocks.size()), d.recs, d.ctr, d.chunks,
+                    p.chunk_cap) != hipSuccess ||
+        launch_look(s, d.items, d.recs, static_cast<uint32_t>(p.w.items.size()), d.ctr) != hipSuccess ||
+        hipMemcpyAsync(&once, &d.ctr->once, 4, hipMemcpyDeviceToHost, s) != hipSuccess ||
+        hipStreamSynchronize(s) != hipSuccess)
+      return PIVCO_E_DEVICE;
+    key.kernel = 1 + once;
+  }
   {
     std::lock_guard<std::mutex> lk(tune_cache_mu());
     auto it = tune_cache().find(key);

@@ -2802,6 +2802,18 @@ __global__ __launch_bounds__(kTilesNT) void k_tiles(const JobDev *jobs, const Ti
   if (tid == 0 && sm.err) set_err(J.status, sm.err);
 }
 
+// What k_merge_either finds for the queue (its look at 64 items), for the
+// autotuner.
+__global__ __launch_bounds__(kWave) void k_look(const uint2 *items, const ParsedBlock *recs, uint32_t n_items,
+                                                Counters *ctr) {
+  const uint32_t lane = lane_id(), looks = n_items < kWave ? n_items : static_cast<uint32_t>(kWave);
+  uint32_t n = 0;
+  bool o = false;
+  if (lane < looks) o = merged_once(items[static_cast<uint64_t>(lane) * n_items / looks], recs, &n);
+  const uint32_t all = wave_incl_scan(n), of = wave_incl_scan(o ? n : 0u);
+  if (lane == kWave - 1) ctr->once = 2ull * of >= all ? 1u : 0u;
+}
+
 // Plan: one wave per work item parses and validates the block's header from
 // a copy of its first bytes in LDS (offsets, code lengths, canonical tree,
 // node table, symbol counts, body offsets, padding) and writes the result as
@@ -3235,6 +3247,12 @@ int rans_occupancy() {
   int nb = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_rans, kRansNT, 0) != hipSuccess) return 1;
   return nb > 0 ? nb : 1;
+}
+
+hipError_t launch_look(hipStream_t s, const uint2 *items, const void *recs, uint32_t n_items, Counters *ctr) {
+  if (n_items == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_look, dim3(1), dim3(kWave), 0, s, items, static_cast<const ParsedBlock *>(recs), n_items, ctr);
+  return hipGetLastError();
 }
 
 hipError_t launch_init(hipStream_t s, Counters *ctr, int32_t *status, const int32_t *status0,

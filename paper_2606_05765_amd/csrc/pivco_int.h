@@ -88,8 +88,10 @@ struct Counters {
   uint32_t rans_next;      // next pair of rANS chunks to decode
   uint32_t rans_chunks;    // entropy-coded chunks listed by the plan kernel
   uint32_t fse_next;       // next pair of chunks for the tANS kernel
-  uint32_t pad[12];
+  uint32_t once;           // launch_look's answer
+  uint32_t pad[11];
 };
+static_assert(sizeof(Counters) == 64, "Counters layout");
 
 // One entropy-coded chunk of a node's bitmap, listed by the plan kernel:
 // where its coded data is, where its decoded bits go, how many.  A binary
@@ -249,6 +251,9 @@ hipError_t launch_merge(uint32_t variant, uint32_t grid, hipStream_t s, const Jo
                         const TiledBlock *tiled, const uint2 *tab, uint32_t n_items,
                         Counters *ctr, const uint32_t *scratch, uint64_t scratch_words,
                         int32_t single, bool skewed);
+// After launch_plan: ctr->once says which of its two ways launch_merge takes for
+// the queue of a skewed batch (1: levels below the roots merged once).
+hipError_t launch_look(hipStream_t s, const uint2 *items, const void *recs, uint32_t n_items, Counters *ctr);
 // Whether a job's blocks may be skewed: whole blocks of more than one tile that
 // take fewer than 3 bits a symbol, stream and decoded bitmaps together (with one
 // symbol at 0.9 and rANS 2.4 bits).  For a batch with at least half its symbols in
