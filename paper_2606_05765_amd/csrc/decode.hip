@@ -1025,7 +1025,8 @@ __global__ __launch_bounds__(kFseNT) void k_fse(const JobDev *jobs, const Parsed
 // ---------------------------------------------------------------------------
 // Kernel: bottom-up merge decode
 // ---------------------------------------------------------------------------
-template <int NT_, int T_, int BODY_, int K_, int LOCK_, bool ONCE_ = false>
+// (KERNEL sets apart the instances of the kernel that holds two of them.)
+template <int NT_, int T_, int BODY_, int K_, int LOCK_, int KERNEL_ = 0, bool ONCE_ = false>
 struct MergeCfg {
   static constexpr int NT = NT_;
   static constexpr int T = T_;                        // output symbols per tile
@@ -2293,12 +2294,7 @@ __device__ void load_tile(const JobDev &J, const ParsedBlock *rec, const uint2 *
     sm.abit[tid] = sm.tv[tid] ? 128u * stg + static_cast<uint32_t>(gb - 8 * a16) : 0u;
 }
 
-// Persistent merge: a workgroup takes items from the queue (largest first) --
-// whole blocks, or tiles of split blocks -- looking one item ahead.  `single`
-// selects the item source: kQueueItems (the persistent queue), kGridItems
-// (workgroup b decodes item b and exits: one non-persistent launch with a
-// workgroup per item), or an item index (one item, one workgroup).
-// merge_begin takes the first item; a barrier, then merge_items.
+// The tables of the merge and the first item; the caller's barrier follows.
 template <class C>
 __device__ __forceinline__ void merge_begin(const uint2 *items, const ParsedBlock *recs, uint32_t n_items,
                                             Counters *ctr, int32_t single, MergeSmem<C> &sm) {
@@ -2318,6 +2314,57 @@ __device__ __forceinline__ void merge_begin(const uint2 *items, const ParsedBloc
   }
 }
 
+// Persistent merge: a workgroup takes items from the queue (largest first) --
+// whole blocks, or tiles of split blocks -- looking one item ahead.  `single`
+// selects the item source: kQueueItems (the persistent queue), kGridItems
+// (workgroup b decodes item b and exits: one non-persistent launch with a
+// workgroup per item), or an item index (one item, one workgroup).
+template <class C>
+__global__ __launch_bounds__(C::NT) void k_merge(const JobDev *jobs, const uint2 *items,
+                                                  const ParsedBlock *recs,
+                                                  const TiledBlock *tiled, const uint2 *tab,
+                                                  uint32_t n_items, Counters *ctr,
+                                                  const uint32_t *scratch, uint64_t scratch_words,
+                                                  int32_t single) {
+  __shared__ MergeSmem<C> sm;
+  const int tid = threadIdx.x;
+  merge_begin<C>(items, recs, n_items, ctr, single, sm);
+  lds_barrier();
+  for (;;) {
+    const uint32_t it = sm.item;
+    if (it >= n_items) break;
+    const uint2 rt = sm.nxt_item;
+    const BlockExt ext = sm.nxt;
+    lds_barrier();                   // the look-ahead slots are rewritten below
+    // look ahead (thread 64, in a wave that is idle while wave 0 computes
+    // the first tile's shares): take the next item now; its extent and
+    // stream are read while this item is decoded, and published to LDS
+    // before the merge (or when the item ends early)
+    Lookahead la{n_items, make_uint2(0, 0), BlockExt{}, nullptr, nullptr};
+    if (tid == kWave && single == kQueueItems) la.item = atomicAdd(&ctr->merge_next, 1u);
+    const JobDev &J = jobs[ext.job];
+    const bool whole = rt.y == kWholeBlock;
+    if (whole) {
+      load_block<C>(J, recs + rt.x, ext, scratch, scratch_words, sm);
+    } else {
+      const TiledBlock tb = tiled[rt.y >> 8];
+      load_tile<C>(J, recs + rt.x, tab + tb.tab, rt.y & 255, scratch, scratch_words, sm);
+    }
+    if (tid == kWave && la.item < n_items) {
+      la.rt = items[la.item];
+      la.ext = load_ext(recs + la.rt.x);
+      la.in = la.ext.err || la.rt.y != kWholeBlock ? nullptr : la.ext.in;
+      la.rec = reinterpret_cast<const uint8_t *>(recs + la.rt.x);
+    }
+    decode_block<C>(J, ext, whole ? kWholeBlock : rt.y & 255, scratch, scratch_words, sm, la);
+    lds_barrier();
+  }
+}
+
+// k_merge's loop, for the kernel that holds it for two configurations.  (k_merge
+// keeps its own: with the loop as a function of both, or a configuration in
+// both, the compiler's choices for one kernel changed the other, 256 MiB Zipf v2
+// 565 -> 585 us.)
 template <class C>
 __device__ __forceinline__ void merge_items(const JobDev *jobs, const uint2 *items, const ParsedBlock *recs,
                                             const TiledBlock *tiled, const uint2 *tab, uint32_t n_items,
@@ -2355,21 +2402,10 @@ __device__ __forceinline__ void merge_items(const JobDev *jobs, const uint2 *ite
   }
 }
 
-template <class C>
-__global__ __launch_bounds__(C::NT) void k_merge(const JobDev *jobs, const uint2 *items,
-                                                  const ParsedBlock *recs,
-                                                  const TiledBlock *tiled, const uint2 *tab,
-                                                  uint32_t n_items, Counters *ctr,
-                                                  const uint32_t *scratch, uint64_t scratch_words,
-                                                  int32_t single) {
-  __shared__ MergeSmem<C> sm;
-  merge_begin<C>(items, recs, n_items, ctr, single, sm);
-  lds_barrier();
-  merge_items<C>(jobs, items, recs, tiled, tab, n_items, ctr, scratch, scratch_words, single, sm);
-}
 
 using Cfg0 = MergeCfg<1024, 32768, 57344, 16, 2>;
-using Cfg0Once = MergeCfg<1024, 32768, 57344, 16, 2, true>;
+using Cfg0Each = MergeCfg<1024, 32768, 57344, 16, 2, 1>;
+using Cfg0Once = MergeCfg<1024, 32768, 57344, 16, 2, 1, true>;
 
 // Whether Cfg0Once merges the levels of item it below its root once; *n gets its
 // symbols (2^24 at most).  Every field is read before any is looked at: one trip
@@ -2398,18 +2434,18 @@ __device__ __forceinline__ bool merged_once(uint2 it, const ParsedBlock *recs, u
 // 0.9 in blocks of 128 Ki 171 us as with Cfg0Once alone, at 0.97 in blocks of 64 Ki,
 // tANS, 386 for 382.  (Counted by the plan kernel, an atomic per block, 2048
 // blocks took 20 us more.)
-__global__ __launch_bounds__(Cfg0::NT) void k_merge_either(const JobDev *jobs, const uint2 *items,
+__global__ __launch_bounds__(Cfg0Each::NT) void k_merge_either(const JobDev *jobs, const uint2 *items,
                                                            const ParsedBlock *recs, const TiledBlock *tiled,
                                                            const uint2 *tab, uint32_t n_items, Counters *ctr,
                                                            const uint32_t *scratch, uint64_t scratch_words,
                                                            int32_t single) {
   __shared__ union {
-    MergeSmem<Cfg0> each;
+    MergeSmem<Cfg0Each> each;
     MergeSmem<Cfg0Once> once;
   } sm;
   __shared__ uint32_t pick;
   static_assert(sizeof(sm.each) == sizeof(sm.once), "what merge_begin wrote is either's");
-  merge_begin<Cfg0>(items, recs, n_items, ctr, single, sm.each);
+  merge_begin<Cfg0Each>(items, recs, n_items, ctr, single, sm.each);
   if (threadIdx.x / kWave == 1) {            // beside the first item's loads
     const uint32_t lane = lane_id();
     const uint32_t looks = single == kQueueItems ? (n_items < kWave ? n_items : static_cast<uint32_t>(kWave)) : 1u;
@@ -2426,7 +2462,7 @@ __global__ __launch_bounds__(Cfg0::NT) void k_merge_either(const JobDev *jobs, c
   if (pick)
     merge_items<Cfg0Once>(jobs, items, recs, tiled, tab, n_items, ctr, scratch, scratch_words, single, sm.once);
   else
-    merge_items<Cfg0>(jobs, items, recs, tiled, tab, n_items, ctr, scratch, scratch_words, single, sm.each);
+    merge_items<Cfg0Each>(jobs, items, recs, tiled, tab, n_items, ctr, scratch, scratch_words, single, sm.each);
 }
 
 // Bits [b0, b1) of a 32-bit word whose first bit is bit wb.
