@@ -1045,11 +1045,12 @@ __device__ __forceinline__ uint32_t bits32(const uint32_t *w, uint32_t x) {
 // places are known and k_head has zeroed the bodies.  A word that this slice
 // does not fill is ORed into zeroed memory, the others are stored.
 //   The first slice's workgroup also lists the block's chunk jobs.
-// Bound by vector instructions (four fifths of the issue slots), about 15 per 64
-// symbols and level, and by the latency of the small levels (two barriers
-// each).  Symbols that end are stored to one unused place instead of being masked
-// off, a place is one shift and add from the rank, and waves take whole groups
-// of 4 chunks: 17 instructions, 1.39 -> 1.31 ms.  256 MiB Zipf(1.1) in 64
+// Bound by vector instructions (four fifths of the issue slots), about 21 per 64
+// symbols and level (522M of the 634M of 256 MiB Zipf(1.1)), and by the latency of
+// the small levels (two barriers each).  Symbols that end are stored to one unused
+// place instead of being masked off, a place is one shift and add from the rank,
+// and waves take whole groups of 4 chunks: 690M -> 634M, 1.39 -> 1.31 ms.  256 MiB
+// Zipf(1.1) in 64
 // KiB blocks: 1.31 ms where one wave per node (the root's 4096 symbols on one
 // wave of four) took 4.15 ms; one 64 KiB block: 18 us, was 86.  LDS holds one
 // level buffer (a level is in registers before it moves) and no more tables
