@@ -73,21 +73,22 @@ struct EncBlock {
   int32_t kbase[16];      // node at depth d with code prefix p: slot p + kbase[d] (in the
                           // split kernel's tables; a prefix without a node takes one too
                           // where a flat-subtree tree has a single leaf among the nodes)
-  uint32_t nfl[16];       // flat nodes per level (the level's first nodes)
+  uint8_t nfl[16];        // flat nodes per level (the level's first nodes)
   uint32_t bit[256];      // node's first bit: in the block's raw image (raw
                           // node) or in its rANS bitmap words (rANS node)
   uint32_t kind[8];       // bit i: node i is rANS-coded
   uint16_t pay[256];      // a symbol's code, left-justified in 16 bits
-  uint16_t lo[256];       // node's leaves [lo, hi), those of its right child
-  uint16_t mid[256];      // [mid, hi)
-  uint16_t hi[256];
-  uint16_t child[256][2]; // internal id, or 0x8000 for a leaf
-  uint16_t slot[256];     // node's slot
+  uint8_t lo[256];        // node's leaves [lo, hi), those of its right child
+  uint8_t mid1[256];      // [mid, hi): mid - 1 and hi - 1
+  uint8_t hi1[256];
+  uint8_t child[256][2];  // internal id, or 255 for a leaf
+  uint8_t slot[256];      // node's slot less its id: the single leaves before it (at most 12)
   uint8_t leaf[256];      // leaf of each symbol (255, never a leaf then, without a code)
   uint8_t depth[256];     // node's level
   uint8_t fd[256];        // flat node: its depth D (>= 2), 0 for binary nodes
 };
 static_assert(sizeof(EncBlock) % 16 == 0, "EncBlock areas stay 16-byte aligned");
+static_assert(sizeof(EncBlock) <= 4048, "a block's share of the workspace (see ws_layout)");
 
 // Per-block layout (k_code), offsets (k_scan) and size (without entropy-coded
 // nodes k_code, else k_sizes and k_scan2).
@@ -740,7 +741,7 @@ __global__ __launch_bounds__(NT) void k_code(
     }
     if (lane < 16) {
       E.kbase[lane] = static_cast<int32_t>(kb_l);
-      E.nfl[lane] = nf_l;
+      E.nfl[lane] = static_cast<uint8_t>(nf_l);
     }
     if (lane == 0) { E.maxlen = levels; E.I = I; E.nleaf = nleaf; }
   }
@@ -842,13 +843,14 @@ __global__ __launch_bounds__(NT) void k_code(
     const uint32_t mid = fd ? hi : (c1 & 0x8000) ? hi - 1 : sm.lo[c1];
     nv = sm.pc[hi] - sm.pc[lo];
     nr = sm.pc[hi] - sm.pc[mid];
-    *reinterpret_cast<uint32_t *>(E.child[t]) = cc;
-    E.lo[t] = static_cast<uint16_t>(lo);
-    E.mid[t] = static_cast<uint16_t>(mid);
-    E.hi[t] = static_cast<uint16_t>(hi);
+    *reinterpret_cast<uint16_t *>(E.child[t]) = static_cast<uint16_t>(((cc & 0x8000) ? 255u : cc & 255) |
+                                                                      ((c1 & 0x8000) ? 255u : c1) << 8);
+    E.lo[t] = static_cast<uint8_t>(lo);
+    E.mid1[t] = static_cast<uint8_t>(mid - 1);
+    E.hi1[t] = static_cast<uint8_t>(hi - 1);
     E.depth[t] = static_cast<uint8_t>(d);
     E.fd[t] = static_cast<uint8_t>(fd);
-    E.slot[t] = static_cast<uint16_t>(slot);
+    E.slot[t] = static_cast<uint8_t>(slot - t);
     if (!fd) {
       if (ans_mode == 3) mk = fse_marker(nv, nr, d, fse_dmax);
       kd = (ans_mode == 3 ? mk != 0 : select_ans(ans_mode, nv, nr)) ? 1u : 0u;
@@ -1100,11 +1102,11 @@ __global__ __launch_bounds__(NT) void k_split(const uint8_t *in, const EncBlock 
     leaf = B.leaf[tid];
     pay = B.pay[tid];
     lo = B.lo[tid];
-    mid = B.mid[tid];
-    hi = B.hi[tid];
-    cc = *reinterpret_cast<const uint32_t *>(B.child[tid]);
+    mid = B.mid1[tid] + 1u;
+    hi = B.hi1[tid] + 1u;
+    cc = *reinterpret_cast<const uint16_t *>(B.child[tid]);
     d = B.depth[tid];
-    slot = B.slot[tid];
+    slot = B.slot[tid] + tid;
     if (FLAT) fd = B.fd[tid];
     nbit = B.bit[tid];
     rans = (B.kind[tid >> 5] >> (tid & 31)) & 1;
@@ -1205,9 +1207,9 @@ __global__ __launch_bounds__(NT) void k_split(const uint8_t *in, const EncBlock 
   if (node) {
     const uint32_t l0 = sm.lvl[d], l1 = sm.lvl[d + 1];
     const uint32_t seg = tv - sm.T[l0], rs = ones - sm.O[l0], t1 = sm.T[l1];
-    const uint32_t c0 = cc & 0xFFFF, c1 = cc >> 16;
-    const uint32_t k0 = (c0 & 0x8000) ? kEndsHere : 2 * (sm.T[c0 & 255] - t1 - seg + rs) & 0xFFFF;
-    const uint32_t k1 = (c1 & 0x8000) ? kEndsHere : 2 * (sm.T[c1 & 255] - t1 - rs) & 0xFFFF;
+    const uint32_t c0 = cc & 255, c1 = cc >> 8;
+    const uint32_t k0 = c0 == 255 ? kEndsHere : 2 * (sm.T[c0] - t1 - seg + rs) & 0xFFFF;
+    const uint32_t k1 = c1 == 255 ? kEndsHere : 2 * (sm.T[c1] - t1 - rs) & 0xFFFF;
     reinterpret_cast<uint32_t *>(sm.K)[slot] = k0 | (k1 << 16);
     const uint32_t sb = FLAT && fd ? 64 * all64 + fx : 64 * lw_d + seg;
     if (FLAT) sm.F[slot] = ((sb - fd * seg) & 0xFFFFFF) | (fd << 24);   // bit sb + D (p - seg)
@@ -1767,7 +1769,10 @@ struct WsLayout {
 };
 
 // Sizes from n and the options alone (the data is not known yet): every
-// area is bounded by the code-length limit and the block count.
+// area is bounded by the code-length limit and the block count.  A block's tables
+// are kept so small that no n and options need more than when the lengths (260
+// bytes a block), codes (3520) and, without entropy-coded nodes too, an image lay
+// here: a workspace of that size still serves.
 WsLayout ws_layout(uint64_t n, const pivco_encode_opts *o) {
   WsLayout L{};
   const uint64_t nb = div_up(n, o->block_size);
@@ -1784,7 +1789,7 @@ WsLayout ws_layout(uint64_t n, const pivco_encode_opts *o) {
   L.lay = x; x = align_up(x + nb * sizeof(BlockLay), 256);
   L.rnodes = x; x = align_up(x + (o->ans_mode ? nb * 255 * sizeof(RansNode) : 0), 256);
   L.hdr = x; x = align_up(x + nb * kHdrStride, 256);
-  L.img = x; x = align_up(x + bits / 8 + nb * (255 + 32) + 64, 256);
+  L.img = x; x = align_up(x + (o->ans_mode ? bits / 8 + nb * (255 + 32) : 0) + 64, 256);
   L.rbm = x; x = align_up(x + (o->ans_mode ? 4 * (bits / 32 + nb * (255 + 4)) : 0) + 64, 256);
   L.jobs = x; x = align_up(x + chunks * sizeof(RansJob), 256);
   L.sizes = x; x = align_up(x + chunks * 4, 256);
