@@ -147,8 +147,9 @@ pivco_status pivco_encode(const void *d_in, uint64_t n, void *d_out, uint64_t ou
  * needs also when it exceeds out_cap) and the call's status to *d_status (a
  * device int32: PIVCO_OK, E_ARG for a supplied tree that misses a present
  * symbol, E_CAPACITY when the stream exceeds out_cap -- then nothing is
- * written to d_out -- or E_UNSUPPORTED as above).  Argument errors are
- * returned at once.  Workspace and bound as for pivco_encode. */
+ * written to d_out -- or E_UNSUPPORTED as above).  Both may be written before
+ * the last of the stream's bytes: all are there once the work on s has completed.
+ * Argument errors are returned at once.  Workspace and bound as for pivco_encode. */
 pivco_status pivco_encode_async(const void *d_in, uint64_t n, void *d_out, uint64_t out_cap,
                                 uint64_t *d_out_len, int32_t *d_status, const pivco_encode_opts *o,
                                 void *d_ws, uint64_t ws_bytes, hipStream_t s);

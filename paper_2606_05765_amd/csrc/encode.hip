@@ -1052,9 +1052,9 @@ __device__ __forceinline__ uint32_t bits32(const uint32_t *w, uint32_t x) {
 // the small levels (two barriers each).  Symbols that end are stored to one unused
 // place instead of being masked off, a place is one shift and add from the rank,
 // and waves take whole groups of 4 chunks: 690M -> 634M, 1.39 -> 1.31 ms.  256 MiB
-// Zipf(1.1) in 64
-// KiB blocks: 1.31 ms where one wave per node (the root's 4096 symbols on one
-// wave of four) took 4.15 ms; one 64 KiB block: 18 us, was 86.  LDS holds one
+// Zipf(1.1) in 64 KiB blocks: 1.31 ms where one wave per node (the root's 4096
+// symbols on one wave of four) took 4.15 ms; one 64 KiB block: 18 us, was 86.  LDS
+// holds one
 // level buffer (a level is in registers before it moves) and no more tables
 // than the levels need, for 6 workgroups of 256 threads on a CU: with two
 // buffers and the tables beside them (4 workgroups) and the block's tables
